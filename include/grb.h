@@ -465,12 +465,13 @@ grb_info grb_pagerank_adaptive(void *p, grb_type type, grb_matrix A, double damp
  * for every vertex, the smallest vertex id of its component (weak
  * components of a directed matrix: A must then carry the CSR of A^T, else
  * GRB_NOT_IMPLEMENTED).  Each iteration takes the smallest grandparent among
- * the neighbours with grb_mxv over MIN_SECOND (accumulated with min), then
+ * the neighbours (the product over MIN_SECOND, accumulated with min), then
  * hooks the old parent and the vertex to it, shortcuts to the grandparent
  * and recomputes the grandparents; it stops once no grandparent changes or
  * after d->max_iter iterations (0 = no cap).  *iters (may be
  * NULL) receives the iterations run.  The descriptor may carry no flags but
- * GRB_PROFILE; its direction and switch rule apply to the products.
+ * GRB_PROFILE; its direction and switch rule are accepted and change nothing
+ * (the product is always a pull).
  * Workspace: GRB_OP_CC.  Synchronises once per batch of iterations.
  */
 grb_info grb_cc(int32_t *labels, grb_matrix A, int32_t *iters, const grb_descriptor *d,

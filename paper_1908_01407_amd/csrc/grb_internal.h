@@ -391,16 +391,17 @@ void launch_msbfs_session_join(const MsbfsArgs &a, const int32_t *lanes, const i
 void launch_msbfs_session_extract(const MsbfsArgs &a, const int32_t *lanes, int32_t count,
                                   int32_t *out, void *stream);
 
-// connected components (grb_cc.hip): FastSV vectors in the workspace
+// connected components (grb_cc.hip): FastSV vectors in the workspace; gf is
+// the caller's label array (at the end every vertex's grandparent is its label)
 struct CcArgs {
   int64_t n = 0, nw = 0;
-  int32_t *f = nullptr, *f_old = nullptr, *gf = nullptr, *mngf = nullptr, *labels = nullptr;
-  uint64_t *gf_bm = nullptr, *mngf_bm = nullptr;
+  int32_t *f = nullptr, *f_old = nullptr, *gf = nullptr, *mngf = nullptr;
+  int32_t *floor = nullptr;    // the smallest vertex id that has an entry
   int64_t *changed = nullptr;  // per iteration: vertices whose grandparent changed
 };
-void launch_cc_init(const CcArgs &a, void *stream);
-void launch_cc_step(const CcArgs &a, int32_t it, void *stream);  // hooking .. grandparents
-void launch_cc_out(const CcArgs &a, void *stream);
+// gt: the transpose of a directed matrix (weak components), else nullptr
+void launch_cc_init(const CcArgs &a, const Csr &g, const Csr *gt, void *stream);
+void launch_cc_step(const CcArgs &a, const Csr &g, const Csr *gt, int32_t it, void *stream);
 
 // generic masked products (grb_mxv.hip)
 struct MxvArgs {
