@@ -365,11 +365,12 @@ grb_info grb_vxm(grb_vector w, grb_vector mask, grb_binop accum, grb_semiring s,
  * keeps that depth (an atomic int, so concurrent calls on one matrix stay
  * safe; it affects speed only).  d->max_iter caps the levels (0 = none).
  * On graphs whose rows are short (at most 64 entries: road-like, high
- * diameter) the levels run back to back inside one kernel of 16 workgroups,
- * separated by a barrier of its own, while the frontier is small (a launch
- * per level would dominate); a frontier that outgrows its queues (more
- * than 256 vertices found by one wave of 64 lanes, or 65,536 edges), that
- * the switch rule would pull, or a barrier not reached by every workgroup
+ * diameter) and of at most 201 million vertices the levels run back to back
+ * inside one kernel of 1 to 256 workgroups, which exchange their finds after
+ * each level, while the frontier is small (a launch per level would
+ * dominate); a frontier that outgrows its queues (4,096 vertices of one
+ * workgroup, a few hundred found by one for another, or 65,536 edges), that
+ * the switch rule would pull, or an exchange not reached by every workgroup
  * within 1 ms, continues with one kernel per level.  Results do not depend
  * on where that hand-over happens.
  */

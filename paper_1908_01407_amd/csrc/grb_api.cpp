@@ -75,10 +75,41 @@ struct BfsWs {
   int32_t *qv;
   uint64_t *qe;
   int32_t qseg;
+  BfsOwn own;     // BFS loop: laid over the queues
   size_t bytes;
 };
 
-BfsWs bfs_layout(void *ws, int64_t n) {
+// The BFS loop's workgroups for n vertices (0: too many for the loop).  Us
+// per level with 1 / 8 / 16 / 32 workgroups: 300 x 300 grid 1.82 / 2.53 /
+// 2.66 / 2.85, 700 x 700 3.31 / 2.38 / 2.55 / 2.69, 2003 x 1009 - / 2.61 /
+// 2.44 / 2.64, 3000 x 3000 - / - / 3.35 / 2.94: one workgroup needs no
+// exchange, and a frontier grows about as the root of n.
+int own_groups(int64_t n) {
+  int g = n <= (1 << 18) ? 1 : (n <= (1 << 20) ? 8 : (n <= (1 << 22) ? 16 : 32));
+  while (g <= kOwnMaxGroups && (n + g - 1) / g > kOwnVertices - 64) g *= 2;
+  return g <= kOwnMaxGroups ? g : 0;
+}
+
+BfsOwn own_layout(Carver c, int64_t n, int groups, size_t *end = nullptr) {
+  BfsOwn o{};
+  o.groups = groups;
+  if (!groups) return o;
+  o.chunk = (int)align_up((size_t)std::max<int64_t>((n + groups - 1) / groups, 1), 64);
+  o.inv_chunk = 1.0f / (float)o.chunk;
+  // box capacities: 512 KB of boxes up to 16 workgroups, 768 KB for 32
+  o.cap = std::min(groups <= 16 ? kOwnCapMax : (groups <= 32 ? 92 : 64), o.chunk);
+  o.nrec = (int64_t)4 * groups * groups + 4 * groups;
+  o.rec = c.take<uint64_t>((size_t)o.nrec);
+  o.rec_edges = o.rec + (int64_t)4 * groups * groups;
+  o.rec2 = o.rec_edges + 2 * groups;
+  o.box = c.take<int32_t>((size_t)2 * groups * groups * o.cap);
+  if (end) *end = c.off;
+  return o;
+}
+
+constexpr int kOwnTestGroups = 4;
+
+BfsWs bfs_layout(void *ws, int64_t n, int min_groups = 1) {
   Carver c(ws);
   BfsWs t{};
   const int64_t nw = words_of(n);
@@ -89,9 +120,18 @@ BfsWs bfs_layout(void *ws, int64_t n) {
   t.qseg = (int32_t)std::max<int64_t>(std::min<int64_t>(kCoopSeg, n), 1);
   t.coop = c.take<CoopCtl>(1);
   const size_t qn = 2 * (size_t)kCoopSegsMax * (size_t)t.qseg;
+  const size_t queues = c.off;
   t.qv = c.take<int32_t>(qn);
   t.qe = c.take<uint64_t>(qn);
-  t.bytes = c.off;
+  // the loop's buffers lie over the queues (SSSP's), with room for at least
+  // four workgroups (min_groups, for GRB_LOOP_NO_WAIT)
+  const int groups = own_groups(n);
+  Carver o(ws);
+  o.off = queues;
+  size_t end = 0;
+  own_layout(o, n, groups ? std::max(groups, kOwnTestGroups) : 0, &end);
+  t.own = own_layout(o, n, groups ? std::max(groups, min_groups) : 0);
+  t.bytes = std::max(c.off, end);
   return t;
 }
 
@@ -537,7 +577,8 @@ grb_info run_bfs(grb_matrix A, int32_t source, int32_t *levels, int32_t *parents
   const int64_t n = A->nrows;
   const bool can_pull = A->at.valid();
   if (!can_pull && (desc.direction == GRB_DIR_PULL || parents)) return GRB_NOT_IMPLEMENTED;
-  BfsWs w = bfs_layout(ws, n);
+  // (a barrier that one workgroup alone arrives at is never unfinished)
+  BfsWs w = bfs_layout(ws, n, (desc.flags & GRB_LOOP_NO_WAIT) ? kOwnTestGroups : 1);
   grb_info info = check_ws(ws, ws_bytes, w.bytes);
   if (info != GRB_SUCCESS) return info;
   hipStream_t s = (hipStream_t)stream;
@@ -583,19 +624,15 @@ grb_info run_bfs(grb_matrix A, int32_t source, int32_t *levels, int32_t *parents
   // multi-workgroup loop while the frontier is small (no launch per level);
   // a frontier that outgrows it, or a barrier it gave up, continues with the
   // level kernel below.
-  const bool small = A->a.max_deg <= kCoopMaxDeg && desc.direction != GRB_DIR_PULL;
-  if (small) {
-    ba.coop = w.coop;
-    ba.qv = w.qv;
-    ba.qe = w.qe;
-    ba.qseg = w.qseg;
-  }
+  const bool small = A->a.max_deg <= kCoopMaxDeg && desc.direction != GRB_DIR_PULL &&
+                     w.own.groups > 0;
+  if (small) ba.own = w.own;
   launch_bfs_start(ba, source, w.F[1], w.F[2], stream);
   if (small) {
     if (profile) (void)hipEventRecord(g_events.get(0), s);
     uint64_t *F[3] = {w.F[0], w.F[1], w.F[2]};
-    launch_bfs_coop(ba, source, cap, F, (desc.flags & GRB_LOOP_NO_WAIT) ? 0 : kCoopWaitTicks,
-                    stream);
+    launch_bfs_own(ba, source, cap, F, (desc.flags & GRB_LOOP_NO_WAIT) ? 0 : kCoopWaitTicks,
+                   stream);
     if (profile) (void)hipEventRecord(g_events.get(1), s);
     launch_level.push_back(0);
     launches = 1;

@@ -29,21 +29,15 @@
 // the search.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "grb_device.h"
 #include "grb_internal.h"
 
 namespace grb {
 namespace {
 
-// multi-workgroup loop of this file: workgroups, queue segments (one per
-// wave), segment counts read per lane of one wave
-constexpr int kCoopGrid = kCoopGridBfs;
-constexpr int kCoopSegs = kCoopGrid * (kCoopThreads / 64);
-constexpr int kCoopSegsPerLane = kCoopSegs / 64;
-static_assert(kCoopSegs % 64 == 0 && kCoopSegs <= kCoopSegsMax,
-              "segment counts are read by one wave");
-
-__device__ __forceinline__ int decide(const BfsArgs &a, int count, int sumdeg) {
+__device__ __forceinline__ int decide(const BfsArgs &a, int64_t count, int64_t sumdeg) {
   if (a.forced) return a.forced;
   if (!a.can_pull) return GRB_DIR_PUSH;
   const bool pull = a.rule == GRB_SWITCH_EXACT ? (int64_t)a.denom * sumdeg > a.nnz
@@ -838,6 +832,7 @@ __global__ __launch_bounds__(kBlock) void k_bfs_start(BfsArgs a, int32_t source,
     f1[w] = 0ull;
     f2[w] = 0ull;
   }
+  for (int64_t i = tid; i < a.own.nrec; i += nt) a.own.rec[i] = 0ull;  // no tag
   if (tid == 0) {
     for (int i = 0; i < kCntSlots; ++i) {
       a.cnt_cur[i] = 0;
@@ -850,226 +845,667 @@ __global__ __launch_bounds__(kBlock) void k_bfs_start(BfsArgs a, int32_t source,
     a.cnt_cur[0] = 1;  // level 0 = {source}
     a.cnt_cur[1] = ds;
     a.cnt_cur[2] = ds > kPushSplit ? 1 : 0;
-    if (a.coop) {  // the multi-workgroup loop's first queue: {source}
-      a.coop->bar = 0ull;
-      for (int i = 0; i < kCoopSegsMax; ++i) a.coop->cnt[0][i] = a.coop->esum[0][i] = 0;
-      a.coop->cnt[0][0] = 1;
-      a.coop->esum[0][0] = ds;
-      a.qv[0] = source;
-      a.qe[0] = ((uint64_t)(uint32_t)ds << 32) | (uint32_t)a.push.rp[source];
-    }
+    a.ctrl->small_levels = INT_MAX;
+    a.ctrl->spilled = 0;
   }
 }
 
 // ---- multi-workgroup level loop for small frontiers -------------------------
-// Level d: workgroup w takes the entries [w nc / G, (w + 1) nc / G) of the
-// level's queue, a thread per entry.  The queue has one segment per wave of
-// the loop; an entry is found through the prefix of the segments' counts.
-// The thread writes the entry's level (deferred from the level that found
-// it, so the store overlaps this level's loads), claims the targets of four
-// out-edges per step with one atomicOr on their visited words (their row
-// extents loaded beside), and queues the winners in its wave's segment of
-// the next queue.  Entries past a segment's capacity get their level and go
-// straight into the next frontier's bitmap (the loop then spills that
-// frontier).  No counter is shared: each wave stores its segment's count
-// and degree sum with its entries, before the barrier.
-__global__ __launch_bounds__(kCoopThreads) void k_bfs_coop(BfsArgs a, int64_t max_levels,
-                                                           uint64_t wait_ticks, uint64_t *F0,
-                                                           uint64_t *F1, uint64_t *F2) {
-  __shared__ int s_pre[kCoopSegs + 1];
-  __shared__ int s_nc, s_ne, s_ovf, s_go;
-  const int tid = threadIdx.x, ln = tid & 63;
-  const int32_t *rp = a.push.rp, *ci = a.push.ci;
-  CoopCtl *cc = a.coop;
-  const int w = (int)blockIdx.x;
-  const int my_seg = w * (kCoopThreads / 64) + (tid >> 6);
-  const int seg = a.qseg, qsize = kCoopSegs * seg;
-  int64_t d = 0;
-  bool spill = false;
-  for (;;) {
-    const int sl = (int)(d & 1);
-    if (tid < 64) {  // the level's queue: segment counts, their prefix, degree sums
-      // lane l holds segments kCoopSegsPerLane * l + r
-      int c[kCoopSegsPerLane], csum = 0, esum = 0;
-      bool over = false;
+// High-diameter graphs spend thousands of levels on a few thousand vertices
+// each, so a level's time is its chain of dependent memory round trips, not
+// its work.  Workgroup w of the loop's G owns the vertices [w * chunk, (w + 1)
+// * chunk): their visited bits sit in its LDS, it alone claims them (LDS
+// atomics), and its share of the frontier is a queue in its LDS.  Level d:
+// * the out-edges of its queue (a thread per vertex, four columns at a time):
+//   an owned target is claimed at once and queued for level d + 1, another
+//   one is sent to its owner;
+// * wave 0 exchanges records with the other workgroups, while the other
+//   waves write the levels of the newly queued vertices and load their row
+//   extents and first columns for the next level;
+// * the targets received are claimed and queued.
+// On a graph whose ids follow its structure (grids, road networks in
+// geographic order) nearly all targets are owned, and a level is the longer
+// of the exchange and the two dependent loads beside it.
+//
+// The exchange needs no barrier and no atomics: workgroup s stores, for every
+// owner o, a head (the number of targets sent and the first two of them) and
+// a total (entries, queued, sent, full), 8-byte words that each carry the
+// level's tag, and o polls the G words written for it.  Further targets go
+// to a box in device memory, whose stores complete before the heads are
+// written.  The words of level d are overwritten at d + 2, when every
+// workgroup has read them (it published level d + 1 afterwards).
+//
+// All workgroups see the same totals.  The targets sent may be visited
+// already or sent twice, so the next frontier holds at most queued + sent
+// vertices: while that bound keeps every queue, the loop's edge limit and
+// the switch rule's push, the next level starts at once; otherwise a second
+// exchange gives the exact sizes, and a frontier that outgrew the loop or
+// that the rule would pull is handed to the level kernels.
+//
+// No wait is unbounded: a workgroup that has polled for wait_ticks leaves the
+// loop.  The others cannot pass the next exchange without it, so they leave
+// one level later at most; the hand-over continues from the earliest of the
+// levels (ctrl->small_levels), whose frontier is complete (every workgroup
+// had published the level before it), and drops what was found beyond.
+// Every step of a level is a short serial chain in one wave (a dependent
+// vector instruction takes 5.5 ns here, an LDS access 25), so the loop keeps
+// scans and 64-bit arithmetic off the usual path: slots come from ballots,
+// and the totals are judged by ballots against a per-workgroup share of the
+// bounds before any sum is taken.
+struct OwnShared {
+  uint32_t vis[kOwnVertices / 32];
+  int q[2][kOwnQueue];
+  int cnt[2];              // entries found by the expansion into each queue
+  int out[kOwnMaxGroups];  // targets sent to each workgroup in this level
+  int msg[kOwnMaxGroups][2];   // the first two of each
+  int pre[kOwnMaxGroups + 1];  // prefix of the boxes' further targets
+  int sent;                // targets sent
+  int edges;               // degree sum of the level's entries
+  int ovf;                 // a queue or box was full
+  int n_new;               // entries of the next level
+  int state, nin, nc, ne, any_ovf;
+};
+enum OwnState { kOwnGo = 0, kOwnDone = 1, kOwnExact = 2, kOwnGaveUp = 3 };
+
+__device__ __forceinline__ int own_sum(int x) { return lane_last(wave_incl_scan(x)); }
+
+// record words (16-bit tag at the top; a tag is never 0, which the start
+// kernel leaves)
+__device__ __forceinline__ uint32_t own_tag(int64_t level) {  // of level L: 1 + L mod 65535
+  return 1u + (uint32_t)level % 65535u;
+}
+__device__ __forceinline__ uint64_t own_head(uint32_t tag, int cnt, int m0, int m1) {
+  return ((uint64_t)((tag << 16) | ((uint32_t)cnt << 8) | ((uint32_t)m0 >> 12)) << 32) |
+         (((uint32_t)m0 << 20) | (uint32_t)m1);
+}
+__device__ __forceinline__ int head_cnt(uint64_t h) { return (int)(h >> 40) & 255; }
+__device__ __forceinline__ int head_m0(uint64_t h) { return (int)(h >> 20) & 0xfffff; }
+__device__ __forceinline__ int head_m1(uint64_t h) { return (int)h & 0xfffff; }
+__device__ __forceinline__ uint64_t own_total(uint32_t tag, int n, int won, int sent, int ovf) {
+  return ((uint64_t)((tag << 16) | (uint32_t)n) << 32) |
+         (((uint64_t)won << 19) + ((uint64_t)sent << 1)) | (uint64_t)ovf;
+}
+__device__ __forceinline__ int total_n(uint64_t t) { return (int)(t >> 32) & 8191; }
+__device__ __forceinline__ int total_won(uint64_t t) { return (int)((uint32_t)t >> 19); }
+__device__ __forceinline__ int total_sent(uint64_t t) { return (int)((uint32_t)t >> 1) & 0x3ffff; }
+static_assert(kOwnVertices <= 1 << 20 && kOwnQueue < 1 << 13 && kOwnCapMax < 256 &&
+                  kCoopEdges < 1 << 18,  // (a level has at most kCoopEdges edges)
+              "fields of the record words");
+
+// Queues the winners among c[0..K) at *cnt of queue q (all 64 lanes call it);
+// vertices past its end go straight into the next frontier's bitmap with
+// their level.  One LDS atomic per wave: one per lane serialises on the
+// counter (1.8 instead of 0.9 us per level).
+template <int K>
+__device__ __forceinline__ void own_queue(const BfsArgs &a, OwnShared &sh, int *cnt, int *q,
+                                          uint64_t *fn, int level, const int (&c)[K],
+                                          const bool (&won)[K]) {
+  uint64_t b[K];
+  int tot = 0;
 #pragma unroll
-      for (int r = 0; r < kCoopSegsPerLane; ++r) {
-        c[r] = ld_coherent(&cc->cnt[sl][kCoopSegsPerLane * tid + r]);
-        esum += ld_coherent(&cc->esum[sl][kCoopSegsPerLane * tid + r]);
-        csum += c[r];
-        over |= c[r] > seg;
-      }
-      const int incl = wave_incl_scan(csum);
-      int run = incl - csum;
-#pragma unroll
-      for (int r = 0; r < kCoopSegsPerLane; ++r) {
-        run += c[r];
-        s_pre[kCoopSegsPerLane * tid + r + 1] = run;
-      }
-      const int tot = lane_last(incl), etot = wave_sum(esum);
-      const bool ovf = __ballot(over) != 0ull;
-      if (tid == 0) {
-        s_pre[0] = 0;
-        s_nc = tot;
-        s_ne = etot;
-        s_ovf = ovf ? 1 : 0;
-      }
-    }
-    __syncthreads();
-    const int nc = s_nc, ne = s_ne;
-    if (nc == 0 || d >= max_levels) break;
-    // a frontier that outgrew its segments, or one the switch rule would
-    // pull, goes to the level kernel
-    if (s_ovf || ne > kCoopEdges || d >= kCoopMaxLevels || decide(a, nc, ne) == GRB_DIR_PULL) {
-      spill = true;
-      break;
-    }
-    if (w == 0 && tid == 0) {
-      a.ctrl->nlev = (int)d + 1;
-      if (a.stats && d < kStatsCap) {
-        a.stats[d * kStatFields + 0] = nc;
-        a.stats[d * kStatFields + 1] = ne;
-        a.stats[d * kStatFields + 2] = GRB_DIR_PUSH;
-      }
-    }
-    const int qin = sl * qsize, qout = (sl ^ 1) * qsize + my_seg * seg;
-    const int sx = (int)((d + 1) % 3);
-    uint64_t *fn = sx == 0 ? F0 : (sx == 1 ? F1 : F2);
-    const int lo = (int)((int64_t)nc * w / kCoopGrid);
-    const int hi = (int)((int64_t)nc * (w + 1) / kCoopGrid);
-    int wcnt = 0, wsum = 0;  // this wave's appends (uniform over the wave)
-    for (int base = lo; base < hi; base += kCoopThreads) {
-      const int i = base + tid;
-      int rs = 0, dg = 0;
-      if (i < hi) {
-        int s = 0;  // segment holding entry i: the last s with s_pre[s] <= i
-#pragma unroll
-        for (int step = kCoopSegs / 2; step > 0; step >>= 1)
-          if (s_pre[s + step] <= i) s += step;
-        const int at = qin + s * seg + (i - s_pre[s]);
-        const int v = ld_coherent(a.qv + at);
-        const uint64_t e = load_relaxed_u64(a.qe + at);
-        rs = (int)(uint32_t)e;
-        dg = (int)(e >> 32);
-        if (d > 0) a.levels[v] = (int)d;
-      }
-      for (int q0 = 0; __ballot(q0 < dg) != 0ull; q0 += 4) {
-        int c[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) c[q] = q0 + q < dg ? ci[rs + q0 + q] : -1;
-        uint64_t old[4];
-        int r0[4], r1[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          old[q] = ~0ull;
-          r0[q] = r1[q] = 0;
-          if (c[q] >= 0) {
-            old[q] = atomicOr((unsigned long long *)&a.visited[c[q] >> 6], 1ull << (c[q] & 63));
-            r0[q] = rp[c[q]];
-            r1[q] = rp[c[q] + 1];
-          }
-        }
-        bool won[4];
-        int nw = 0, wdeg = 0;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          won[q] = c[q] >= 0 && !((old[q] >> (c[q] & 63)) & 1ull);
-          nw += won[q] ? 1 : 0;
-          wdeg += won[q] ? r1[q] - r0[q] : 0;
-        }
-        const int incl = wave_incl_scan(nw);
-        const int tot = lane_last(incl);
-        if (tot == 0) continue;
-        int slot = wcnt + incl - nw;
-        wcnt += tot;
-        wsum += wave_sum(wdeg);
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          if (!won[q]) continue;
-          if (slot < seg) {
-            st_coherent(a.qv + qout + slot, c[q]);
-            store_relaxed_u64(a.qe + qout + slot,
-                              ((uint64_t)(uint32_t)(r1[q] - r0[q]) << 32) | (uint32_t)r0[q]);
-          } else {
-            a.levels[c[q]] = (int)d + 1;
-            atomicOr((unsigned long long *)&fn[c[q] >> 6], 1ull << (c[q] & 63));
-          }
-          ++slot;
-        }
-      }
-    }
-    // the wave's segment count and degree sum go with its entries; the
-    // barrier follows once every memory operation of the workgroup is done
-    if (ln == 0) {
-      st_coherent(&cc->cnt[sl ^ 1][my_seg], wcnt);
-      st_coherent(&cc->esum[sl ^ 1][my_seg], wsum);
-    }
-    __builtin_amdgcn_s_waitcnt(0);
-    __syncthreads();
-    if (tid == 0) s_go = coop_barrier(&cc->bar, kCoopGrid, d, wait_ticks);
-    __syncthreads();
-    ++d;
-    if (!s_go) {
-      // barrier given up: the frontier of level d (found by every
-      // workgroup before the barrier) goes to the level kernel
-      spill = true;
-      break;
-    }
+  for (int k = 0; k < K; ++k) {
+    b[k] = __ballot(won[k]);
+    tot += __popcll(b[k]);
   }
-  if (w == 0 && tid == 0) {
-    a.ctrl->small_levels = (int)d;
-    a.ctrl->spilled = spill ? 1 : 0;
+  if (tot == 0) return;
+  int base = 0;
+  if ((threadIdx.x & 63) == 0) base = atomicAdd(cnt, tot);
+  base = __builtin_amdgcn_readfirstlane(base);
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    const int slot =
+        base + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(b[k] >> 32),
+                                              __builtin_amdgcn_mbcnt_lo((uint32_t)b[k], 0));
+    base += __popcll(b[k]);
+    if (!won[k]) continue;
+    if (slot < kOwnQueue) {
+      q[slot] = c[k];
+    } else {
+      a.levels[c[k]] = level;
+      atomicOr((unsigned long long *)&fn[c[k] >> 6], 1ull << (c[k] & 63));
+      sh.ovf = 1;
+    }
   }
 }
 
-// After the loop: the frontier it left in its queue (level h =
-// ctrl->small_levels, whose levels are not written yet) gets its levels;
-// when the loop spilled it, it also becomes the bitmap and counters of
-// level h for the level kernel (the entries past a segment's capacity are
-// in the bitmap already).
-__global__ __launch_bounds__(kBlock) void k_bfs_coop_handover(BfsArgs a, int32_t source,
-                                                               uint64_t *F0, uint64_t *F1,
-                                                               uint64_t *F2) {
-  const bool spilled = a.ctrl->spilled != 0;
-  const int64_t h = a.ctrl->small_levels;
-  uint64_t *fh = (h % 3 == 0) ? F0 : ((h % 3 == 1) ? F1 : F2);
-  const int sl = (int)(h & 1), seg = a.qseg, qsize = kCoopSegs * seg;
-  const int32_t *qv = a.qv + sl * qsize;
-  for (int t = blockIdx.x * kBlock + threadIdx.x; t < qsize; t += gridDim.x * kBlock) {
-    const int s = t / seg, j = t - s * seg;
-    if (j < a.coop->cnt[sl][s]) {
-      const int v = qv[t];
-      if (h > 0) a.levels[v] = (int)h;
-      if (spilled) atomicOr((unsigned long long *)&fh[v >> 6], 1ull << (v & 63));
+// Claims the owned targets among c[0..4) (all four LDS atomics are issued
+// before a result is used), sends the others to their owners and queues the
+// claims won.
+__device__ __forceinline__ void own_expand(const BfsArgs &a, OwnShared &sh, int lo, int nv, int w,
+                                           int *cnt, int *q, uint64_t *fn, int32_t *box, int level,
+                                           const int (&c)[4]) {
+  uint32_t old[4];
+  bool far = false;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const uint32_t l = (uint32_t)(c[k] - lo);  // (no target: beyond nv)
+    const bool own = l < (uint32_t)nv;
+    far |= c[k] >= 0 && !own;
+    old[k] = ~0u;
+    if (own) old[k] = atomicOr(&sh.vis[l >> 5], 1u << (l & 31));
+  }
+  if (__ballot(far)) {
+    const int G = a.own.groups, cap = a.own.cap;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      if (c[k] < 0 || (uint32_t)(c[k] - lo) < (uint32_t)nv) continue;
+      int o = (int)((float)c[k] * a.own.inv_chunk);  // off by one at most
+      int m = c[k] - o * a.own.chunk;
+      if (m < 0) {
+        --o;
+        m += a.own.chunk;
+      } else if (m >= a.own.chunk) {
+        ++o;
+        m -= a.own.chunk;
+      }
+      const int slot = atomicAdd(&sh.out[o], 1);
+      atomicAdd(&sh.sent, 1);
+      if (slot < 2) {
+        sh.msg[o][slot] = m;
+      } else if (slot < cap) {
+        st_coherent(&box[((int64_t)w * G + o) * cap + slot], c[k]);
+      } else {  // box full: into the bitmap, sorted out by the hand-over
+        atomicOr((unsigned long long *)&fn[c[k] >> 6], 1ull << (c[k] & 63));
+        sh.ovf = 1;
+      }
     }
   }
-  if (spilled && blockIdx.x == 0 && threadIdx.x == 0) {
-    // the start kernel's source bit in F0 is the only other bit set
-    // (h > 0: the source is not in this frontier)
-    if (h > 0) atomicAnd((unsigned long long *)&F0[source >> 6], ~(1ull << (source & 63)));
-    int nq = 0, ne = 0;
-    for (int s = 0; s < kCoopSegs; ++s) {
-      nq += a.coop->cnt[sl][s];
-      ne += a.coop->esum[sl][s];
+  bool won[4];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const uint32_t l = (uint32_t)(c[k] - lo);
+    won[k] = !((old[k] >> (l & 31)) & 1u);
+  }
+  own_queue(a, sh, cnt, q, fn, level, c, won);
+}
+
+// R: polled records per lane of wave 0 (G <= 64 R).  `most`: a frontier of at
+// most this many vertices is within the edge limit and one the rule pushes;
+// `share`: a level in which no workgroup found and sent more than this keeps
+// that bound and every queue.
+template <int R>
+__global__ __launch_bounds__(kOwnThreads) void k_bfs_own(BfsArgs a, int32_t source,
+                                                         int max_levels, uint64_t wait_ticks,
+                                                         int most, int share, uint64_t *F0,
+                                                         uint64_t *F1, uint64_t *F2) {
+  __shared__ OwnShared sh;
+  constexpr int T = kOwnThreads - 64;  // threads that take queue entries (waves 1, 2, ...)
+  const int tid = threadIdx.x, ln = tid & 63;
+  const int et = tid - 64;  // this thread's first entry (wave 0 takes none)
+  const int w = (int)blockIdx.x, G = a.own.groups, cap = a.own.cap;
+  const int32_t *rp = a.push.rp, *ci = a.push.ci;
+  const int64_t first = (int64_t)w * a.own.chunk;
+  const int lo = (int)(first < a.n ? first : a.n);
+  const int nv = (int)(a.n - lo < a.own.chunk ? a.n - lo : a.own.chunk);  // vertices owned
+  // visited bits as the start kernel left them (rows nothing reaches, source)
+  for (int i = tid; i < (nv + 31) / 32; i += kOwnThreads)
+    sh.vis[i] = reinterpret_cast<const uint32_t *>(a.visited)[lo / 32 + i];
+  if (tid < kOwnMaxGroups) sh.out[tid] = sh.msg[tid][0] = sh.msg[tid][1] = 0;
+  const bool mine = source >= lo && source - lo < nv;
+  if (tid == 0) {
+    sh.cnt[0] = sh.cnt[1] = 0;
+    sh.sent = sh.edges = sh.ovf = 0;
+    sh.q[0][0] = source;
+  }
+  __syncthreads();
+  int n = mine ? 1 : 0, npre = 0;  // entries of this level, of them prefetched
+  int prs = 0, pdg = 0, pc[4] = {-1, -1, -1, -1};  // this thread's prefetched entry
+  // per level parity: boxes, records written and read by this lane, and what
+  // rotates with the level, kept in registers (the address and modulo
+  // arithmetic would otherwise open every level)
+  int32_t *box = a.own.box, *box1 = box + (int64_t)G * G * cap;
+  uint64_t *put = a.own.rec + 2 * ((int64_t)ln * G + w);  // + 128 G r: to workgroup 64 r + ln
+  uint64_t *get = a.own.rec + 2 * ((int64_t)w * G + ln);  // + 128 r: from workgroup 64 r + ln
+  uint64_t *put1 = put + (int64_t)G * G * 2, *get1 = get + (int64_t)G * G * 2;
+  uint64_t *fn = F1, *fn1 = F2, *fn2 = F0;
+  uint32_t tag = own_tag(0);
+  int cur = 0, d = 0, slow = 0;  // queue, level, second exchanges so far
+  bool spill = false;
+  for (;;) {
+    const int nxt = cur ^ 1;
+    const bool rec_level = d < kStatsCap;
+    if (et >= 0) {
+      int esum = 0;
+      for (int i0 = et & ~63; i0 < n; i0 += T) {
+        const int i = i0 + ln;
+        int rs = 0, dg = 0, c[4] = {-1, -1, -1, -1};
+        if (i0 < T && i < npre) {
+          rs = prs;
+          dg = pdg;
+#pragma unroll
+          for (int q = 0; q < 4; ++q) c[q] = pc[q];
+        } else if (i < n) {
+          const int v = sh.q[cur][i];
+          rs = rp[v];
+          dg = rp[v + 1] - rs;
+#pragma unroll
+          for (int q = 0; q < 4; ++q) c[q] = q < dg ? ci[rs + q] : -1;
+        }
+        esum += dg;
+        own_expand(a, sh, lo, nv, w, &sh.cnt[nxt], sh.q[nxt], fn, box, d + 1, c);
+        for (int q0 = 4; __ballot(q0 < dg) != 0ull; q0 += 4) {
+#pragma unroll
+          for (int q = 0; q < 4; ++q) c[q] = q0 + q < dg ? ci[rs + q0 + q] : -1;
+          own_expand(a, sh, lo, nv, w, &sh.cnt[nxt], sh.q[nxt], fn, box, d + 1, c);
+        }
+      }
+      if (rec_level) {
+        esum = own_sum(esum);
+        if (ln == 0 && esum) atomicAdd(&sh.edges, esum);
+      }
+      __builtin_amdgcn_s_waitcnt(0);  // box stores are done before the heads go out
     }
+    __syncthreads();
+    const int nl = min(sh.cnt[nxt], kOwnQueue);
+    if (et < 0) {
+      int total = nl, nin = 0, state = kOwnGo, nc = n, ne = sh.edges;
+      int any_ovf = sh.ovf;
+      bool any_n = n > 0;
+      if (G == 1) {
+        if (nl == 0) state = kOwnDone;
+        else if (nl > most || any_ovf) state = kOwnExact;
+      } else {
+        // lane l: workgroups l, l + 64, ...
+        const uint64_t tot = own_total(tag, n, nl, sh.sent, any_ovf);
+        uint64_t hd[R], tt[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+          const int o = r * 64 + ln;
+          if (o >= G) continue;
+          const int x = sh.out[o];
+          uint64_t *p = put + (int64_t)128 * G * r;
+          store_relaxed_u64(p, own_head(tag, min(x, cap), sh.msg[o][0], sh.msg[o][1]));
+          store_relaxed_u64(p + 1, tot);
+          if (x) sh.out[o] = 0;
+        }
+        if (rec_level && ln == 0)
+          store_relaxed_u64(&a.own.rec_edges[(d & 1) * G + w],
+                            ((uint64_t)tag << 48) | (uint32_t)ne);
+        // poll the words written for this workgroup
+        uint64_t t0 = 0;
+        for (;;) {
+          bool ok = true;
+#pragma unroll
+          for (int r = 0; r < R; ++r) {
+            const int sd = r * 64 + ln;
+            hd[r] = tt[r] = 0ull;
+            if (sd >= G) continue;
+            hd[r] = load_relaxed_u64(get + 128 * r);
+            tt[r] = load_relaxed_u64(get + 128 * r + 1);
+            ok &= (uint32_t)(hd[r] >> 48) == tag && (uint32_t)(tt[r] >> 48) == tag;
+          }
+          if (__ballot(!ok) == 0ull) break;
+          if (t0 == 0) t0 = wall_clock64();
+          if (wall_clock64() - t0 >= wait_ticks) {
+            state = kOwnGaveUp;
+            break;
+          }
+        }
+        if (state == kOwnGo) {
+          bool found = false, much = false, full = false, more = false, front = false;
+#pragma unroll
+          for (int r = 0; r < R; ++r) {
+            const int x = total_won(tt[r]) + total_sent(tt[r]);
+            found |= x != 0;
+            much |= x > share;
+            full |= (tt[r] & 1ull) != 0;
+            front |= total_n(tt[r]) != 0;
+            const int kc = head_cnt(hd[r]);
+            more |= kc > 2;
+            if (__ballot(kc != 0) == 0ull) continue;
+            // the first two targets of each sender
+            const int m0 = head_m0(hd[r]), m1 = head_m1(hd[r]);
+            uint32_t o0 = ~0u, o1 = ~0u;
+            if (kc > 0) o0 = atomicOr(&sh.vis[m0 >> 5], 1u << (m0 & 31));
+            if (kc > 1) o1 = atomicOr(&sh.vis[m1 >> 5], 1u << (m1 & 31));
+            const bool w0 = !((o0 >> (m0 & 31)) & 1u), w1 = !((o1 >> (m1 & 31)) & 1u);
+            const uint64_t b0 = __ballot(w0), b1 = __ballot(w1);
+            if (b0 | b1) {  // this wave alone appends here
+              int slot = total + __popcll(b0 & mask_below(ln)) + __popcll(b1 & mask_below(ln));
+#pragma unroll
+              for (int q = 0; q < 2; ++q) {
+                if (!(q == 0 ? w0 : w1)) continue;
+                const int c = lo + (q == 0 ? m0 : m1);
+                a.levels[c] = d + 1;
+                if (slot < kOwnQueue) {
+                  sh.q[nxt][slot] = c;
+                } else {
+                  atomicOr((unsigned long long *)&fn[c >> 6], 1ull << (c & 63));
+                  sh.ovf = 1;
+                }
+                ++slot;
+              }
+              total += __popcll(b0) + __popcll(b1);
+            }
+          }
+          any_ovf = __ballot(full) != 0ull;
+          any_n = __ballot(front) != 0ull;
+          if (__ballot(found) == 0ull) state = kOwnDone;
+          else if (any_ovf) state = kOwnExact;
+          else if (__ballot(much)) {
+            int wsum = 0, ssum = 0, mw = 0;
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+              wsum += total_won(tt[r]);
+              ssum += total_sent(tt[r]);
+              mw = max(mw, total_won(tt[r]));
+            }
+            wsum = own_sum(wsum);
+            ssum = own_sum(ssum);
+            mw = lane_last(wave_max_scan(mw));
+            if (wsum + ssum > most || ssum + mw > kOwnQueue) state = kOwnExact;
+          }
+          if (__ballot(more)) {  // boxes: prefix of the further targets, lane-major
+            int k[R], in = 0;
+#pragma unroll
+            for (int r = 0; r < R; ++r) in += k[r] = max(head_cnt(hd[r]) - 2, 0);
+            const int incl = wave_incl_scan(in);
+            int run = incl - in;
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+              run += k[r];
+              sh.pre[ln * R + r + 1] = run;
+            }
+            if (ln == 0) sh.pre[0] = 0;
+            nin = lane_last(incl);
+          }
+          if (w == 0 && rec_level) {  // the level's record: sizes and degree sums
+            nc = 0;
+#pragma unroll
+            for (int r = 0; r < R; ++r) nc += total_n(tt[r]);
+            nc = own_sum(nc);
+            ne = 0;
+            for (int sd = ln; sd < G; sd += 64) {
+              uint64_t x;
+              t0 = wall_clock64();
+              do {
+                x = load_relaxed_u64(&a.own.rec_edges[(d & 1) * G + sd]);
+              } while ((uint32_t)(x >> 48) != tag && wall_clock64() - t0 < kCoopWaitTicks);
+              ne += (int)(uint32_t)x;
+            }
+            ne = own_sum(ne);
+          }
+        }
+      }
+      if (ln == 0) {
+        sh.state = state;
+        sh.n_new = total;
+        sh.nin = nin;
+        sh.any_ovf = any_ovf;
+        sh.cnt[cur] = 0;
+        sh.sent = 0;
+        if (rec_level) sh.edges = 0;
+        if (w == 0 && state != kOwnGaveUp && any_n) {
+          a.ctrl->nlev = d + 1;
+          if (rec_level && a.stats) {
+            a.stats[d * kStatFields + 0] = nc;
+            a.stats[d * kStatFields + 1] = ne;
+            a.stats[d * kStatFields + 2] = GRB_DIR_PUSH;
+          }
+        }
+      }
+    } else {
+      // beside the exchange: levels, row extents and first columns of what
+      // this workgroup queued
+      prs = pdg = 0;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) pc[q] = -1;
+      if (et < nl) {
+        const int v = sh.q[nxt][et];
+        prs = rp[v];
+        pdg = rp[v + 1] - prs;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) pc[q] = q < pdg ? ci[prs + q] : -1;
+      }
+      for (int i = et; i < nl; i += T) a.levels[sh.q[nxt][i]] = d + 1;
+    }
+    npre = min(nl, T);
+    __syncthreads();
+    ++d;
+    const int state = sh.state;
+    if (state == kOwnGaveUp) {
+      spill = true;
+      break;
+    }
+    if (state == kOwnDone) break;
+    const int nin = sh.nin;
+    if (nin > 0) {  // further targets, from the boxes
+      for (int i0 = tid & ~63; i0 < nin; i0 += kOwnThreads) {
+        const int i = i0 + ln;
+        int c[1] = {-1};
+        bool wn[1] = {false};
+        if (i < nin) {
+          int at = 0;  // the last position with pre[at] <= i
+#pragma unroll
+          for (int step = 32 * R; step > 0; step >>= 1)
+            if (sh.pre[at + step] <= i) at += step;
+          const int sd = (at % R) * 64 + at / R;
+          c[0] = ld_coherent(&box[((int64_t)sd * G + w) * cap + 2 + (i - sh.pre[at])]);
+          const int l = c[0] - lo;
+          wn[0] = !((atomicOr(&sh.vis[l >> 5], 1u << (l & 31)) >> (l & 31)) & 1u);
+          if (wn[0]) a.levels[c[0]] = d;
+        }
+        own_queue(a, sh, &sh.n_new, sh.q[nxt], fn, d, c, wn);
+      }
+      __syncthreads();
+    }
+    n = min(sh.n_new, kOwnQueue);
+    cur = nxt;
+    {
+      int32_t *b = box;
+      uint64_t *p = put, *g = get, *f = fn;
+      box = box1, box1 = b;
+      put = put1, put1 = p;
+      get = get1, get1 = g;
+      fn = fn1, fn1 = fn2, fn2 = f;
+      tag = tag == 65535u ? 1u : tag + 1u;
+    }
+    if (d >= max_levels) {
+      spill = sh.any_ovf != 0;  // targets that found a box full get their level there
+      break;
+    }
+    if (state == kOwnExact || d >= kOwnMaxLevels) {
+      // the exact frontier: sizes, degree sums and full queues of every
+      // workgroup over a second exchange
+      int e = 0;
+      for (int i = tid; i < n; i += kOwnThreads) {
+        const int v = sh.q[cur][i];
+        e += rp[v + 1] - rp[v];
+      }
+      __syncthreads();
+      if (tid == 0) sh.edges = 0;
+      __syncthreads();
+      e = own_sum(e);
+      if (ln == 0 && e) atomicAdd(&sh.edges, e);
+      __syncthreads();
+      if (tid < 64) {
+        int nc = n, ne = sh.edges, gave_up = 0;
+        bool ov = sh.ovf != 0 || sh.any_ovf != 0;
+        if (G > 1) {
+          uint64_t *r2 = a.own.rec2 + (slow & 1) * G;
+          const uint32_t tag2 = own_tag(slow);
+          if (ln == 0)
+            store_relaxed_u64(&r2[w], ((uint64_t)((tag2 << 16) | (uint32_t)n) << 32) |
+                                          ((uint32_t)ne << 1) | (ov ? 1u : 0u));
+          const uint64_t t0 = wall_clock64();
+          for (;;) {
+            bool ok = true;
+            int c = 0, es = 0, ovs = 0;
+            for (int sd = ln; sd < G; sd += 64) {
+              const uint64_t x = load_relaxed_u64(&r2[sd]);
+              ok &= (uint32_t)(x >> 48) == tag2;
+              c += (int)(x >> 32) & 0xffff;
+              es += (int)((uint32_t)x >> 1);
+              ovs |= (int)x & 1;
+            }
+            if (__ballot(!ok) == 0ull) {
+              nc = own_sum(c);
+              ne = own_sum(es);
+              ov = __ballot(ovs != 0) != 0ull;
+              break;
+            }
+            if (wall_clock64() - t0 >= wait_ticks) {
+              gave_up = 1;
+              break;
+            }
+          }
+        }
+        if (ln == 0) {
+          sh.state = gave_up ? kOwnGaveUp : kOwnGo;
+          sh.nc = nc;
+          sh.ne = ne;
+          sh.any_ovf = ov ? 1 : 0;
+          sh.edges = 0;
+        }
+      }
+      ++slow;
+      __syncthreads();
+      if (sh.state == kOwnGaveUp) {
+        spill = true;
+        break;
+      }
+      if (sh.nc == 0 && !sh.any_ovf) break;
+      if (sh.any_ovf || sh.ne > kCoopEdges || d >= kOwnMaxLevels ||
+          decide(a, sh.nc, sh.ne) == GRB_DIR_PULL) {
+        spill = true;
+        break;
+      }
+    }
+  }
+  if (tid == 0) {
+    atomicMin(&a.ctrl->small_levels, d);
+    if (spill) atomicOr(&a.ctrl->spilled, 1);
+  }
+}
+
+// After a loop that spilled at level h = ctrl->small_levels.  What it left:
+// the levels of every vertex claimed (the frontier's are h; a workgroup that
+// left a level later also claimed some at h + 1), the targets sent in that
+// level, which their owners may not have read, and the bits of targets that
+// found a box full.  First the targets sent join those bits; then one pass
+// over the vertices makes the frontier's bitmap and counters (vertices at
+// level h, and unreached ones whose bit is set, which get the level) and the
+// visited bitmap of level h for the level kernel, and resets what lies beyond.
+__global__ __launch_bounds__(kBlock) void k_bfs_own_boxes(BfsArgs a, uint64_t *F0, uint64_t *F1,
+                                                          uint64_t *F2) {
+  if (!a.ctrl->spilled) return;
+  const int64_t h = a.ctrl->small_levels;
+  uint64_t *fh = (h % 3 == 0) ? F0 : ((h % 3 == 1) ? F1 : F2);
+  const int G = a.own.groups, cap = a.own.cap, par = (int)((h - 1) & 1);
+  const int32_t *box = a.own.box + (int64_t)par * G * G * cap;
+  const uint64_t *rec = a.own.rec + (int64_t)par * G * G * 2;
+  const uint32_t tag = own_tag(h - 1);
+  const int64_t tid = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+  if (G > 1) {
+    const int64_t m = (int64_t)G * G * cap, nt = (int64_t)gridDim.x * kBlock;
+    for (int64_t t = tid; t < m; t += nt) {
+      const int64_t pair = t / cap;
+      const int sd = (int)(pair / G), o = (int)(pair % G), j = (int)(t % cap);
+      const uint64_t hd = rec[((int64_t)o * G + sd) * 2];
+      if ((uint32_t)(hd >> 48) != tag || j >= head_cnt(hd)) continue;
+      const int c = j >= 2 ? box[t] : o * a.own.chunk + (j == 0 ? head_m0(hd) : head_m1(hd));
+      atomicOr((unsigned long long *)&fh[c >> 6], 1ull << (c & 63));
+    }
+  }
+  if (tid == 0) {
     for (int i = 0; i < 3 * kCntSlots; ++i) a.ctrl->lists[i] = 0;
-    int32_t *cnt = a.ctrl->lists + (h % 3) * kCntSlots;
-    cnt[0] = nq;
-    cnt[1] = ne;
-    cnt[2] = 0;  // rows are at most kCoopMaxDeg long
     a.ctrl->pushed[0] = a.ctrl->pushed[1] = a.ctrl->pushed[2] = 0;  // parents: final pass
+    if (G > 1) {  // the record of level h - 1, where workgroup 0 left before it
+      int nc = 0, ne = 0;
+      for (int sd = 0; sd < G; ++sd) {
+        nc += total_n(rec[(int64_t)sd * 2 + 1]);
+        ne += (int)(uint32_t)a.own.rec_edges[par * G + sd];
+      }
+      if (nc > 0) {
+        a.ctrl->nlev = (int)h;
+        if (a.stats && h - 1 < kStatsCap) {
+          a.stats[(h - 1) * kStatFields + 0] = nc;
+          a.stats[(h - 1) * kStatFields + 1] = ne;
+          a.stats[(h - 1) * kStatFields + 2] = GRB_DIR_PUSH;
+        }
+      }
+    }
+  }
+}
+
+__global__ __launch_bounds__(kBlock) void k_bfs_own_handover(BfsArgs a, uint64_t *F0, uint64_t *F1,
+                                                             uint64_t *F2) {
+  __shared__ int s_red[kWavesPerBlock][2];
+  if (!a.ctrl->spilled) return;
+  const int64_t h = a.ctrl->small_levels;
+  uint64_t *const F[3] = {F0, F1, F2};
+  uint64_t *fh = F[h % 3], *f1 = F[(h + 1) % 3], *f2 = F[(h + 2) % 3];
+  const int ln = threadIdx.x & 63;
+  const int64_t gw = (int64_t)blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6);
+  const int64_t nwaves = (int64_t)gridDim.x * kWavesPerBlock;
+  int fc = 0, fd = 0;
+  for (int64_t w = gw; w < a.nw; w += nwaves) {
+    const int64_t v = w * 64 + ln;
+    const bool inb = v < a.n;
+    int lev = inb ? a.levels[v] : 0;
+    const uint64_t bits = fh[w];
+    const bool beyond = inb && lev > h;
+    if (beyond) a.levels[v] = lev = -1;
+    const bool found = inb && lev == -1 && ((bits >> ln) & 1ull);
+    const bool front = inb && (lev == h || found);
+    if (found) a.levels[v] = (int)h;
+    if (front) {
+      fc += 1;
+      fd += a.push.rp[v + 1] - a.push.rp[v];
+    }
+    const uint64_t fm = __ballot(front), vm = __ballot(inb && (lev >= 0 || found));
+    if (ln == 0) {
+      fh[w] = fm;
+      f1[w] = 0ull;
+      f2[w] = 0ull;
+      a.visited[w] |= vm;
+    }
+  }
+  fc = wave_sum(fc);
+  fd = wave_sum(fd);
+  if (ln == 0) {
+    s_red[threadIdx.x >> 6][0] = fc;
+    s_red[threadIdx.x >> 6][1] = fd;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    int c = 0, sd = 0;
+    for (int i = 0; i < kWavesPerBlock; ++i) {
+      c += s_red[i][0];
+      sd += s_red[i][1];
+    }
+    if (c) {  // rows are at most kCoopMaxDeg long: none has pieces
+      int32_t *cnt = a.ctrl->lists + (h % 3) * kCntSlots + kCntFields * (blockIdx.x % kCntStripes);
+      atomicAdd(&cnt[0], c);
+      atomicAdd(&cnt[1], sd);
+    }
   }
 }
 
 }  // namespace
 
-void launch_bfs_coop(const BfsArgs &a, int32_t source, int64_t max_levels, uint64_t *const F[3],
-                     uint64_t wait_ticks, void *stream) {
-  hipLaunchKernelGGL(k_bfs_coop, dim3(kCoopGrid), dim3(kCoopThreads), 0, (hipStream_t)stream, a,
-                     max_levels, wait_ticks, F[0], F[1], F[2]);
-  const int g = (kCoopSegs * a.qseg + kBlock - 1) / kBlock;
-  hipLaunchKernelGGL(k_bfs_coop_handover, dim3(g < 1 ? 1 : g), dim3(kBlock), 0,
-                     (hipStream_t)stream, a, source, F[0], F[1], F[2]);
+void launch_bfs_own(const BfsArgs &a, int32_t source, int64_t max_levels, uint64_t *const F[3],
+                    uint64_t wait_ticks, void *stream) {
+  hipStream_t s = (hipStream_t)stream;
+  const int64_t deg = std::max<int64_t>(a.push.max_deg, 1);
+  int64_t m = kCoopEdges / deg;
+  if (!a.forced && a.can_pull) {
+    const int64_t den = std::max<int64_t>(a.denom, 1);
+    m = std::min(m, a.rule == GRB_SWITCH_EXACT ? a.nnz / den / deg : a.n / den);
+  }
+  const int cap = (int)std::min<int64_t>(max_levels, kOwnMaxLevels + 1);
+  const int most = (int)m, share = (int)std::min<int64_t>(m, kOwnQueue) / a.own.groups;
+  if (a.own.groups <= 64)
+    hipLaunchKernelGGL(k_bfs_own<1>, dim3(a.own.groups), dim3(kOwnThreads), 0, s, a, source,
+                       cap, wait_ticks, most, share, F[0], F[1], F[2]);
+  else
+    hipLaunchKernelGGL(k_bfs_own<4>, dim3(a.own.groups), dim3(kOwnThreads), 0, s, a, source,
+                       cap, wait_ticks, most, share, F[0], F[1], F[2]);
+  hipLaunchKernelGGL(k_bfs_own_boxes, dim3(256), dim3(kBlock), 0, s, a, F[0], F[1], F[2]);
+  int64_t g = (a.nw + kWavesPerBlock - 1) / kWavesPerBlock;
+  g = g < 1 ? 1 : (g > kExpandGrid ? kExpandGrid : g);
+  hipLaunchKernelGGL(k_bfs_own_handover, dim3((unsigned)g), dim3(kBlock), 0, s, a, F[0], F[1],
+                     F[2]);
 }
 
 void launch_bfs_start(const BfsArgs &a, int32_t source, uint64_t *f1, uint64_t *f2,

@@ -185,11 +185,9 @@ void launch_compact(const CompactArgs &a, void *stream);
 // (agent-scope) atomics, loads and stores, so no L2 write-back is needed.
 // State shared by the loop's workgroups:
 constexpr int kCoopThreads = 256;
-// workgroups of the loop: BFS levels carry few entries (the 3000 x 3000
-// grid's frontier holds at most 3,000 vertices), bucket rounds more (a
-// pending set of up to ~8,000 there), and a barrier costs more the more
+// workgroups of the bucketed SSSP loop: a pending set holds up to ~8,000
+// vertices on the 3000 x 3000 grid, and a barrier costs more the more
 // workgroups arrive (measured: 0.85 us for 16, 1.0 for 32)
-constexpr int kCoopGridBfs = 16;
 constexpr int kCoopGridSssp = 32;
 constexpr int kCoopSegsMax = kCoopGridSssp * (kCoopThreads / 64);  // one queue segment per wave
 constexpr int kCoopSeg = 256;          // queue entries per wave and level (more: spill)
@@ -211,6 +209,24 @@ constexpr int64_t kCoopMaxLevels = int64_t(1) << 24;  // arrivals stay below 2^3
 // also when some of the loop's workgroups are not resident.
 constexpr uint64_t kCoopWaitTicks = 100000;
 
+// BFS loop (grb_bfs.hip): workgroup w owns the vertices [w * chunk, (w + 1) *
+// chunk), visited bits and queues in LDS.
+constexpr int kOwnThreads = 512;
+constexpr int kOwnVertices = 786432;  // visited bits a workgroup can hold (96 KB of LDS)
+constexpr int kOwnQueue = 4096;       // queue entries per workgroup (two queues: 32 KB)
+constexpr int kOwnMaxGroups = 256;
+constexpr int kOwnMaxLevels = 1 << 30;
+constexpr int kOwnCapMax = 255;      // targets one workgroup can send another in a level
+struct BfsOwn {
+  int groups = 0, chunk = 0, cap = 0;  // workgroups, vertices each, box capacity
+  float inv_chunk = 0.0f;              // 1 / chunk
+  // record words, nrec of them in one array cleared by the start kernel:
+  // [level parity][owner][sender] head and total, [level parity][sender] edges,
+  // [parity of the second exchange][sender] exact sizes
+  uint64_t *rec = nullptr, *rec_edges = nullptr, *rec2 = nullptr;
+  int64_t nrec = 0;
+  int32_t *box = nullptr;  // [level parity][sender][owner][cap] targets (the first two unused)
+};
 // BFS with one kernel per level (grb_bfs.hip).  Each of the three rotating
 // frontier buffers has kCntStripes (count, degree sum) counter pairs.
 // per stripe: frontier size, its degree sum, its rows longer than kPushSplit
@@ -230,26 +246,19 @@ struct BfsArgs {
   int64_t *stats = nullptr;
   int32_t d = 0;
   int32_t rule = 0, denom = 10, forced = 0;
-  // multi-workgroup loop: shared state and the two level queues (entries:
-  // vertex, and row start | degree << 32; queue d & 1 at offset (d & 1) *
-  // kCoopSegsMax * qseg, segment s of a queue at s * qseg)
-  CoopCtl *coop = nullptr;
-  int32_t *qv = nullptr;
-  uint64_t *qe = nullptr;
-  int32_t qseg = 0;
+  BfsOwn own;  // multi-workgroup loop (groups 0: not used)
 };
 void launch_bfs_start(const BfsArgs &a, int32_t source, uint64_t *f1, uint64_t *f2,
                       void *stream);
 void launch_bfs_level(const BfsArgs &a, void *stream);
 constexpr int kCoopMaxDeg = 64;  // graphs whose rows are at most this long use the loop
-// BFS levels in kCoopGridBfs workgroups while the frontier fits the queues
-// (kCoopSeg vertices per wave, kCoopEdges edges) and pushes; starts at level 0 after
-// launch_bfs_start (which fills the first queue), then a hand-over kernel
-// leaves a frontier that outgrew the loop (or a given-up barrier's next
-// frontier) as the bitmap and counters of level ctrl->small_levels.
+// BFS levels in own.groups workgroups while the frontier fits their queues
+// and pushes; starts at level 0 after launch_bfs_start, then two hand-over
+// kernels leave a frontier that outgrew the loop (or a given-up barrier's
+// next frontier) as the bitmap and counters of level ctrl->small_levels.
 // Parents are left to the parents pass.
-void launch_bfs_coop(const BfsArgs &a, int32_t source, int64_t max_levels, uint64_t *const F[3],
-                     uint64_t wait_ticks, void *stream);
+void launch_bfs_own(const BfsArgs &a, int32_t source, int64_t max_levels, uint64_t *const F[3],
+                    uint64_t wait_ticks, void *stream);
 void launch_bfs_parents(const BfsArgs &a, void *stream);
 
 // SSSP with one kernel per round (grb_sssp.hip); counters as BFS
