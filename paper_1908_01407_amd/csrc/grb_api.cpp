@@ -71,11 +71,7 @@ struct BfsWs {
   Ctrl *ctrl;
   int64_t *stats;
   uint64_t *visited, *F[3];
-  CoopCtl *coop;  // multi-workgroup loop: shared state, two queues of kCoopSegsMax segments
-  int32_t *qv;
-  uint64_t *qe;
-  int32_t qseg;
-  BfsOwn own;     // BFS loop: laid over the queues
+  OwnLoop own;  // multi-workgroup loop
   size_t bytes;
 };
 
@@ -90,8 +86,8 @@ int own_groups(int64_t n) {
   return g <= kOwnMaxGroups ? g : 0;
 }
 
-BfsOwn own_layout(Carver c, int64_t n, int groups, size_t *end = nullptr) {
-  BfsOwn o{};
+OwnLoop own_layout(Carver c, int64_t n, int groups, size_t *end = nullptr) {
+  OwnLoop o{};
   o.groups = groups;
   if (!groups) return o;
   o.chunk = (int)align_up((size_t)std::max<int64_t>((n + groups - 1) / groups, 1), 64);
@@ -117,22 +113,41 @@ BfsWs bfs_layout(void *ws, int64_t n, int min_groups = 1) {
   t.stats = c.take<int64_t>((size_t)kStatsCap * kStatFields);
   t.visited = c.take<uint64_t>((size_t)nw);
   for (int i = 0; i < 3; ++i) t.F[i] = c.take<uint64_t>((size_t)nw);
-  t.qseg = (int32_t)std::max<int64_t>(std::min<int64_t>(kCoopSeg, n), 1);
-  t.coop = c.take<CoopCtl>(1);
-  const size_t qn = 2 * (size_t)kCoopSegsMax * (size_t)t.qseg;
-  const size_t queues = c.off;
-  t.qv = c.take<int32_t>(qn);
-  t.qe = c.take<uint64_t>(qn);
-  // the loop's buffers lie over the queues (SSSP's), with room for at least
-  // four workgroups (min_groups, for GRB_LOOP_NO_WAIT)
+  // room for at least kOwnTestGroups workgroups (min_groups: GRB_LOOP_NO_WAIT)
   const int groups = own_groups(n);
-  Carver o(ws);
-  o.off = queues;
-  size_t end = 0;
-  own_layout(o, n, groups ? std::max(groups, kOwnTestGroups) : 0, &end);
-  t.own = own_layout(o, n, groups ? std::max(groups, min_groups) : 0);
-  t.bytes = std::max(c.off, end);
+  size_t end = c.off;
+  own_layout(c, n, groups ? std::max(groups, kOwnTestGroups) : 0, &end);
+  t.own = own_layout(c, n, groups ? std::max(groups, min_groups) : 0);
+  t.bytes = end;
   return t;
+}
+
+// Bucket rounds: the fewest workgroups whose distances fit their LDS (0: too
+// many vertices, the queue loop takes them).  Us per round, 62 workgroups
+// holding the 2003 x 1009 grid's distances in LDS 4.7, 32 holding them in
+// device memory 6.9, the queue loop 7.7.
+int delta_groups(int64_t n) {
+  const int64_t g = (n + kDeltaOwnLds - 65) / (kDeltaOwnLds - 64);
+  return g <= kDeltaMaxGroups ? (int)std::max<int64_t>(g, 1) : 0;
+}
+
+// `box`, box_bytes: the frontier-distance vectors, which bucket rounds don't use
+OwnLoop delta_layout(Carver c, int64_t n, int groups, void *box, size_t box_bytes,
+                     size_t *end = nullptr) {
+  OwnLoop o{};
+  o.groups = groups;
+  if (!groups) return o;
+  o.chunk = (int)align_up((size_t)std::max<int64_t>((n + groups - 1) / groups, 1), 64);
+  o.inv_chunk = 1.0f / (float)o.chunk;
+  const int64_t pairs = (int64_t)2 * groups * groups;
+  o.cap = (int)std::min<int64_t>((int64_t)(box_bytes / 8) / pairs, kDeltaCapMax);
+  o.nrec = (int64_t)4 * groups * groups + 4 * groups;
+  o.rec = c.take<uint64_t>((size_t)o.nrec);
+  o.rec_edges = o.rec + (int64_t)4 * groups * groups;
+  o.rec2 = o.rec_edges + 2 * groups;
+  o.box64 = (uint64_t *)box;
+  if (end) *end = c.off;
+  return o;
 }
 
 // SSSP: the BFS state plus three rotating "frontier distance" vectors
@@ -140,16 +155,37 @@ BfsWs bfs_layout(void *ws, int64_t n, int min_groups = 1) {
 struct SsspWs {
   BfsWs b;
   float *fd[3];
+  // multi-workgroup loops of the bucket rounds: own, or (own.groups 0) shared
+  // state and two queues of kCoopSegsMax segments
+  OwnLoop own;
+  CoopCtl *coop;
+  int32_t *qv;
+  uint64_t *qe;
+  int32_t qseg;
   size_t bytes;
 };
 
-SsspWs sssp_layout(void *ws, int64_t n) {
+SsspWs sssp_layout(void *ws, int64_t n, int min_groups = 1) {
   SsspWs t{};
   t.b = bfs_layout(ws, n);
   Carver c(ws);
   c.off = t.b.bytes;
+  const size_t fd_off = c.off;
   for (int i = 0; i < 3; ++i) t.fd[i] = c.take<float>((size_t)std::max<int64_t>(n, 1));
-  t.bytes = c.off;
+  const int groups = delta_groups(n);
+  size_t end = c.off;
+  const size_t fd_bytes = c.off - fd_off;
+  delta_layout(c, n, groups ? std::max(groups, kOwnTestGroups) : 0, t.fd[0], fd_bytes, &end);
+  t.own = delta_layout(c, n, groups ? std::max(groups, min_groups) : 0, t.fd[0], fd_bytes);
+  if (!groups) {
+    t.qseg = kCoopSeg;
+    t.coop = c.take<CoopCtl>(1);
+    const size_t qn = 2 * (size_t)kCoopSegsMax * (size_t)t.qseg;
+    t.qv = c.take<int32_t>(qn);
+    t.qe = c.take<uint64_t>(qn);
+    end = c.off;
+  }
+  t.bytes = end;
   return t;
 }
 
@@ -805,7 +841,7 @@ grb_info run_sssp(grb_matrix A, int32_t source, float *dist, const grb_descripto
 grb_info run_sssp_delta(grb_matrix A, int32_t source, float *dist, float delta,
                         const grb_descriptor &desc, void *ws, size_t ws_bytes, void *stream) {
   const int64_t n = A->nrows;
-  SsspWs sw = sssp_layout(ws, n);
+  SsspWs sw = sssp_layout(ws, n, (desc.flags & GRB_LOOP_NO_WAIT) ? kOwnTestGroups : 1);
   grb_info info = check_ws(ws, ws_bytes, sw.bytes);
   if (info != GRB_SUCCESS) return info;
   const BfsWs &w = sw.b;
@@ -841,10 +877,11 @@ grb_info run_sssp_delta(grb_matrix A, int32_t source, float *dist, float delta,
   // barrier the loop gave up, continues with the round kernel
   const bool small = A->a.max_deg <= kCoopMaxDeg;
   if (small) {
-    sa.coop = w.coop;
-    sa.qv = w.qv;
-    sa.qe = w.qe;
-    sa.qseg = w.qseg;
+    sa.own = sw.own;
+    sa.coop = sw.coop;
+    sa.qv = sw.qv;
+    sa.qe = sw.qe;
+    sa.qseg = sw.qseg;
   }
   launch_sssp_delta_start(sa, source, w.F[1], w.F[2], stream);
   const int64_t cap = desc.max_iter > 0 ? desc.max_iter : INT64_MAX;
@@ -859,8 +896,9 @@ grb_info run_sssp_delta(grb_matrix A, int32_t source, float *dist, float delta,
   if (small) {
     if (profile) (void)hipEventRecord(g_events.get(0), s);
     uint64_t *F[3] = {w.F[0], w.F[1], w.F[2]};
-    launch_sssp_delta_coop(sa, cap, F, (desc.flags & GRB_LOOP_NO_WAIT) ? 0 : kCoopWaitTicks,
-                           stream);
+    const uint64_t ticks = (desc.flags & GRB_LOOP_NO_WAIT) ? 0 : kCoopWaitTicks;
+    if (sa.own.groups > 0) launch_sssp_delta_own(sa, source, cap, F, ticks, stream);
+    else launch_sssp_delta_coop(sa, cap, F, ticks, stream);
     if (profile) (void)hipEventRecord(g_events.get(1), s);
     launch_round.push_back(0);
     launches = 1;

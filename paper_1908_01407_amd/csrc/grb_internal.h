@@ -177,47 +177,51 @@ struct CompactArgs {
 int compact_blocks(int64_t nw);
 void launch_compact(const CompactArgs &a, void *stream);
 
-// Multi-workgroup level loop (high-diameter, low-degree graphs): a small grid
-// of workgroups runs BFS levels (SSSP bucket rounds) back to back, separated
-// by a barrier of its own (one arrival per workgroup on a shared counter,
-// then a bounded wait), with the frontier as a queue in device memory.
-// Everything one workgroup hands to another goes through device-coherent
-// (agent-scope) atomics, loads and stores, so no L2 write-back is needed.
-// State shared by the loop's workgroups:
-constexpr int kCoopThreads = 256;
-// workgroups of the bucketed SSSP loop: a pending set holds up to ~8,000
-// vertices on the 3000 x 3000 grid, and a barrier costs more the more
-// workgroups arrive (measured: 0.85 us for 16, 1.0 for 32)
-constexpr int kCoopGridSssp = 32;
-constexpr int kCoopSegsMax = kCoopGridSssp * (kCoopThreads / 64);  // one queue segment per wave
-constexpr int kCoopSeg = 256;          // queue entries per wave and level (more: spill)
-constexpr int kCoopEdges = 65536;      // a frontier with more edges goes to the level kernel
-// Each level's queue has one segment per wave of the loop; the wave that
-// found the entries stores their count and degree sum (slot d & 1 for the
-// frontier of level d).
-struct CoopCtl {
-  unsigned long long bar;  // arrivals (low 32 bits) | 1 + the barrier given up (high 32 bits)
-  int32_t cnt[2][kCoopSegsMax];   // entries queued
-  int32_t esum[2][kCoopSegsMax];  // BFS: their degree sum; bucketed SSSP: that of the near ones
-  int32_t near[2][kCoopSegsMax];  // bucketed SSSP: entries below the round's limit
-  int32_t far[2][kCoopSegsMax];   // bucketed SSSP: smallest bucket of the others (INT_MAX: none)
-};
-constexpr int64_t kCoopMaxLevels = int64_t(1) << 24;  // arrivals stay below 2^32
-// A barrier not completed after this many ticks of the 100 MHz real-time
+// Multi-workgroup loops (high-diameter, low-degree graphs): a few workgroups
+// run BFS levels (SSSP bucket rounds) back to back in one kernel.  Workgroup
+// w owns the vertices [w * chunk, (w + 1) * chunk), their state and its share
+// of the frontier sit in its LDS, and after each level the workgroups
+// exchange records through device-coherent (agent-scope) words.
+constexpr int kCoopEdges = 65536;  // a frontier with more edges goes to the level kernel
+// An exchange not completed after this many ticks of the 100 MHz real-time
 // clock (1 ms: a level of the loop takes microseconds) is given up; the
 // frontier then continues with the level kernel.  Nothing waits unboundedly,
 // also when some of the loop's workgroups are not resident.
 constexpr uint64_t kCoopWaitTicks = 100000;
 
-// BFS loop (grb_bfs.hip): workgroup w owns the vertices [w * chunk, (w + 1) *
-// chunk), visited bits and queues in LDS.
+// Bucket rounds of graphs too large for their distances to sit in LDS: a
+// pending queue in device memory, split evenly over the workgroups, one
+// segment per wave, and a counter barrier between the rounds.  (With a
+// wide pending band the even split matters more than the exchange: owners
+// with distances in device memory took 12 to 14 us per round on the 3000 x
+// 3000 grid, this 10.6.)
+constexpr int kCoopThreads = 256;
+// a pending set holds up to ~8,000 vertices on the 3000 x 3000 grid, and a
+// barrier costs more the more workgroups arrive (0.85 us for 16, 1.0 for 32)
+constexpr int kCoopGridSssp = 32;
+constexpr int kCoopSegsMax = kCoopGridSssp * (kCoopThreads / 64);  // one queue segment per wave
+constexpr int kCoopSeg = 256;          // queue entries per wave and round (more: spill)
+// Each round's queue has one segment per wave of the loop; the wave that
+// found the entries stores their counts (slot d & 1 for round d).
+struct CoopCtl {
+  unsigned long long bar;  // arrivals (low 32 bits) | 1 + the barrier given up (high 32 bits)
+  int32_t cnt[2][kCoopSegsMax];   // entries queued
+  int32_t esum[2][kCoopSegsMax];  // degree sum of the near ones
+  int32_t near[2][kCoopSegsMax];  // entries below the round's limit
+  int32_t far[2][kCoopSegsMax];   // smallest bucket of the others (INT_MAX: none)
+};
+constexpr int64_t kCoopMaxLevels = int64_t(1) << 24;  // arrivals stay below 2^32
+
 constexpr int kOwnThreads = 512;
-constexpr int kOwnVertices = 786432;  // visited bits a workgroup can hold (96 KB of LDS)
-constexpr int kOwnQueue = 4096;       // queue entries per workgroup (two queues: 32 KB)
+constexpr int kOwnVertices = 786432;  // BFS: visited bits a workgroup can hold (96 KB of LDS)
+constexpr int kOwnQueue = 4096;       // BFS: queue entries per workgroup (two queues: 32 KB)
 constexpr int kOwnMaxGroups = 256;
+constexpr int kDeltaCapMax = 8191;         // bucket rounds: messages from one workgroup to another per round
+constexpr int kDeltaMaxGroups = 64;        // ... workgroups
+constexpr int kDeltaOwnLds = 32768;        // bucket rounds: vertices whose distances fit LDS (128 KB)
 constexpr int kOwnMaxLevels = 1 << 30;
 constexpr int kOwnCapMax = 255;      // targets one workgroup can send another in a level
-struct BfsOwn {
+struct OwnLoop {
   int groups = 0, chunk = 0, cap = 0;  // workgroups, vertices each, box capacity
   float inv_chunk = 0.0f;              // 1 / chunk
   // record words, nrec of them in one array cleared by the start kernel:
@@ -225,7 +229,10 @@ struct BfsOwn {
   // [parity of the second exchange][sender] exact sizes
   uint64_t *rec = nullptr, *rec_edges = nullptr, *rec2 = nullptr;
   int64_t nrec = 0;
-  int32_t *box = nullptr;  // [level parity][sender][owner][cap] targets (the first two unused)
+  // [level parity][sender][owner][cap]: BFS targets (the first two unused),
+  // SSSP messages (vertex within its owner << 32 | distance bits; the first unused)
+  int32_t *box = nullptr;
+  uint64_t *box64 = nullptr;
 };
 // BFS with one kernel per level (grb_bfs.hip).  Each of the three rotating
 // frontier buffers has kCntStripes (count, degree sum) counter pairs.
@@ -246,7 +253,7 @@ struct BfsArgs {
   int64_t *stats = nullptr;
   int32_t d = 0;
   int32_t rule = 0, denom = 10, forced = 0;
-  BfsOwn own;  // multi-workgroup loop (groups 0: not used)
+  OwnLoop own;  // multi-workgroup loop (groups 0: not used)
 };
 void launch_bfs_start(const BfsArgs &a, int32_t source, uint64_t *f1, uint64_t *f2,
                       void *stream);
@@ -280,7 +287,11 @@ struct SsspArgs {
   int64_t *stats = nullptr;
   int32_t d = 0;
   int32_t rule = 0, denom = 10, forced = 0;
-  // bucketed rounds in the multi-workgroup loop: as BfsArgs
+  // bucketed rounds in a multi-workgroup loop: own (groups > 0), or the shared
+  // state and the two round queues (entries: vertex, and row start | degree <<
+  // 32; queue d & 1 at offset (d & 1) * kCoopSegsMax * qseg, segment s of a
+  // queue at s * qseg)
+  OwnLoop own;
   CoopCtl *coop = nullptr;
   int32_t *qv = nullptr;
   uint64_t *qe = nullptr;
@@ -298,10 +309,15 @@ constexpr int kDeltaSlots = kDeltaFields * kCntStripes;
 void launch_sssp_delta_start(const SsspArgs &a, int32_t source, uint64_t *f1, uint64_t *f2,
                              void *stream);
 void launch_sssp_delta_round(const SsspArgs &a, void *stream);
-// bucket rounds in the multi-workgroup loop (kCoopGridSssp workgroups, the BFS
-// loop's queues and limits), then a hand-over kernel that leaves a pending
-// set that outgrew it (or a given-up barrier's next set) as the bitmap and
-// counters of round ctrl->small_levels for the round kernel
+// bucket rounds in the multi-workgroup loop (own.groups workgroups), then two
+// hand-over kernels that leave a pending set that outgrew it (or a given-up
+// exchange's next set) as the bitmap and counters of round ctrl->small_levels
+// for the round kernel
+void launch_sssp_delta_own(const SsspArgs &a, int32_t source, int64_t max_rounds,
+                           uint64_t *const F[3], uint64_t wait_ticks, void *stream);
+
+// the same for graphs above the limit of own (kCoopGridSssp workgroups, queue
+// in device memory)
 void launch_sssp_delta_coop(const SsspArgs &a, int64_t max_rounds, uint64_t *const F[3],
                             uint64_t wait_ticks, void *stream);
 

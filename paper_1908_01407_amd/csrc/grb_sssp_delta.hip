@@ -21,13 +21,15 @@
 //   bucket), plus the pending total, all in striped counters.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "grb_device.h"
 #include "grb_internal.h"
 
 namespace grb {
 namespace {
 
-// multi-workgroup loop of this file: workgroups, queue segments (one per
+// queue loop of this file: workgroups, queue segments (one per
 // wave), segment counts read per lane of one wave
 constexpr int kCoopGrid = kCoopGridSssp;
 constexpr int kCoopSegs = kCoopGrid * (kCoopThreads / 64);
@@ -314,6 +316,8 @@ __global__ __launch_bounds__(kBlock) void k_sssp_delta_start(SsspArgs a, int32_t
     a.cnt_cur[4] = 1;
     a.ctrl->nlev = 0;
     a.ctrl->bucket = 0;
+    a.ctrl->small_levels = INT_MAX;
+    a.ctrl->spilled = 0;
     if (a.coop) {  // the multi-workgroup loop's first queue: {source}, near
       a.coop->bar = 0ull;
       for (int i = 0; i < kCoopSegsMax; ++i) {
@@ -327,9 +331,613 @@ __global__ __launch_bounds__(kBlock) void k_sssp_delta_start(SsspArgs a, int32_t
       a.qe[0] = ((uint64_t)(uint32_t)ds << 32) | (uint32_t)a.push.rp[source];
     }
   }
+  for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < a.own.nrec;
+       i += (int64_t)gridDim.x * kBlock)
+    a.own.rec[i] = 0ull;  // no tag
 }
 
 // ---- multi-workgroup bucket rounds while the pending set is small ----------
+// The BFS level loop's scheme (grb_bfs.hip, k_bfs_own) for bucket rounds:
+// workgroup w owns the vertices [w * chunk, (w + 1) * chunk); its pending
+// vertices are two lists in its LDS, near (below the bucket's limit) and far,
+// with a membership bit each, and it alone relaxes their distances, which sit
+// in its LDS too (up to 64 workgroups of 32,768 vertices).  A round takes every near vertex: it relaxes the owned targets of
+// its out-edges, which join the next near list or the far one, and sends the
+// others (vertex, distance) to their owners.  Wave 0 then exchanges records
+// with the other workgroups (words that carry the round's tag; the first
+// message of each pair inside, more in a box), while the other waves load the
+// next near vertices' rows and weights.  Once no workgroup has a near vertex,
+// a second exchange finds the smallest far distance, the limit moves past its
+// bucket, and each workgroup splits its far list.
+//
+// A round's near vertices read their distance after leaving the list, so one
+// improved again later in the round is queued again.  Messages are path
+// lengths: applying one late or twice changes nothing, and a workgroup whose
+// list or box is full marks the vertex (the target, or the vertex whose edge
+// it could not send) in the pending bitmap and the loop hands over.  The same
+// goes for an exchange given up: each workgroup leaves with its distances and
+// lists written back, whatever round it reached, the hand-over applies every
+// message still in the boxes, and the round kernels continue from the pending
+// bitmap.
+constexpr int kNearCap = 1792, kFarCap = 2048;  // list entries per workgroup (LDS: 160 KB in all)
+struct DeltaShared {
+  float dist[kDeltaOwnLds];
+  uint32_t nbit[kDeltaOwnLds / 32], fbit[kDeltaOwnLds / 32];
+  int near[2][kNearCap];
+  int far[kFarCap];
+  int cnt[2], nfar, nkeep;
+  int out[kDeltaMaxGroups];   // messages to each workgroup in this round
+  int midx[kDeltaMaxGroups];  // the first of each: vertex (within its owner) and distance
+  float mdist[kDeltaMaxGroups];
+  int pre[kDeltaMaxGroups + 1];  // prefix of the boxes' further messages
+  int sent_near, edges, ovf, n_new, nin, state, gave_up;
+  float limit;
+};
+enum DeltaState { kDeltaGo = 0, kDeltaAdvance = 1, kDeltaSpill = 2 };
+
+__device__ __forceinline__ uint32_t delta_tag(int round) { return 1u + (uint32_t)round % 8190u; }
+__device__ __forceinline__ uint64_t delta_head(uint32_t tag, int idx, float d) {
+  return ((uint64_t)((tag << 19) | (uint32_t)idx) << 32) | __float_as_uint(d);
+}
+__device__ __forceinline__ uint64_t delta_total(uint32_t tag, int cnt, bool near, bool ovf) {
+  return ((uint64_t)tag << 51) | ((uint64_t)cnt << 2) | (near ? 2ull : 0ull) | (ovf ? 1ull : 0ull);
+}
+static_assert(kDeltaOwnLds <= 1 << 19 && kDeltaCapMax < 1 << 13 && kDeltaMaxGroups == 64,
+              "fields of the record words; a lane of wave 0 per workgroup");
+
+__device__ __forceinline__ float own_relax(DeltaShared &sh, int l, float nd) {
+  return __int_as_float(atomicMin((int *)&sh.dist[l], __float_as_int(nd)));
+}
+
+// Appends the wanted ones among local vertices l[0..K) to a list (all 64
+// lanes call it; one LDS atomic per wave); past its end a vertex is marked in
+// the pending bitmap.
+template <int K>
+__device__ __forceinline__ void list_add(DeltaShared &sh, uint64_t *pend, int lo, const bool (&want)[K],
+                                         const int (&l)[K], int *cnt, int *list, int cap) {
+  uint64_t b[K];
+  int tot = 0;
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    b[k] = __ballot(want[k]);
+    tot += __popcll(b[k]);
+  }
+  if (tot == 0) return;
+  int base = 0;
+  if ((threadIdx.x & 63) == 0) base = atomicAdd(cnt, tot);
+  base = __builtin_amdgcn_readfirstlane(base);
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    const int slot =
+        base + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(b[k] >> 32),
+                                              __builtin_amdgcn_mbcnt_lo((uint32_t)b[k], 0));
+    base += __popcll(b[k]);
+    if (!want[k]) continue;
+    if (slot < cap) {
+      list[slot] = l[k];
+    } else {
+      const int c = lo + l[k];
+      atomicOr((unsigned long long *)&pend[c >> 6], 1ull << (c & 63));
+      sh.ovf = 1;
+    }
+  }
+}
+
+// Owned targets whose distance was lowered to nd join the near or the far
+// list unless they are there already (all bit atomics before any result).
+template <int K>
+__device__ __forceinline__ void improved(DeltaShared &sh, uint64_t *pend, int lo, const bool (&imp)[K],
+                                         const int (&l)[K], const float (&nd)[K], float limit,
+                                         int *cnt, int *list) {
+  uint32_t old[K];
+  bool any = false, nr[K];
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    nr[k] = nd[k] < limit;
+    any |= imp[k];
+    old[k] = ~0u;
+    if (imp[k]) old[k] = atomicOr((nr[k] ? sh.nbit : sh.fbit) + (l[k] >> 5), 1u << (l[k] & 31));
+  }
+  if (__ballot(any) == 0ull) return;
+  bool add_n[K], add_f[K];
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    const bool fresh = !((old[k] >> (l[k] & 31)) & 1u);
+    add_n[k] = fresh && nr[k];
+    add_f[k] = fresh && !nr[k];
+  }
+  list_add<K>(sh, pend, lo, add_n, l, cnt, list, kNearCap);
+  list_add<K>(sh, pend, lo, add_f, l, &sh.nfar, sh.far, kFarCap);
+}
+
+// Relaxes the targets c[0..4) (none: -1) of vertex v with distances nd.
+__device__ __forceinline__ void delta_expand(const SsspArgs &a, DeltaShared &sh, uint64_t *pend, int lo,
+                                             int nv, int w, int v, float limit, int *cnt, int *list,
+                                             uint64_t *box, const int (&c)[4],
+                                             const float (&nd)[4]) {
+  float old[4];
+  bool far = false;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const uint32_t l = (uint32_t)(c[k] - lo);
+    const bool own = l < (uint32_t)nv;
+    far |= c[k] >= 0 && !own;
+    old[k] = 0.0f;
+    if (own) old[k] = own_relax(sh, (int)l, nd[k]);
+  }
+  if (__ballot(far)) {
+    const int G = a.own.groups, cap = a.own.cap;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      if (c[k] < 0 || (uint32_t)(c[k] - lo) < (uint32_t)nv) continue;
+      int o = (int)((float)c[k] * a.own.inv_chunk);  // off by one at most
+      int m = c[k] - o * a.own.chunk;
+      if (m < 0) {
+        --o;
+        m += a.own.chunk;
+      } else if (m >= a.own.chunk) {
+        ++o;
+        m -= a.own.chunk;
+      }
+      const int slot = atomicAdd(&sh.out[o], 1);
+      if (nd[k] < limit) sh.sent_near = 1;
+      if (slot == 0) {
+        sh.midx[o] = m;
+        sh.mdist[o] = nd[k];
+      } else if (slot < cap) {
+        store_relaxed_u64(&box[((int64_t)w * G + o) * cap + slot],
+                          ((uint64_t)(uint32_t)m << 32) | __float_as_uint(nd[k]));
+      } else {  // box full: the vertex stays pending
+        atomicOr((unsigned long long *)&pend[v >> 6], 1ull << (v & 63));
+        sh.ovf = 1;
+      }
+    }
+  }
+  bool imp[4];
+  int l[4];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    l[k] = c[k] - lo;
+    imp[k] = (uint32_t)l[k] < (uint32_t)nv && nd[k] < old[k];
+  }
+  improved<4>(sh, pend, lo, imp, l, nd, limit, cnt, list);
+}
+
+__device__ __forceinline__ int wave_add(int x) { return lane_last(wave_incl_scan(x)); }
+
+__global__ __launch_bounds__(kOwnThreads) void k_sssp_delta_own(SsspArgs a, int32_t source,
+                                                                int max_rounds,
+                                                                uint64_t wait_ticks,
+                                                                uint64_t *pend) {
+  __shared__ DeltaShared sh;
+  constexpr int T = kOwnThreads - 64;  // threads that take near vertices (waves 1, 2, ...)
+  const int tid = threadIdx.x, ln = tid & 63;
+  const int et = tid - 64;
+  const int w = (int)blockIdx.x, G = a.own.groups, cap = a.own.cap;
+  const int32_t *rp = a.push.rp, *ci = a.push.ci;
+  const float *wt = a.wpush;
+  const float inf = __int_as_float(0x7f800000);
+  const int64_t first = (int64_t)w * a.own.chunk;
+  const int lo = (int)(first < a.n ? first : a.n);
+  const int nv = (int)(a.n - lo < a.own.chunk ? a.n - lo : a.own.chunk);  // vertices owned
+  for (int i = tid; i < (nv + 31) / 32; i += kOwnThreads) sh.nbit[i] = sh.fbit[i] = 0u;
+  for (int i = tid; i < nv; i += kOwnThreads) sh.dist[i] = lo + i == source ? 0.0f : inf;
+  for (int i = tid; i < kDeltaMaxGroups; i += kOwnThreads) {
+    sh.out[i] = sh.midx[i] = 0;
+    sh.mdist[i] = 0.0f;
+  }
+  const bool mine = source >= lo && source - lo < nv;
+  if (tid == 0) {
+    sh.cnt[0] = sh.cnt[1] = sh.nfar = 0;
+    sh.sent_near = sh.edges = sh.ovf = 0;
+    sh.near[0][0] = source - lo;
+  }
+  __syncthreads();
+  if (tid == 0 && mine) sh.nbit[(source - lo) >> 5] = 1u << ((source - lo) & 31);
+  __syncthreads();
+  int n = mine ? 1 : 0, npre = 0;
+  int prs = 0, pdg = 0, pc[4] = {-1, -1, -1, -1};
+  float pw[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+  float limit = a.delta;
+  uint64_t *box = a.own.box64, *box1 = box + (int64_t)G * G * cap;
+  uint64_t *put = a.own.rec + 2 * ((int64_t)ln * G + w);
+  uint64_t *get = a.own.rec + 2 * ((int64_t)w * G + ln);
+  uint64_t *put1 = put + (int64_t)G * G * 2, *get1 = get + (int64_t)G * G * 2;
+  uint32_t tag = delta_tag(0);
+  int cur = 0, d = 0, slow = 0;  // near list, round, second exchanges so far
+  bool spill = false;
+  for (;;) {
+    const int nxt = cur ^ 1;
+    const bool rec_round = d < kStatsCap;
+    if (et >= 0) {
+      int esum = 0;
+      for (int i0 = et & ~63; i0 < n; i0 += T) {
+        const int i = i0 + ln;
+        int l = 0, rs = 0, dg = 0, c[4] = {-1, -1, -1, -1};
+        float dv = 0.0f, x[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+        if (i < n) {
+          l = sh.near[cur][i];
+          // off the list before its distance is read
+          atomicAnd(&sh.nbit[l >> 5], ~(1u << (l & 31)));
+          dv = *(volatile float *)&sh.dist[l];
+          if (i0 < T && i < npre) {
+            rs = prs;
+            dg = pdg;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+              c[q] = pc[q];
+              x[q] = pw[q];
+            }
+          } else {
+            rs = rp[lo + l];
+            dg = rp[lo + l + 1] - rs;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+              c[q] = q < dg ? ci[rs + q] : -1;
+              x[q] = q < dg ? wt[rs + q] : 0.0f;
+            }
+          }
+        }
+        esum += dg;
+        float nd[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) nd[q] = dv + x[q];
+        delta_expand(a, sh, pend, lo, nv, w, lo + l, limit, &sh.cnt[nxt], sh.near[nxt], box,
+                           c, nd);
+        for (int q0 = 4; __ballot(q0 < dg) != 0ull; q0 += 4) {
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            c[q] = q0 + q < dg ? ci[rs + q0 + q] : -1;
+            nd[q] = dv + (q0 + q < dg ? wt[rs + q0 + q] : 0.0f);
+          }
+          delta_expand(a, sh, pend, lo, nv, w, lo + l, limit, &sh.cnt[nxt], sh.near[nxt],
+                             box, c, nd);
+        }
+      }
+      if (rec_round) {
+        esum = wave_add(esum);
+        if (ln == 0 && esum) atomicAdd(&sh.edges, esum);
+      }
+      __builtin_amdgcn_s_waitcnt(0);  // box stores are done before the heads go out
+    }
+    __syncthreads();
+    const int nl = min(sh.cnt[nxt], kNearCap);
+    if (et < 0) {
+      int nin = 0, state = kDeltaGo, gave_up = 0;
+      int np = n + sh.nfar, ne = sh.edges;
+      bool any_n = n > 0;
+      if (G == 1) {
+        if (sh.ovf) state = kDeltaSpill;
+        else if (nl == 0) state = kDeltaAdvance;
+        if (ln == 0) sh.n_new = nl;
+      } else {
+        const bool nr = nl > 0 || sh.sent_near != 0, ov = sh.ovf != 0;
+        uint64_t hd = 0ull, tt = 0ull;
+        if (ln < G) {
+          const int k = sh.out[ln];
+          store_relaxed_u64(put, delta_head(tag, sh.midx[ln], sh.mdist[ln]));
+          store_relaxed_u64(put + 1, delta_total(tag, min(k, cap), nr, ov));
+          if (k) sh.out[ln] = 0;
+        }
+        if (rec_round && ln == 0)
+          store_relaxed_u64(&a.own.rec_edges[(d & 1) * G + w],
+                            ((uint64_t)tag << 51) | ((uint64_t)(uint32_t)min(np, 0xfffff) << 31) |
+                                (uint32_t)ne);
+        uint64_t t0 = 0;
+        for (;;) {
+          bool ok = true;
+          if (ln < G) {
+            hd = load_relaxed_u64(get);
+            tt = load_relaxed_u64(get + 1);
+            ok = (uint32_t)(hd >> 51) == tag && (uint32_t)(tt >> 51) == tag;
+          }
+          if (__ballot(!ok) == 0ull) break;
+          if (t0 == 0) t0 = wall_clock64();
+          if (wall_clock64() - t0 >= wait_ticks) {
+            gave_up = 1;
+            state = kDeltaSpill;
+            break;
+          }
+        }
+        if (ln == 0) sh.n_new = nl;  // only this wave appends until the next sync
+        if (!gave_up) {
+          const int k = (int)(tt >> 2) & 8191;  // messages from workgroup ln
+          if (__ballot(k > 0)) {
+            const int l[1] = {(int)(hd >> 32) & 0x7ffff};
+            const float nd[1] = {__uint_as_float((uint32_t)hd)};
+            float old = 0.0f;
+            if (k > 0) old = own_relax(sh, l[0], nd[0]);
+            const bool imp[1] = {k > 0 && nd[0] < old};
+            improved<1>(sh, pend, lo, imp, l, nd, limit, &sh.n_new, sh.near[nxt]);
+          }
+          if (__ballot((tt & 1ull) != 0)) state = kDeltaSpill;
+          else if (__ballot((tt & 2ull) != 0) == 0ull) state = kDeltaAdvance;
+          if (__ballot(k > 1)) {  // boxes: prefix of the further messages
+            const int in = max(k - 1, 0);
+            const int incl = wave_incl_scan(in);
+            sh.pre[ln + 1] = incl;
+            if (ln == 0) sh.pre[0] = 0;
+            nin = lane_last(incl);
+          }
+          if (w == 0 && rec_round) {
+            np = ne = 0;
+            for (int sd = ln; sd < G; sd += 64) {
+              uint64_t x;
+              t0 = wall_clock64();
+              do {
+                x = load_relaxed_u64(&a.own.rec_edges[(d & 1) * G + sd]);
+              } while ((uint32_t)(x >> 51) != tag && wall_clock64() - t0 < kCoopWaitTicks);
+              np += (int)(x >> 31) & 0xfffff;
+              ne += (int)(x & 0x7fffffffull);
+            }
+            np = wave_add(np);
+            ne = wave_add(ne);
+          }
+          any_n = true;  // (a round starts only with a near vertex somewhere, or a message)
+        }
+      }
+      if (ln == 0) {
+        sh.state = state;
+        sh.gave_up = gave_up;
+        sh.nin = nin;
+        sh.cnt[cur] = 0;
+        sh.sent_near = 0;
+        if (rec_round) sh.edges = 0;
+        if (w == 0 && !gave_up && any_n) {
+          a.ctrl->nlev = d + 1;
+          const float bk = floorf(limit / a.delta) - 1.0f;
+          const int bucket = bk < 2.0e9f ? (int)bk : INT_MAX;
+          a.ctrl->bucket = bucket;
+          if (rec_round && a.stats) {
+            a.stats[d * kStatFields + 0] = np;
+            a.stats[d * kStatFields + 1] = ne;
+            a.stats[d * kStatFields + 2] = GRB_DIR_PUSH;
+            a.stats[d * kStatFields + 3] = bucket;
+          }
+        }
+      }
+    } else {
+      // beside the exchange: rows, first columns and weights of the next round
+      prs = pdg = 0;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        pc[q] = -1;
+        pw[q] = 0.0f;
+      }
+      if (et < nl) {
+        const int v = lo + sh.near[nxt][et];
+        prs = rp[v];
+        pdg = rp[v + 1] - prs;
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          if (q < pdg) {
+            pc[q] = ci[prs + q];
+            pw[q] = wt[prs + q];
+          }
+      }
+    }
+    npre = min(nl, T);
+    __syncthreads();
+    ++d;
+    const int state = sh.state;
+    if (sh.gave_up) {
+      n = min(sh.n_new, kNearCap);
+      cur = nxt;
+      spill = true;
+      break;
+    }
+    const int nin = sh.nin;
+    if (nin > 0) {  // further messages, from the boxes
+      for (int i0 = tid & ~63; i0 < nin; i0 += kOwnThreads) {
+        const int i = i0 + ln;
+        int l = 0;
+        float nd = 0.0f, old = 0.0f;
+        if (i < nin) {
+          int sd = 0;  // the sender: the last one with pre[sd] <= i
+#pragma unroll
+          for (int step = 32; step > 0; step >>= 1)
+            if (sh.pre[sd + step] <= i) sd += step;
+          const uint64_t x =
+              load_relaxed_u64(&box[((int64_t)sd * G + w) * cap + 1 + (i - sh.pre[sd])]);
+          l = (int)(x >> 32);
+          nd = __uint_as_float((uint32_t)x);
+          old = own_relax(sh, l, nd);
+        }
+        const bool imp[1] = {i < nin && nd < old};
+        const int la[1] = {l};
+        const float na[1] = {nd};
+        improved<1>(sh, pend, lo, imp, la, na, limit, &sh.n_new, sh.near[nxt]);
+      }
+      __syncthreads();
+    }
+    n = min(sh.n_new, kNearCap);
+    cur = nxt;
+    {
+      uint64_t *b = box, *p = put, *g = get;
+      box = box1, box1 = b;
+      put = put1, put1 = p;
+      get = get1, get1 = g;
+      tag = delta_tag(d);
+    }
+    if (state == kDeltaSpill || d >= kOwnMaxLevels) {
+      spill = true;
+      break;
+    }
+    if (d >= max_rounds) break;
+    if (state != kDeltaAdvance) continue;
+    // No near vertex was left anywhere before the messages of this round,
+    // and none of those was below the limit: the next bucket.  A full list
+    // since then hands over here.
+    const int nf = min(sh.nfar, kFarCap);
+    float m = inf;
+    for (int i = tid; i < nf; i += kOwnThreads) {
+      const float x = sh.dist[sh.far[i]];
+      if (x >= limit) m = fminf(m, x);  // (below: relaxed since, from the near list)
+    }
+    m = wave_min(m);
+    __syncthreads();
+    if (tid == 0) {
+      sh.limit = inf;
+      sh.nkeep = 0;
+    }
+    __syncthreads();
+    if (ln == 0) atomicMin((int *)&sh.limit, __float_as_int(m));
+    __syncthreads();
+    if (et < 0) {
+      float mm = sh.limit;
+      int gave_up = 0;
+      bool ov = sh.ovf != 0;
+      if (G > 1) {
+        uint64_t *r2 = a.own.rec2 + (slow & 1) * G;
+        const uint32_t tag2 = delta_tag(slow);
+        if (ln == 0)
+          store_relaxed_u64(&r2[w], ((uint64_t)tag2 << 51) | ((uint64_t)(ov ? 1u : 0u) << 32) |
+                                        __float_as_uint(mm));
+        const uint64_t t0 = wall_clock64();
+        for (;;) {
+          bool ok = true, o1 = false;
+          mm = inf;
+          for (int sd = ln; sd < G; sd += 64) {
+            const uint64_t x = load_relaxed_u64(&r2[sd]);
+            ok &= (uint32_t)(x >> 51) == tag2;
+            mm = fminf(mm, __uint_as_float((uint32_t)x));
+            o1 |= ((x >> 32) & 1ull) != 0;
+          }
+          if (__ballot(!ok) == 0ull) {
+            mm = wave_min(mm);
+            ov = __ballot(o1) != 0ull;
+            break;
+          }
+          if (wall_clock64() - t0 >= wait_ticks) {
+            gave_up = 1;
+            break;
+          }
+        }
+      }
+      if (ln == 0) {
+        sh.gave_up = gave_up;
+        sh.limit = mm;
+        sh.state = ov ? kDeltaSpill : kDeltaGo;
+      }
+    }
+    ++slow;
+    __syncthreads();
+    const float mm = sh.limit;
+    if (sh.gave_up || sh.state == kDeltaSpill) {
+      spill = true;
+      break;
+    }
+    if (!(mm < inf)) break;  // nothing pending anywhere: done
+    const float was = limit;
+    limit = (floorf(mm / a.delta) + 1.0f) * a.delta;
+    if (!(mm < limit)) limit = __uint_as_float(__float_as_uint(mm) + 1u);  // rounding: past mm
+    // split the far list in place, kOwnThreads entries at a time
+    if (tid == 0) sh.cnt[cur] = 0;
+    for (int b = 0; b < nf; b += kOwnThreads) {
+      const int i = b + tid;
+      const int l = i < nf ? sh.far[i] : 0;
+      const float x = i < nf ? sh.dist[l] : inf;
+      __syncthreads();
+      // entries below the old limit were relaxed since they joined the list
+      bool add = false;
+      const bool keep = i < nf && x >= limit;
+      if (i < nf && !keep) {
+        atomicAnd(&sh.fbit[l >> 5], ~(1u << (l & 31)));
+        if (x >= was) add = !((atomicOr(&sh.nbit[l >> 5], 1u << (l & 31)) >> (l & 31)) & 1u);
+      }
+      const bool an[1] = {add}, kp[1] = {keep};
+      const int la[1] = {l};
+      list_add<1>(sh, pend, lo, an, la, &sh.cnt[cur], sh.near[cur], kNearCap);
+      list_add<1>(sh, pend, lo, kp, la, &sh.nkeep, sh.far, kFarCap);
+      __syncthreads();
+    }
+    __syncthreads();
+    n = min(sh.cnt[cur], kNearCap);
+    npre = 0;
+    if (tid == 0) sh.nfar = sh.nkeep;
+    __syncthreads();
+  }
+  // distances and, where the loop hands over, the pending vertices
+  for (int i = tid; i < nv; i += kOwnThreads) a.dist[lo + i] = sh.dist[i];
+  if (spill) {
+    const int nf = min(sh.nfar, kFarCap);
+    for (int i = tid; i < n + nf; i += kOwnThreads) {
+      const int c = lo + (i < n ? sh.near[cur][i] : sh.far[i - n]);
+      atomicOr((unsigned long long *)&pend[c >> 6], 1ull << (c & 63));
+    }
+  }
+  if (tid == 0) {
+    atomicMin(&a.ctrl->small_levels, d);
+    if (spill) atomicOr(&a.ctrl->spilled, 1);
+  }
+}
+
+// After a loop that spilled: every message still in the boxes is applied
+// (most were: then it lowers nothing), its target joining the pending bitmap
+// where it does ...
+__global__ __launch_bounds__(kBlock) void k_sssp_delta_own_boxes(SsspArgs a, uint64_t *pend) {
+  if (!a.ctrl->spilled) return;
+  const int G = a.own.groups, cap = a.own.cap;
+  if (G > 1) {
+    const int64_t m = (int64_t)2 * G * G * cap, nt = (int64_t)gridDim.x * kBlock;
+    for (int64_t t = (int64_t)blockIdx.x * kBlock + threadIdx.x; t < m; t += nt) {
+      const int64_t pair = t / cap;
+      const int j = (int)(t % cap), par = (int)(pair / ((int64_t)G * G));
+      const int sd = (int)(pair / G % G), o = (int)(pair % G);
+      const uint64_t *rec = a.own.rec + 2 * (((int64_t)par * G + o) * G + sd);
+      if (j >= ((int)(rec[1] >> 2) & 8191)) continue;
+      const uint64_t x = j == 0 ? rec[0] : a.own.box64[t];
+      const int c = o * a.own.chunk + ((int)(x >> 32) & 0x7ffff);
+      const float nd = __uint_as_float((uint32_t)x);
+      if (nd < __int_as_float(atomicMin((int *)&a.dist[c], __float_as_int(nd))))
+        atomicOr((unsigned long long *)&pend[c >> 6], 1ull << (c & 63));
+    }
+  }
+  if (blockIdx.x == 0 && threadIdx.x == 0)
+    for (int i = 0; i < 3 * kDeltaSlots; ++i)
+      a.ctrl->lists[i] = (i % kDeltaFields) == 3 ? INT_MAX : 0;
+}
+
+// ... then the bitmap (pend = F1) becomes that of round h =
+// ctrl->small_levels for the round kernel, with the round's counters.
+__global__ __launch_bounds__(kBlock) void k_sssp_delta_own_handover(SsspArgs a, uint64_t *F0,
+                                                                     uint64_t *F1, uint64_t *F2) {
+  if (!a.ctrl->spilled) return;
+  const int h = a.ctrl->small_levels;
+  uint64_t *const F[3] = {F0, F1, F2};
+  const float limit = (float)(a.ctrl->bucket + 1) * a.delta;
+  const int ln = threadIdx.x & 63;
+  const int64_t gw = (int64_t)blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6);
+  const int64_t nwaves = (int64_t)gridDim.x * kWavesPerBlock;
+  DCount c;
+  for (int64_t w0 = gw * 64; w0 < a.nw; w0 += nwaves * 64) {
+    const int64_t mw = w0 + ln;
+    const uint64_t x = mw < a.nw ? F1[mw] : 0ull;
+    if (mw < a.nw) {
+      F0[mw] = F1[mw] = F2[mw] = 0ull;
+      F[h % 3][mw] = x;
+    }
+    for (uint64_t any = __ballot(x != 0ull); any; any &= any - 1) {
+      const int k = __ffsll((unsigned long long)any) - 1;
+      const uint64_t xk = __shfl(x, k);
+      const int64_t v = (w0 + k) * 64 + ln;
+      if ((xk >> ln) & 1ull) count_new(a, a.push.rp[v + 1] - a.push.rp[v], a.dist[v], limit, c);
+    }
+  }
+  c.near = wave_sum(c.near);
+  c.sd = wave_sum(c.sd);
+  c.pend = wave_sum(c.pend);
+  c.far = lane_last(wave_scan(c.far, INT_MAX, [](int x, int y) { return x < y ? x : y; }));
+  if (ln == 0 && c.pend) {  // rows are at most kCoopMaxDeg long: none has pieces
+    int32_t *cnt = a.ctrl->lists + (h % 3) * kDeltaSlots + kDeltaFields * (gw % kCntStripes);
+    atomicAdd(&cnt[0], c.near);
+    atomicAdd(&cnt[1], c.sd);
+    if (c.far != INT_MAX) atomicMin(&cnt[3], c.far);
+    atomicAdd(&cnt[4], c.pend);
+  }
+}
+
+// ---- bucket rounds of larger graphs: a queue in device memory ----------------
 // The pending set as a queue in device memory (one segment per wave of the
 // loop; entries: vertex, row start | degree << 32) with membership bits in
 // F0 / F1 (round d consumes F[d & 1] and fills F[(d + 1) & 1]).  A vertex
@@ -574,6 +1182,19 @@ __global__ __launch_bounds__(kBlock) void k_sssp_delta_coop_handover(SsspArgs a,
 }
 
 }  // namespace
+
+void launch_sssp_delta_own(const SsspArgs &a, int32_t source, int64_t max_rounds,
+                           uint64_t *const F[3], uint64_t wait_ticks, void *stream) {
+  hipStream_t s = (hipStream_t)stream;
+  const int cap = (int)std::min<int64_t>(max_rounds, kOwnMaxLevels + 1);
+  hipLaunchKernelGGL(k_sssp_delta_own, dim3(a.own.groups), dim3(kOwnThreads), 0, s, a, source, cap,
+                     wait_ticks, F[1]);
+  hipLaunchKernelGGL(k_sssp_delta_own_boxes, dim3(256), dim3(kBlock), 0, s, a, F[1]);
+  int64_t gh = (a.nw + kBlock - 1) / kBlock;
+  gh = gh < 1 ? 1 : (gh > kExpandGrid ? kExpandGrid : gh);
+  hipLaunchKernelGGL(k_sssp_delta_own_handover, dim3((unsigned)gh), dim3(kBlock), 0, s, a, F[0],
+                     F[1], F[2]);
+}
 
 void launch_sssp_delta_coop(const SsspArgs &a, int64_t max_rounds, uint64_t *const F[3],
                             uint64_t wait_ticks, void *stream) {
