@@ -193,7 +193,7 @@ struct MsWs {
   Ctrl *ctrl;
   int64_t *stats;
   unsigned long long *cnt;
-  uint64_t *V, *F[3], *act[3];
+  uint64_t *V, *S, *F[2], *act[3];
   // sessions: start level per query, three "has a frontier bit" arrays of W
   // words, the joining queries' bits per word, lane / source staging
   int32_t *start, *lanes, *sources;
@@ -210,7 +210,8 @@ MsWs ms_layout(void *ws, int64_t n, int64_t k) {
   t.stats = c.take<int64_t>((size_t)kStatsCap * kStatFields);
   t.cnt = c.take<unsigned long long>((size_t)6 * kCntStripes);
   t.V = c.take<uint64_t>((size_t)nb);
-  for (int i = 0; i < 3; ++i) t.F[i] = c.take<uint64_t>((size_t)nb);
+  t.S = c.take<uint64_t>((size_t)nb);
+  for (int i = 0; i < 2; ++i) t.F[i] = c.take<uint64_t>((size_t)nb);
   for (int i = 0; i < 3; ++i) t.act[i] = c.take<uint64_t>((size_t)std::max<int64_t>(nw, 1));
   t.start = c.take<int32_t>((size_t)std::max<int64_t>(k, 1));
   t.lanes = c.take<int32_t>((size_t)std::max<int64_t>(k, 1));
@@ -1498,6 +1499,7 @@ grb_info grb_msbfs(int32_t *levels, grb_matrix A, const int32_t *sources, int32_
   ma.can_pull = can_pull;
   ma.levels = levels;
   ma.V = w.V;
+  ma.S = w.S;
   ma.cnt_base = w.cnt;
   ma.ctrl = w.ctrl;
   ma.stats = w.stats;
@@ -1506,9 +1508,8 @@ grb_info grb_msbfs(int32_t *levels, grb_matrix A, const int32_t *sources, int32_
   ma.forced = desc.direction;
   auto at_level = [&](int64_t dd) {
     const int i = (int)(dd % 3), j = (int)((dd + 1) % 3), q = (int)((dd + 2) % 3);
-    ma.F = w.F[i];
-    ma.Fn = w.F[j];
-    ma.Fc = w.F[q];
+    ma.F = w.F[dd & 1];
+    ma.Fn = w.F[(dd + 1) & 1];
     ma.act = w.act[i];
     ma.actn = w.act[j];
     ma.actc = w.act[q];
@@ -1518,7 +1519,7 @@ grb_info grb_msbfs(int32_t *levels, grb_matrix A, const int32_t *sources, int32_
     ma.d = (int32_t)std::min<int64_t>(dd, INT32_MAX);
   };
   at_level(0);
-  launch_msbfs_start(ma, sources, w.F[1], w.F[2], w.act[1], w.act[2], stream);
+  launch_msbfs_start(ma, sources, w.act[1], w.act[2], stream);
   const int64_t cap = desc.max_iter > 0 ? desc.max_iter : INT64_MAX;
   int64_t dlev = 0;
   int chunk = 6;
@@ -1579,9 +1580,8 @@ namespace {
 void session_level(grb_msbfs_session_s &ss, int64_t dd) {
   const int i = (int)(dd % 3), j = (int)((dd + 1) % 3), q = (int)((dd + 2) % 3);
   MsbfsArgs &ma = ss.ma;
-  ma.F = ss.w.F[i];
-  ma.Fn = ss.w.F[j];
-  ma.Fc = ss.w.F[q];
+  ma.F = ss.w.F[dd & 1];
+  ma.Fn = ss.w.F[(dd + 1) & 1];
   ma.act = ss.w.act[i];
   ma.actn = ss.w.act[j];
   ma.actc = ss.w.act[q];
@@ -1647,6 +1647,7 @@ grb_info grb_msbfs_session_create(grb_msbfs_session *ss, grb_matrix A, int32_t k
   ma.can_pull = can_pull;
   ma.levels = levels;
   ma.V = w.V;
+  ma.S = w.S;
   ma.cnt_base = w.cnt;
   ma.ctrl = w.ctrl;
   ma.stats = nullptr;
@@ -1655,7 +1656,7 @@ grb_info grb_msbfs_session_create(grb_msbfs_session *ss, grb_matrix A, int32_t k
   ma.forced = desc.direction;
   ma.start = w.start;
   session_level(*x, 0);
-  launch_msbfs_session_init(ma, w.F[1], w.F[2], w.act[1], w.act[2], w.alive, stream);
+  launch_msbfs_session_init(ma, w.act[1], w.act[2], w.alive, stream);
   if ((info = check_launch()) != GRB_SUCCESS) {
     delete x;
     return info;

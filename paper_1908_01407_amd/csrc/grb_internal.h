@@ -388,7 +388,8 @@ struct MsbfsArgs {
   bool can_pull = true;
   int32_t *levels = nullptr;  // n x k, vertex-major
   uint64_t *V = nullptr;      // visited, n x W
-  uint64_t *F = nullptr, *Fn = nullptr, *Fc = nullptr;      // frontier blocks
+  uint64_t *S = nullptr;      // visited or found by the running level; V between levels
+  uint64_t *F = nullptr, *Fn = nullptr;                       // frontier blocks
   uint64_t *act = nullptr, *actn = nullptr, *actc = nullptr;  // vertex has a frontier bit
   unsigned long long *cnt_cur = nullptr, *cnt_nxt = nullptr, *cnt_clr = nullptr, *cnt_base = nullptr;
   Ctrl *ctrl = nullptr;
@@ -401,12 +402,12 @@ struct MsbfsArgs {
   const int32_t *start = nullptr;
   unsigned long long *alive_nxt = nullptr, *alive_clr = nullptr;
 };
-void launch_msbfs_start(const MsbfsArgs &a, const int32_t *sources, uint64_t *F1, uint64_t *F2,
-                        uint64_t *act1, uint64_t *act2, void *stream);
+void launch_msbfs_start(const MsbfsArgs &a, const int32_t *sources, uint64_t *act1, uint64_t *act2,
+                        void *stream);
 void launch_msbfs_level(const MsbfsArgs &a, int grid_x, void *stream);
-// sessions: every query idle (its bits set in V), blocks and counters cleared
-void launch_msbfs_session_init(const MsbfsArgs &a, uint64_t *F1, uint64_t *F2, uint64_t *act1,
-                               uint64_t *act2, unsigned long long *alive3, void *stream);
+// sessions: every query idle (its bits set in V and S), blocks and counters cleared
+void launch_msbfs_session_init(const MsbfsArgs &a, uint64_t *act1, uint64_t *act2,
+                               unsigned long long *alive3, void *stream);
 // sessions: queries lanes[i] start from sources[i] at level a.d (device
 // arrays of `count` entries; clr[W] holds the joining queries' bits per word)
 void launch_msbfs_session_join(const MsbfsArgs &a, const int32_t *lanes, const int32_t *sources,

@@ -3,23 +3,36 @@
 // multi-nodeset traversal with mxm, Table 6 and Section 3.3; matrix-matrix
 // direction optimisation is its stated future work, Section 9).
 //
-// F (frontier) and V (visited) are n x W blocks of uint64 words, vertex
-// major: word j of vertex v holds queries 64j .. 64j+63.  A level runs one
-// kernel over a 2-D grid: blockIdx.y picks a tile of kt query words.
+// F (frontier), V (visited before this level) and S (seen: V and what the
+// running level has found) are n x W blocks of uint64 words, vertex major:
+// word j of vertex v holds queries 64j .. 64j+63.  A level is two kernels.
+// The expansion, over a 2-D grid (blockIdx.y picks a tile of kt query words),
+// only adds to S and to the bitmap of the vertices it found:
 // * pull: each wave owns 64 consecutive vertices; for the tile's words of
 //   every vertex with an unvisited query, the in-edges are streamed as one
 //   concatenated list, 64 per step, and the neighbours' frontier words are
 //   OR-reduced per row with a segmented scan; a row stops as soon as every
 //   unvisited query of the tile is found (early exit of the Boolean
 //   semiring, per query word);
-// * push: each wave owns one word of the "active vertex" bitmap; the
-//   out-edges of active rows are streamed the same way and each target is
-//   claimed with atomicOr on its visited word, so every (vertex, query) is
-//   discovered exactly once; rows longer than kPushSplit use the static
-//   256-edge pieces;
-// * discoveries write their level (vertex-major output, coalesced per row)
-//   and set the next frontier and the next active bitmap; frontier sizes
-//   for the device-side direction choice go to striped counters.
+// * push: the active vertices are dealt to the waves in groups of 16 and
+//   compacted into queues of rows; their out-edges are streamed as one
+//   concatenated list, kUnroll x 64 per step, and what a target has not seen
+//   is ORed into its seen word (one gather per edge, one atomic per claim
+//   whose result nobody waits for); rows longer than kPushSplit use the
+//   static 256-edge pieces.
+// The commit then takes each found vertex once: S & ~V becomes its frontier
+// word, V = S, its levels are written (vertex-major output, one coalesced
+// store per row), and the frontier's sizes for the next level's direction
+// choice are counted.
+//
+// Why: a vertex is reached over many edges, and when the push wrote levels
+// and counted at each claim it was visited as often, with three returning
+// atomics and a store loop over the wave's lanes.  RMAT-20 (31.4M edges), 64
+// queries, the two push levels (4.2M and 30.7M edges): 471 + 1065 us then,
+// 196 + 40 and 785 + 65 us now (expansion + commit); the pulls 229 -> 178 +
+// 44 us.  Of the 785 us the stream's bookkeeping and loads are 180, the
+// gather 250 and the atomics 280; more workgroups do not change it, and
+// reading V and the next frontier in place of S, two gathers, took 900.
 #include <hip/hip_runtime.h>
 
 #include "grb_device.h"
@@ -50,45 +63,28 @@ __device__ __forceinline__ int ms_decide(const MsbfsArgs &a, int64_t active, int
   return pull ? GRB_DIR_PULL : GRB_DIR_PUSH;
 }
 
-// Writes level d+1 for the new bits of (v, word j) held by each lane:
-// the wave visits every lane with new bits and stores its 64 levels with
-// one coalesced store.
-// In a session the level is relative to the query's start level, and the
-// new bits are ORed into the workgroup's per-word "has a frontier bit"
-// words (s_alive, indexed by word - first word of the pass).
-__device__ __forceinline__ void write_levels(const MsbfsArgs &a, int64_t v, int j,
-                                             uint64_t newbits, unsigned long long *s_alive) {
-  const int ln = threadIdx.x & 63;
-  uint64_t todo = __ballot(newbits != 0ull);
-  const int j0 = blockIdx.y * a.kt;
-  while (todo) {
-    const int r = __ffsll((unsigned long long)todo) - 1;
-    todo &= todo - 1;
-    const int64_t rv = __shfl(v, r);
-    const int rj = __shfl(j, r);
-    const uint64_t nb = __shfl(newbits, r);
-    const int64_t q = (int64_t)rj * 64 + ln;
-    if (((nb >> ln) & 1ull) && q < a.k)
-      a.levels[rv * a.k + q] = a.d + 1 - (a.start ? a.start[q] : 0);
-    if (a.alive_nxt && ln == 0) atomicOr(&s_alive[rj - j0], (unsigned long long)nb);
+// ORs bits into the seen word (v, j) where the queries are not there yet, for
+// kUnroll targets at once (tv < 0: none), and marks the vertex.  Both reads
+// are filters: bits ORed twice, or a vertex marked twice, change nothing.
+__device__ __forceinline__ void claim_batch(const MsbfsArgs &a, const int (&tv)[kUnroll], int j,
+                                            const uint64_t (&bits)[kUnroll]) {
+  uint64_t nb[kUnroll], mk[kUnroll];
+#pragma unroll
+  for (int s = 0; s < kUnroll; ++s)
+    nb[s] = tv[s] >= 0 ? a.S[(int64_t)tv[s] * a.W + j] : ~0ull;
+#pragma unroll
+  for (int s = 0; s < kUnroll; ++s) nb[s] = bits[s] & ~nb[s];
+#pragma unroll
+  for (int s = 0; s < kUnroll; ++s) mk[s] = nb[s] ? a.actn[tv[s] >> 6] : ~0ull;
+#pragma unroll
+  for (int s = 0; s < kUnroll; ++s)
+    if (nb[s])
+      atomicOr((unsigned long long *)&a.S[(int64_t)tv[s] * a.W + j], (unsigned long long)nb[s]);
+#pragma unroll
+  for (int s = 0; s < kUnroll; ++s) {
+    const uint64_t bit = 1ull << (tv[s] & 63);
+    if (!(mk[s] & bit)) atomicOr((unsigned long long *)&a.actn[tv[s] >> 6], bit);
   }
-}
-
-// Claim the query bits `bits` of vertex v, word j, for the next level.
-__device__ __forceinline__ uint64_t claim_bits(const MsbfsArgs &a, int64_t v, int j, uint64_t bits,
-                                               int64_t &edges_acc) {
-  if (bits == 0ull) return 0ull;
-  uint64_t *vw = &a.V[v * a.W + j];
-  bits &= ~*vw;  // plain read: a filter, the atomic decides
-  if (bits == 0ull) return 0ull;
-  const uint64_t old = atomicOr((unsigned long long *)vw, (unsigned long long)bits);
-  const uint64_t nb = bits & ~old;
-  if (nb) {
-    const uint64_t pf = atomicOr((unsigned long long *)&a.Fn[v * a.W + j], (unsigned long long)nb);
-    if (pf == 0ull) edges_acc += a.push.rp[v + 1] - a.push.rp[v];
-    atomicOr((unsigned long long *)&a.actn[v >> 6], 1ull << (v & 63));
-  }
-  return nb;
 }
 
 // Pull over the pass's query words j0 .. j0 + nj - 1 (nj <= L <= 8): an edge
@@ -100,8 +96,7 @@ __device__ __forceinline__ uint64_t claim_bits(const MsbfsArgs &a, int64_t v, in
 // found.  Rows longer than kPushSplit are left to the pieces below, which
 // claim with atomics like push.
 template <int L>
-__device__ void ms_pull_rows(const MsbfsArgs &a, int *mark, int64_t &act_acc,
-                             int64_t &edges_acc, unsigned long long *s_alive) {
+__device__ void ms_pull_rows(const MsbfsArgs &a, int *mark) {
   constexpr int S = 64 / L;
   const int ln = threadIdx.x & 63;
   const int sl = ln / L, jl = ln % L;
@@ -195,26 +190,20 @@ __device__ void ms_pull_rows(const MsbfsArgs &a, int *mark, int64_t &act_acc,
       }
       // found bits: this wave owns row v in pull
       bool anyb = false;
-      int64_t e_add = 0;
 #pragma unroll
       for (int q = 0; q < L; ++q) {
         const uint64_t nb = acc[q] & need[q];
         if (nb) {
-          a.V[v * a.W + j0 + q] |= nb;
-          a.Fn[v * a.W + j0 + q] = nb;
-          act_acc += __popcll(nb);
+          a.S[v * a.W + j0 + q] = ~(need[q] & ~nb);  // V | nb
           anyb = true;
-          e_add += a.push.rp[v + 1] - a.push.rp[v];
         }
-        write_levels(a, v, j0 + q, nb, s_alive);
       }
-      edges_acc += e_add;
       const uint64_t ab = __ballot(anyb);
       if (ab && ln == 0) atomicOr((unsigned long long *)&a.actn[w], (unsigned long long)ab);
     }
   }
   // pieces of long rows: OR of the piece's neighbours' frontier words, then
-  // claims like push (kPushSplit edges: S per sub-step)
+  // into the row's words like push (kPushSplit edges: S per sub-step)
   for (int64_t h = gw; h < a.pull.nsplit; h += nwaves) {
     const int r = a.pull.split[2 * h], b = a.pull.split[2 * h + 1];
     const int e = min(b + kPushSplit, rp[r + 1]);
@@ -234,73 +223,86 @@ __device__ void ms_pull_rows(const MsbfsArgs &a, int *mark, int64_t &act_acc,
       for (int u = 0; u < kUnroll; ++u) acc |= f[u];
       if (__ballot((acc & need) != need) == 0ull) break;  // every word complete
     }
-    // OR over the slots (lanes L apart) and claim in lanes 0 .. L-1
+    // OR over the slots (lanes L apart), into the words by lanes 0 .. L-1
 #pragma unroll
     for (int off = L; off < 64; off <<= 1) acc |= __shfl_xor(acc, off);
-    int64_t ea = 0;
-    uint64_t nb = 0ull;
-    if (sl == 0 && jv) nb = claim_bits(a, r, j0 + jl, acc & need, ea);
-    act_acc += sl == 0 ? __popcll(nb) : 0;
-    edges_acc += ea;
-    write_levels(a, sl == 0 ? (int64_t)r : -1, j0 + jl, sl == 0 ? nb : 0ull, s_alive);
+    const uint64_t nb = sl == 0 && jv ? acc & need : 0ull;
+    if (nb) atomicOr((unsigned long long *)&a.S[(int64_t)r * a.W + j0 + jl], (unsigned long long)nb);
+    if (__ballot(nb != 0ull) && ln == 0)
+      atomicOr((unsigned long long *)&a.actn[r >> 6], 1ull << (r & 63));
   }
 }
 
-__device__ void ms_pull(const MsbfsArgs &a, int *mark, int64_t &act_acc, int64_t &edges_acc,
-                        unsigned long long *s_alive) {
-  if (a.kt <= 1) ms_pull_rows<1>(a, mark, act_acc, edges_acc, s_alive);
-  else if (a.kt <= 2) ms_pull_rows<2>(a, mark, act_acc, edges_acc, s_alive);
-  else if (a.kt <= 4) ms_pull_rows<4>(a, mark, act_acc, edges_acc, s_alive);
-  else ms_pull_rows<8>(a, mark, act_acc, edges_acc, s_alive);
+__device__ void ms_pull(const MsbfsArgs &a, int *mark) {
+  if (a.kt <= 1) ms_pull_rows<1>(a, mark);
+  else if (a.kt <= 2) ms_pull_rows<2>(a, mark);
+  else if (a.kt <= 4) ms_pull_rows<4>(a, mark);
+  else ms_pull_rows<8>(a, mark);
 }
 
-__device__ void ms_push(const MsbfsArgs &a, int *mark, int64_t &act_acc, int64_t &edges_acc,
-                        unsigned long long *s_alive) {
+// Active vertices are dealt out in groups of 16, a quarter of a bitmap word:
+// rows of similar degree have nearby ids, and a wave left with a whole word
+// of the longest unsplit rows ran 16,000 edges alone.
+__device__ void ms_push(const MsbfsArgs &a, int *mark) {
   const int ln = threadIdx.x & 63;
   const int64_t gw = (int64_t)blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6);
   const int64_t nwaves = (int64_t)gridDim.x * kWavesPerBlock;
   const int32_t *rp = a.push.rp, *ci = a.push.ci;
   const int j0 = blockIdx.y * a.kt;
-  for (int64_t w = gw; w < a.nw; w += nwaves) {
-    const uint64_t aw = a.act[w];
-    if (aw == 0ull) continue;
-    const int64_t u = w * 64 + ln;
-    int rs = 0, re = 0;
-    if ((aw >> ln) & 1ull) {
-      rs = rp[u];
-      re = rp[u + 1];
-      if (re - rs > kPushSplit) re = rs;  // long rows: static pieces below
-    }
-    for (int jj = 0; jj < a.kt; ++jj) {
-      const int j = j0 + jj;
-      if (j >= a.W) break;
-      const uint64_t fu = (re > rs) ? a.F[u * a.W + j] : 0ull;
-      int cur = rs;
-      const int end = fu ? re : rs;
-      for (;;) {
-        const int len = end - cur;
-        const int incl = wave_incl_scan(len);
-        const int total = lane_last(incl);
-        if (total == 0) break;
-        const int excl = incl - len;
-        const bool starts = len > 0 && excl < 64;
-        const int r = slot_rows(mark, starts, excl);
-        const int rcur = __shfl(cur, r), rexcl = __shfl(excl, r);
-        const uint64_t rf = __shfl(fu, r);
-        int64_t tv = -1;
-        uint64_t nb = 0ull;
-        if (ln < total) {
-          tv = ci[rcur + (ln - rexcl)];
-          nb = claim_bits(a, tv, j, rf, edges_acc);
-          act_acc += __popcll(nb);
+  const int nj = min(a.kt, a.W - j0);
+  for (int64_t u0 = gw; u0 < 4 * a.nw; u0 += 64 * nwaves) {
+    const int64_t un = u0 + (int64_t)ln * nwaves;  // group of 16 vertices
+    uint64_t m = 0ull;
+    if (un < 4 * a.nw) m = a.act[un >> 2] & (0xffffull << (16 * (un & 3)));
+    const int cnt = __popcll(m);
+    const int incl = wave_incl_scan(cnt);
+    const int total = lane_last(incl);
+    for (int b = 0; b < total; b += 64) {
+      const int64_t u = queue_slot(mark, m, cnt, incl, total, b, un >> 2);
+      int rs = 0, re = 0;
+      if (u >= 0) {
+        rs = rp[u];
+        re = rp[u + 1];
+        if (re - rs > kPushSplit) re = rs;  // long rows: static pieces below
+      }
+      for (int jj = 0; jj < nj; ++jj) {
+        const int j = j0 + jj;
+        const uint64_t fu = (re > rs) ? a.F[u * a.W + j] : 0ull;
+        int cur = rs;
+        const int end = fu ? re : rs;
+        for (bool more = true; more;) {
+          int tv[kUnroll];
+          uint64_t bits[kUnroll];
+#pragma unroll
+          for (int s = 0; s < kUnroll; ++s) {
+            tv[s] = -1;
+            bits[s] = 0ull;
+            if (!more) continue;
+            const int len = end - cur;
+            const int incl2 = wave_incl_scan(len);
+            const int tot2 = lane_last(incl2);
+            if (tot2 == 0) {
+              more = false;
+              continue;
+            }
+            const int excl = incl2 - len;
+            const bool starts = len > 0 && excl < 64;
+            const int r = slot_rows(mark, starts, excl);
+            const int rcur = __shfl(cur, r), rexcl = __shfl(excl, r);
+            bits[s] = __shfl(fu, r);
+            if (ln < tot2) tv[s] = rcur + (ln - rexcl);
+            if (starts) cur += min(incl2, 64) - excl;
+          }
+#pragma unroll
+          for (int s = 0; s < kUnroll; ++s) tv[s] = tv[s] >= 0 ? ci[tv[s]] : -1;
+          claim_batch(a, tv, j, bits);
         }
-        write_levels(a, tv, j, nb, s_alive);
-        if (starts) cur += min(incl, 64) - excl;
       }
     }
   }
   // static pieces of long rows, spread over the waves (wave gw owns pieces
   // gw, gw + nwaves, ...), 64 tested per step
+  static_assert(kPushSplit == 64 * kUnroll, "a piece is one unrolled step");
   for (int64_t hb = gw; hb < a.push.nsplit; hb += 64 * nwaves) {
     const int64_t h = hb + (int64_t)ln * nwaves;
     int u = -1, b = 0, e = 0;
@@ -315,22 +317,19 @@ __device__ void ms_push(const MsbfsArgs &a, int *mark, int64_t &act_acc, int64_t
       const int kk = __ffsll((unsigned long long)act) - 1;
       act &= act - 1;
       const int pu = __shfl(u, kk), pb = __shfl(b, kk), pe = __shfl(e, kk);
-      for (int jj = 0; jj < a.kt; ++jj) {
-        const int j = j0 + jj;
-        if (j >= a.W) break;
-        const uint64_t fu = a.F[(int64_t)pu * a.W + j];
+      int tv[kUnroll];
+#pragma unroll
+      for (int s = 0; s < kUnroll; ++s) {
+        const int pos = pb + s * 64 + ln;
+        tv[s] = pos < pe ? ci[pos] : -1;
+      }
+      for (int jj = 0; jj < nj; ++jj) {
+        const uint64_t fu = a.F[(int64_t)pu * a.W + j0 + jj];
         if (fu == 0ull) continue;
-        for (int base = pb; base < pe; base += 64) {
-          const int pos = base + ln;
-          int64_t tv = -1;
-          uint64_t nb = 0ull;
-          if (pos < pe) {
-            tv = ci[pos];
-            nb = claim_bits(a, tv, j, fu, edges_acc);
-            act_acc += __popcll(nb);
-          }
-          write_levels(a, tv, j, nb, s_alive);
-        }
+        uint64_t bits[kUnroll];
+#pragma unroll
+        for (int s = 0; s < kUnroll; ++s) bits[s] = fu;
+        claim_batch(a, tv, j0 + jj, bits);
       }
     }
   }
@@ -339,10 +338,7 @@ __device__ void ms_push(const MsbfsArgs &a, int *mark, int64_t &act_acc, int64_t
 __global__ __launch_bounds__(kBlock) void k_ms_level(MsbfsArgs a) {
   __shared__ int s_mark[kWavesPerBlock][64];
   __shared__ int64_t s_act, s_edges;
-  __shared__ int64_t s_red[kWavesPerBlock][2];
-  __shared__ unsigned long long s_alive[kMsMaxWordsPerPass];
   const bool leader = blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0;
-  if (threadIdx.x < kMsMaxWordsPerPass) s_alive[threadIdx.x] = 0ull;
   if (threadIdx.x == 0) {
     int64_t c = 0, e = 0;
     for (int t = 0; t < kCntStripes; ++t) {
@@ -366,9 +362,10 @@ __global__ __launch_bounds__(kBlock) void k_ms_level(MsbfsArgs a) {
     }
   }
   __syncthreads();
-  // clear the frontier block two levels ahead: only rows its active bitmap
-  // marks can be non-zero; tile 0 clears all words of those rows, then the
-  // bitmap word (the same thread reads and clears it, no other tile reads it)
+  // clear the block that the commit writes the next frontier into; it holds
+  // the previous level's, so only rows marked in that level's bitmap can be
+  // non-zero: tile 0 clears all words of those rows, then the bitmap word (the
+  // same thread reads and clears it, no other tile reads it)
   if (blockIdx.y == 0) {
     for (int64_t w = (int64_t)blockIdx.x * kBlock + threadIdx.x; w < a.nw;
          w += (int64_t)gridDim.x * kBlock) {
@@ -377,29 +374,69 @@ __global__ __launch_bounds__(kBlock) void k_ms_level(MsbfsArgs a) {
       while (aw) {
         const int b = __ffsll((unsigned long long)aw) - 1;
         aw &= aw - 1;
-        uint64_t *row = a.Fc + (w * 64 + b) * a.W;
+        uint64_t *row = a.Fn + (w * 64 + b) * a.W;
         for (int j = 0; j < a.W; ++j) row[j] = 0ull;
       }
       a.actc[w] = 0ull;
     }
   }
   if (s_act == 0) return;
-  const int dir = ms_decide(a, s_act, s_edges);
-  int64_t act_acc = 0, edges_acc = 0;
-  if (dir == GRB_DIR_PUSH) ms_push(a, s_mark[threadIdx.x >> 6], act_acc, edges_acc, s_alive);
-  else ms_pull(a, s_mark[threadIdx.x >> 6], act_acc, edges_acc, s_alive);
-  act_acc = wave_sum64(act_acc);
-  const int64_t ed = wave_sum64(edges_acc);
-  if ((threadIdx.x & 63) == 0) {
-    s_red[threadIdx.x >> 6][0] = act_acc;
-    s_red[threadIdx.x >> 6][1] = ed;
+  if (ms_decide(a, s_act, s_edges) == GRB_DIR_PUSH) ms_push(a, s_mark[threadIdx.x >> 6]);
+  else ms_pull(a, s_mark[threadIdx.x >> 6]);
+}
+
+// The vertices the level found, a wave per word of their bitmap (dealt out
+// round-robin, 64 words tested per step, lane = vertex): V, levels (in a
+// session relative to the query's start level), the next frontier's (vertex,
+// query) pairs and the out-edges of its (vertex, query word) pairs, and in a
+// session the queries that have a frontier bit.
+__global__ __launch_bounds__(kBlock) void k_ms_commit(MsbfsArgs a) {
+  __shared__ int64_t s_red[kWavesPerBlock][2];
+  const int ln = threadIdx.x & 63;
+  const int64_t gw = (int64_t)blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6);
+  const int64_t nwaves = (int64_t)gridDim.x * kWavesPerBlock;
+  int64_t pairs = 0, edges = 0;
+  for (int64_t w0 = gw; w0 < a.nw; w0 += 64 * nwaves) {
+    const int64_t mw = w0 + (int64_t)ln * nwaves;
+    const uint64_t m = mw < a.nw ? a.actn[mw] : 0ull;
+    for (uint64_t any = __ballot(m != 0ull); any; any &= any - 1) {
+      const int k = __ffsll((unsigned long long)any) - 1;
+      const uint64_t mk = __shfl(m, k);
+      const int64_t v0 = (w0 + (int64_t)k * nwaves) * 64, v = v0 + ln;
+      const bool on = (mk >> ln) & 1ull;
+      const int deg = on ? a.push.rp[v + 1] - a.push.rp[v] : 0;
+      for (int j = 0; j < a.W; ++j) {
+        const uint64_t seen = on ? a.S[v * a.W + j] : 0ull;
+        const uint64_t f = on ? seen & ~a.V[v * a.W + j] : 0ull;
+        if (f) {
+          a.V[v * a.W + j] = seen;
+          a.Fn[v * a.W + j] = f;
+          pairs += __popcll(f);
+          edges += deg;
+        }
+        const int64_t q = (int64_t)j * 64 + ln;
+        const int lev = a.d + 1 - (a.start && q < a.k ? a.start[q] : 0);
+        const int flo = (int)(uint32_t)f, fhi = (int)(uint32_t)(f >> 32);
+        uint64_t all = 0ull;
+        for (uint64_t rows = __ballot(f != 0ull); rows; rows &= rows - 1) {
+          const int r = __builtin_amdgcn_readfirstlane(__ffsll((unsigned long long)rows) - 1);
+          const uint64_t nb = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane(fhi, r) << 32) |
+                              (uint32_t)__builtin_amdgcn_readlane(flo, r);
+          all |= nb;
+          if (((nb >> ln) & 1ull) && q < a.k) a.levels[(v0 + r) * a.k + q] = lev;
+        }
+        if (a.alive_nxt && ln == 0 && (all & ~a.alive_nxt[j]))
+          atomicOr(&a.alive_nxt[j], (unsigned long long)all);
+      }
+    }
+  }
+  pairs = wave_sum64(pairs);
+  edges = wave_sum64(edges);
+  if (ln == 0) {
+    s_red[threadIdx.x >> 6][0] = pairs;
+    s_red[threadIdx.x >> 6][1] = edges;
   }
   __syncthreads();
-  if (a.alive_nxt && threadIdx.x < kMsMaxWordsPerPass) {
-    const int j = blockIdx.y * a.kt + threadIdx.x;
-    const unsigned long long x = s_alive[threadIdx.x];
-    if (x && j < a.W) atomicOr(&a.alive_nxt[j], x);
-  }
   if (threadIdx.x == 0) {
     int64_t c = 0, e = 0;
     for (int i = 0; i < kWavesPerBlock; ++i) {
@@ -407,7 +444,7 @@ __global__ __launch_bounds__(kBlock) void k_ms_level(MsbfsArgs a) {
       e += s_red[i][1];
     }
     if (c) {
-      const int t = (blockIdx.x + blockIdx.y * 7) % kCntStripes;
+      const int t = blockIdx.x % kCntStripes;
       atomicAdd((unsigned long long *)&a.cnt_nxt[2 * t], (unsigned long long)c);
       atomicAdd((unsigned long long *)&a.cnt_nxt[2 * t + 1], (unsigned long long)e);
     }
@@ -415,18 +452,18 @@ __global__ __launch_bounds__(kBlock) void k_ms_level(MsbfsArgs a) {
 }
 
 // levels = -1, blocks zeroed, sources set
-__global__ void k_ms_start(MsbfsArgs a, const int32_t *sources, uint64_t *F1, uint64_t *F2,
-                           uint64_t *act1, uint64_t *act2) {
+__global__ void k_ms_start(MsbfsArgs a, const int32_t *sources, uint64_t *act1, uint64_t *act2) {
   const int64_t gt = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int64_t nt = (int64_t)gridDim.x * blockDim.x;
   const int64_t nk = a.n * (int64_t)a.k;
   for (int64_t i = gt; i < nk; i += nt) a.levels[i] = -1;
   const int64_t nb = a.n * (int64_t)a.W;
   for (int64_t i = gt; i < nb; i += nt) {
-    a.V[i] = ~qmask(a, (int)(i % a.W));  // queries beyond k count as visited
+    const uint64_t v = ~qmask(a, (int)(i % a.W));  // queries beyond k count as visited
+    a.V[i] = v;
+    a.S[i] = v;
     a.F[i] = 0ull;
-    F1[i] = 0ull;
-    F2[i] = 0ull;
+    a.Fn[i] = 0ull;
   }
   for (int64_t i = gt; i < a.nw; i += nt) {
     a.act[i] = 0ull;
@@ -444,16 +481,16 @@ __global__ void k_ms_start(MsbfsArgs a, const int32_t *sources, uint64_t *F1, ui
 // visited everything, so it never claims); frontier blocks, active
 // bitmaps, counters and the three "has a frontier bit" arrays cleared.  The
 // level block is not touched: a query's levels are valid where its V bit is.
-__global__ void k_ms_session_init(MsbfsArgs a, uint64_t *F1, uint64_t *F2, uint64_t *act1,
-                                  uint64_t *act2, unsigned long long *alive3) {
+__global__ void k_ms_session_init(MsbfsArgs a, uint64_t *act1, uint64_t *act2,
+                                  unsigned long long *alive3) {
   const int64_t gt = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int64_t nt = (int64_t)gridDim.x * blockDim.x;
   const int64_t nb = a.n * (int64_t)a.W;
   for (int64_t i = gt; i < nb; i += nt) {
     a.V[i] = ~0ull;
+    a.S[i] = ~0ull;
     a.F[i] = 0ull;
-    F1[i] = 0ull;
-    F2[i] = 0ull;
+    a.Fn[i] = 0ull;
   }
   for (int64_t i = gt; i < a.nw; i += nt) {
     a.act[i] = 0ull;
@@ -468,14 +505,18 @@ __global__ void k_ms_session_init(MsbfsArgs a, uint64_t *F1, uint64_t *F2, uint6
   }
 }
 
-// Joining queries: their bits cleared in every vertex's V word (clr[j]
+// Joining queries: their bits cleared in every vertex's V and S words (clr[j]
 // holds the joining queries of word j)
 __global__ void k_ms_session_clear(MsbfsArgs a, const uint64_t *clr) {
   const int64_t nb = a.n * (int64_t)a.W;
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < nb;
        i += (int64_t)gridDim.x * blockDim.x) {
     const uint64_t m = clr[i % a.W];
-    if (m) a.V[i] &= ~m;
+    if (m) {
+      const uint64_t v = a.V[i] & ~m;
+      a.V[i] = v;
+      a.S[i] = v;
+    }
   }
 }
 
@@ -491,6 +532,7 @@ __global__ void k_ms_session_sources(MsbfsArgs a, const int32_t *lanes, const in
   const int j = (int)(q >> 6);
   const uint64_t bit = 1ull << (q & 63);
   atomicOr((unsigned long long *)&a.V[s * a.W + j], (unsigned long long)bit);
+  atomicOr((unsigned long long *)&a.S[s * a.W + j], (unsigned long long)bit);
   const uint64_t pf = atomicOr((unsigned long long *)&a.F[s * a.W + j], (unsigned long long)bit);
   atomicOr((unsigned long long *)&a.act[s >> 6], 1ull << (s & 63));
   a.levels[s * a.k + q] = 0;
@@ -528,6 +570,7 @@ __global__ void k_ms_sources(MsbfsArgs a, const int32_t *sources) {
   const int j = (int)(q >> 6);
   const uint64_t bit = 1ull << (q & 63);
   atomicOr((unsigned long long *)&a.V[s * a.W + j], (unsigned long long)bit);
+  atomicOr((unsigned long long *)&a.S[s * a.W + j], (unsigned long long)bit);
   const uint64_t pf = atomicOr((unsigned long long *)&a.F[s * a.W + j], (unsigned long long)bit);
   atomicOr((unsigned long long *)&a.act[s >> 6], 1ull << (s & 63));
   a.levels[s * a.k + q] = 0;
@@ -539,18 +582,18 @@ __global__ void k_ms_sources(MsbfsArgs a, const int32_t *sources) {
 
 }  // namespace
 
-void launch_msbfs_start(const MsbfsArgs &a, const int32_t *sources, uint64_t *F1, uint64_t *F2,
-                        uint64_t *act1, uint64_t *act2, void *stream) {
+void launch_msbfs_start(const MsbfsArgs &a, const int32_t *sources, uint64_t *act1, uint64_t *act2,
+                        void *stream) {
   hipStream_t s = (hipStream_t)stream;
-  hipLaunchKernelGGL(k_ms_start, dim3(2048), dim3(256), 0, s, a, sources, F1, F2, act1, act2);
+  hipLaunchKernelGGL(k_ms_start, dim3(2048), dim3(256), 0, s, a, sources, act1, act2);
   const int g = (int)((a.k + 255) / 256);
   hipLaunchKernelGGL(k_ms_sources, dim3(g < 1 ? 1 : g), dim3(256), 0, s, a, sources);
 }
 
-void launch_msbfs_session_init(const MsbfsArgs &a, uint64_t *F1, uint64_t *F2, uint64_t *act1,
-                               uint64_t *act2, unsigned long long *alive3, void *stream) {
-  hipLaunchKernelGGL(k_ms_session_init, dim3(2048), dim3(256), 0, (hipStream_t)stream, a, F1, F2,
-                     act1, act2, alive3);
+void launch_msbfs_session_init(const MsbfsArgs &a, uint64_t *act1, uint64_t *act2,
+                               unsigned long long *alive3, void *stream) {
+  hipLaunchKernelGGL(k_ms_session_init, dim3(2048), dim3(256), 0, (hipStream_t)stream, a, act1,
+                     act2, alive3);
 }
 
 void launch_msbfs_session_join(const MsbfsArgs &a, const int32_t *lanes, const int32_t *sources,
@@ -575,6 +618,9 @@ void launch_msbfs_session_extract(const MsbfsArgs &a, const int32_t *lanes, int3
 void launch_msbfs_level(const MsbfsArgs &a, int grid_x, void *stream) {
   const int tiles = (a.W + a.kt - 1) / a.kt;
   hipLaunchKernelGGL(k_ms_level, dim3(grid_x, tiles), dim3(kBlock), 0, (hipStream_t)stream, a);
+  int64_t g = (a.nw + kWavesPerBlock - 1) / kWavesPerBlock;
+  g = g < 1 ? 1 : (g > 2048 ? 2048 : g);
+  hipLaunchKernelGGL(k_ms_commit, dim3((unsigned)g), dim3(kBlock), 0, (hipStream_t)stream, a);
 }
 
 }  // namespace grb
