@@ -802,7 +802,8 @@ grb_info run_sssp(grb_matrix A, int32_t source, float *dist, const grb_descripto
   launch_sssp_start(sa, source, w.F[1], w.F[2], sw.fd[1], sw.fd[2], stream);
   const int64_t cap = desc.max_iter > 0 ? desc.max_iter : INT64_MAX;
   int64_t d = 0;
-  int chunk = 8;
+  int chunk = 8;  // then 2 and doubling, as for BFS (an empty round costs 8 us with its gap)
+  bool first_batch = true;
   Ctrl hc{};
   for (;;) {
     for (int i = 0; i < chunk && d < cap; ++i, ++d) {
@@ -816,7 +817,8 @@ grb_info run_sssp(grb_matrix A, int32_t source, float *dist, const grb_descripto
     int64_t next = 0;
     for (int t = 0; t < kCntStripes; ++t) next += hc.lists[(d % 3) * kCntSlots + kCntFields * t];
     if (next == 0 || d >= cap) break;
-    chunk = std::min(chunk * 2, 512);
+    chunk = first_batch ? 2 : std::min(chunk * 2, 512);
+    first_batch = false;
   }
   const int iters = hc.nlev;
   std::vector<int64_t> rec((size_t)kStatsCap * kStatFields, 0);
@@ -1522,7 +1524,11 @@ grb_info grb_msbfs(int32_t *levels, grb_matrix A, const int32_t *sources, int32_
   launch_msbfs_start(ma, sources, w.act[1], w.act[2], stream);
   const int64_t cap = desc.max_iter > 0 ? desc.max_iter : INT64_MAX;
   int64_t dlev = 0;
+  // a search deeper than the first batch usually ends a level or two later, and
+  // an empty level still costs its launches (16 us with the gaps), so the second
+  // batch is short and the next ones double
   int chunk = 6;
+  bool first_batch = true;
   std::vector<unsigned long long> hcnt((size_t)6 * kCntStripes);
   Ctrl hc{};
   for (;;) {
@@ -1540,7 +1546,8 @@ grb_info grb_msbfs(int32_t *levels, grb_matrix A, const int32_t *sources, int32_
     unsigned long long next = 0;
     for (int t = 0; t < kCntStripes; ++t) next += hcnt[(size_t)(dlev % 3) * 2 * kCntStripes + 2 * t];
     if (next == 0 || dlev >= cap) break;
-    chunk = std::min(chunk * 2, 256);
+    chunk = first_batch ? 2 : std::min(chunk * 2, 256);
+    first_batch = false;
   }
   const int iters = hc.nlev;
   std::vector<int64_t> rec((size_t)kStatsCap * kStatFields, 0);
