@@ -1884,7 +1884,7 @@ grb_info grb_tricount(int64_t *count, grb_matrix L, const grb_descriptor *d, voi
   hipStream_t s = (hipStream_t)stream;
   const bool profile = (desc.flags & GRB_PROFILE) != 0;
   unsigned long long *cnt = (unsigned long long *)ws;
-  launch_fill_u64((uint64_t *)cnt, 1, 0ull, stream);
+  launch_fill_u64((uint64_t *)cnt, kCountStripes, 0ull, stream);
   MxmArgs ma;
   ma.nrows = L->nrows;
   ma.M = L->a;
@@ -1895,8 +1895,9 @@ grb_info grb_tricount(int64_t *count, grb_matrix L, const grb_descriptor *d, voi
   if (L->nnz > 0) launch_mxm_dot(ma, true, stream);
   if (profile) (void)hipEventRecord(g_events.get(1), s);
   if ((info = check_launch()) != GRB_SUCCESS) return info;
-  unsigned long long h = 0;
-  if (!read_back({{&h, cnt, sizeof(h)}}, s)) return GRB_PANIC;
+  unsigned long long part[kCountStripes], h = 0;
+  if (!read_back({{part, cnt, sizeof(part)}}, s)) return GRB_PANIC;
+  for (int i = 0; i < kCountStripes; ++i) h += part[i];
   *count = (int64_t)h;
   std::vector<int64_t> rec((size_t)kStatsCap * kStatFields, 0);
   rec[0] = L->nnz;

@@ -352,16 +352,24 @@ void launch_pr_iter(int is_fp64, const PrArgs &a, void *stream);  // adaptive if
 
 // masked SpGEMM in the dot-product form, C = (A B^T) .* M (grb_mxm.hip)
 constexpr int kMxmLds = 1024;  // entries of a row of A a wave keeps in LDS
-constexpr size_t kMxmWs = 256; // workspace: the triangle counter
-constexpr int kPairBits = 1 << 16;  // structure-only product: LDS bitmap columns per wave
-constexpr int kPairTail = 256;      // ... and LDS entries of a row's part above them
-constexpr int kPairLong = 128;      // rows of B streamed one at a time from this length
-constexpr int kPairUnroll = 8;      // ... 64 x kPairUnroll entries per step
+constexpr int kCountStripes = 32;
+constexpr size_t kMxmWs = 8 * kCountStripes;  // workspace: the triangle counter's stripes
+constexpr int kPairBits = 1 << 15;  // structure-only product: LDS bitmap columns per wave
+constexpr int kPairTail = 128;      // ... and LDS entries of a row's part above them
+// rows of B cut into units from this length, else streamed together (RMAT-20
+// triangle count 2.00 ms with 16 to 64)
+constexpr int kPairLong = 32;
+// units of 128 entries a batch, two batches in flight (2 and 4: no difference)
+constexpr int kPairUnits = 2;
+constexpr int kPairGridMin = 8192;  // one-wave workgroups: all that fit the chip, to
+constexpr int kPairGridMax = 65536; // eight times as many
+constexpr int kPairGroups = 2;      // workgroups that share a long mask row ...
+constexpr int kPairSplit = 32;      // ... from this many entries
 struct MxmArgs {
   int64_t nrows = 0;  // rows of M (and of A)
   Csr M, A, B;        // B is given by its rows (the columns of B^T)
   void *c = nullptr;  // nnz(M) results in M's entry order (write mode)
-  unsigned long long *count = nullptr;  // count mode: the sum of all results
+  unsigned long long *count = nullptr;  // count mode: kCountStripes parts of the sum
   int vt = 0;         // GRB_FP32 / GRB_FP64 (PLUS_TIMES), else PLUS_PAIR
 };
 void launch_mxm_dot(const MxmArgs &a, bool count, void *stream);
