@@ -793,9 +793,9 @@ grb_info run_sssp(grb_matrix A, int32_t source, float *dist, const grb_descripto
     sa.fd_cur = sw.fd[i];
     sa.fd_nxt = sw.fd[j];
     sa.fd_clr = sw.fd[k];
-    sa.cnt_cur = cnt + i * kCntSlots;
-    sa.cnt_nxt = cnt + j * kCntSlots;
-    sa.cnt_clr = cnt + k * kCntSlots;
+    sa.cnt_cur = cnt + i * kSsspSlots;
+    sa.cnt_nxt = cnt + j * kSsspSlots;
+    sa.cnt_clr = cnt + k * kSsspSlots;
     sa.d = (int32_t)std::min<int64_t>(d, INT32_MAX);
   };
   at_round(0);
@@ -815,7 +815,7 @@ grb_info run_sssp(grb_matrix A, int32_t source, float *dist, const grb_descripto
     if ((info = check_launch()) != GRB_SUCCESS) return info;
     if (!read_back({{&hc, w.ctrl, sizeof(Ctrl)}}, s)) return GRB_PANIC;
     int64_t next = 0;
-    for (int t = 0; t < kCntStripes; ++t) next += hc.lists[(d % 3) * kCntSlots + kCntFields * t];
+    for (int t = 0; t < kCntStripes; ++t) next += hc.lists[(d % 3) * kSsspSlots + kSsspFields * t];
     if (next == 0 || d >= cap) break;
     chunk = first_batch ? 2 : std::min(chunk * 2, 512);
     first_batch = false;

@@ -268,7 +268,13 @@ void launch_bfs_own(const BfsArgs &a, int32_t source, int64_t max_levels, uint64
                     uint64_t wait_ticks, void *stream);
 void launch_bfs_parents(const BfsArgs &a, void *stream);
 
-// SSSP with one kernel per round (grb_sssp.hip); counters as BFS
+// SSSP with one kernel per round (grb_sssp.hip); counters as BFS, and per
+// stripe +inf's bits less those of the frontier's smallest distance
+constexpr int kSsspFields = 4;
+constexpr int kSsspSlots = kSsspFields * kCntStripes;
+// workgroups of a round: what the kernel's registers keep resident, 6 per CU
+// (RMAT-22, all rounds: 1024 1.85 ms, 1536 1.72, 2048 1.87, 4096 1.86)
+constexpr int kSsspGrid = 1536;
 struct SsspArgs {
   int64_t n = 0, nw = 0, nnz = 0;
   Csr push, pull;

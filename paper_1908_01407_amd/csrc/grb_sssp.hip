@@ -5,11 +5,13 @@
 // * push streams the out-edges of the frontier rows and relaxes dist[v]
 //   with an atomicMin on the float's bits (distances are >= 0, so the bit
 //   patterns order like the values);
-// * pull streams the in-edges of every row that has any and takes a
-//   segmented minimum of fd[u] + w(u,v), where fd holds the distances of
-//   the frontier's vertices and +inf elsewhere (one gather per edge, no
-//   bitmap test); the row's wave writes it with a plain store, and pieces
-//   of long rows combine their minima with atomicMin;
+// * pull streams the in-edges of every row that has any and is not settled
+//   (at or below the frontier's smallest distance, which every round finds
+//   for the next) and takes a segmented minimum of fd[u] + w(u,v), where fd
+//   holds the distances of the frontier's vertices and +inf elsewhere; an
+//   edge whose weight already rules it out gathers nothing; the row's wave
+//   writes it with a plain store, and pieces of long rows combine their
+//   minima with atomicMin;
 // * every improved vertex sets its bit in the next frontier and its new
 //   distance in the next fd vector (atomicMin); the first setter counts it
 //   (size and degree sum for the direction choice).  fd vectors rotate with
@@ -42,17 +44,25 @@ __device__ __forceinline__ int decide(const SsspArgs &a, int count, int sumdeg) 
   return pull ? GRB_DIR_PULL : GRB_DIR_PUSH;
 }
 
+// What a thread adds to the next frontier: vertices, their out-edges, their
+// rows longer than kPushSplit, and their smallest distance.
+struct Next {
+  int count = 0, edges = 0, longs = 0;
+  float low = __int_as_float(0x7f800000);
+  __device__ __forceinline__ void add(int deg) {
+    count += 1;
+    edges += deg;
+    longs += deg > kPushSplit ? 1 : 0;
+  }
+};
+
 // Marks v improved for the next round; the first marker counts it.
-__device__ __forceinline__ void mark_improved(const SsspArgs &a, int v, int &fc, int &fd,
-                                              int &fl) {
+__device__ __forceinline__ void mark_improved(const SsspArgs &a, int v, Next &nx) {
   const uint64_t b = 1ull << (v & 63);
   if (a.fnxt[v >> 6] & b) return;
   const uint64_t old = atomicOr((unsigned long long *)&a.fnxt[v >> 6], (unsigned long long)b);
   if (old & b) return;
-  const int pd = a.push.rp[v + 1] - a.push.rp[v];
-  fc += 1;
-  fd += pd;
-  fl += pd > kPushSplit ? 1 : 0;
+  nx.add(a.push.rp[v + 1] - a.push.rp[v]);
 }
 
 // Relaxes dist[c[s]] with nd[s] for s < kUnroll (c < 0: none).  The
@@ -62,8 +72,7 @@ __device__ __forceinline__ void mark_improved(const SsspArgs &a, int v, int &fc,
 // all s are issued before any is counted, so a batch waits a fixed number
 // of times whatever its wins.
 __device__ __forceinline__ void relax_batch(const SsspArgs &a, const int (&c)[kUnroll],
-                                            const float (&nd)[kUnroll], int &fc, int &fd,
-                                            int &fl) {
+                                            const float (&nd)[kUnroll], Next &nx) {
   float cd[kUnroll];
 #pragma unroll
   for (int s = 0; s < kUnroll; ++s) cd[s] = c[s] >= 0 ? a.dist[c[s]] : 0.0f;
@@ -87,6 +96,7 @@ __device__ __forceinline__ void relax_batch(const SsspArgs &a, const int (&c)[kU
     o[s] = ~0ull;
     if (c[s] >= 0 && nd[s] < cd[s] && nd[s] < __int_as_float(old[s])) {
       atomicMin((int *)&a.fd_nxt[c[s]], __float_as_int(nd[s]));
+      nx.low = fminf(nx.low, nd[s]);
       const uint64_t b = 1ull << (c[s] & 63);
       if (!(w[s] & b))
         o[s] = atomicOr((unsigned long long *)&a.fnxt[c[s] >> 6], (unsigned long long)b);
@@ -94,12 +104,7 @@ __device__ __forceinline__ void relax_batch(const SsspArgs &a, const int (&c)[kU
   }
 #pragma unroll
   for (int s = 0; s < kUnroll; ++s) {
-    if (c[s] >= 0 && !(o[s] & (1ull << (c[s] & 63)))) {
-      const int pd = r1[s] - r0[s];
-      fc += 1;
-      fd += pd;
-      fl += pd > kPushSplit ? 1 : 0;
-    }
+    if (c[s] >= 0 && !(o[s] & (1ull << (c[s] & 63)))) nx.add(r1[s] - r0[s]);
   }
 }
 
@@ -132,8 +137,7 @@ __device__ __forceinline__ void clear_behind(const SsspArgs &a, int64_t mw, bool
   }
 }
 
-__device__ void sssp_push(const SsspArgs &a, int *mark, bool long_rows, int &fc, int &fd,
-                          int &fl) {
+__device__ void sssp_push(const SsspArgs &a, int *mark, bool long_rows, Next &nx) {
   const int ln = threadIdx.x & 63;
   const int64_t gw = (int64_t)blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6);
   const int64_t nwaves = (int64_t)gridDim.x * kWavesPerBlock;
@@ -191,7 +195,7 @@ __device__ void sssp_push(const SsspArgs &a, int *mark, bool long_rows, int &fc,
             nd[s] += a.wpush[pos];
           }
         }
-        relax_batch(a, cc, nd, fc, fd, fl);
+        relax_batch(a, cc, nd, nx);
       }
     }
   }
@@ -226,20 +230,23 @@ __device__ void sssp_push(const SsspArgs &a, int *mark, bool long_rows, int &fc,
         cc[s] = pos < pe ? ci[pos] : -1;
         nd[s] = pos < pe ? pdu + a.wpush[pos] : 0.0f;
       }
-      relax_batch(a, cc, nd, fc, fd, fl);
+      relax_batch(a, cc, nd, nx);
     }
   }
 }
 
 // Pull-round candidate distances fd(c) + w(pos) of the stream positions pos
-// (pos < 0: none) with column ids c (+inf off the frontier).  kGatherAll:
-// the weights load with the ids and every id's distance is gathered (the
-// fewest dependent loads: for frontiers that most edges leave).  kProbe:
-// each id's frontier bit is read first (the bitmap is n/8 bytes and stays
-// in cache) and only frontier members gather their distance.  kProbeSparse:
-// as kProbe, and only members load their weight, beside the distance.
+// (pos < 0: none) with column ids c (+inf off the frontier).  An entry counts
+// only if `low` + its weight, `low` the smallest distance on the frontier, is
+// below `lim`, the row's distance so far: sums of floats keep their order, so
+// no other entry can improve the row, and only what counts gathers its
+// distance.  kGatherAll: the weights load with the ids.  kProbe: each id's
+// frontier bit is read first (the bitmap is n/8 bytes and stays in cache) and
+// only frontier members gather their distance.  kProbeSparse: as kProbe, and
+// only members load their weight, beside the distance.
 template <int K>
-__device__ __forceinline__ void pull_terms(const SsspArgs &a, const int (&pos)[K], int mode,
+__device__ __forceinline__ void pull_terms(const SsspArgs &a, const int (&pos)[K],
+                                           const float (&lim)[K], float low, int mode,
                                            float (&t)[K]) {
   const float inf = __int_as_float(0x7f800000);
   int c[K];
@@ -249,6 +256,9 @@ __device__ __forceinline__ void pull_terms(const SsspArgs &a, const int (&pos)[K
     c[s] = pos[s] >= 0 ? a.pull.ci[pos[s]] : -1;
     w[s] = (mode != kProbeSparse && pos[s] >= 0) ? a.wpull[pos[s]] : 0.0f;
   }
+#pragma unroll
+  for (int s = 0; s < K; ++s)
+    if (!(low + w[s] < lim[s])) c[s] = -1;
   if (mode == kGatherAll) {
 #pragma unroll
     for (int s = 0; s < K; ++s) t[s] = (c[s] >= 0 ? a.fd_cur[c[s]] : inf) + w[s];
@@ -268,7 +278,7 @@ __device__ __forceinline__ void pull_terms(const SsspArgs &a, const int (&pos)[K
   for (int s = 0; s < K; ++s) t[s] = d[s] + w[s];
 }
 
-__device__ void sssp_pull(const SsspArgs &a, int *mark, int mode, int &fc, int &fd, int &fl) {
+__device__ void sssp_pull(const SsspArgs &a, int *mark, int mode, float low, Next &nx) {
   const int ln = threadIdx.x & 63;
   const int64_t gw = (int64_t)blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6);
   const int64_t nwaves = (int64_t)gridDim.x * kWavesPerBlock;
@@ -291,10 +301,13 @@ __device__ void sssp_pull(const SsspArgs &a, int *mark, int mode, int &fc, int &
         const int64_t v = w * 64 + ln;
         bool act = (cand >> ln) & 1ull;
         int cur = 0, end = 0;
+        float dv = 0.0f;
         if (act) {
           cur = rp[v];
           end = rp[v + 1];
-          if (end - cur > kPushSplit) act = false;  // long rows: pieces below
+          dv = a.dist[v];  // only this wave writes row v in a pull round
+          // long rows: pieces below; a row at or below the frontier is settled
+          if (end - cur > kPushSplit || !(low < dv)) act = false;
         }
         if (!act) end = cur;
         const int deg0 = end - cur;
@@ -304,10 +317,13 @@ __device__ void sssp_pull(const SsspArgs &a, int *mark, int mode, int &fc, int &
         // candidate is +inf)
         for (bool more = true; more;) {
           int pos[kUnroll], row[kUnroll], se[kUnroll];
+          float lim[kUnroll];
           bool st[kUnroll];
+          const float bound = fminf(dv, best);
   #pragma unroll
           for (int s = 0; s < kUnroll; ++s) {
             pos[s] = -1;
+            lim[s] = 0.0f;
             row[s] = 0;
             se[s] = 0;
             st[s] = false;
@@ -323,6 +339,7 @@ __device__ void sssp_pull(const SsspArgs &a, int *mark, int mode, int &fc, int &
             const bool starts = len > 0 && excl < 64;
             const int r = slot_rows(mark, starts, excl);
             const int rcur = __shfl(cur, r), rexcl = __shfl(excl, r);
+            lim[s] = __shfl(bound, r);
             if (ln < total) pos[s] = rcur + (ln - rexcl);
             row[s] = r;
             st[s] = starts;
@@ -330,7 +347,7 @@ __device__ void sssp_pull(const SsspArgs &a, int *mark, int mode, int &fc, int &
             if (starts) cur += se[s] - excl;
           }
           float tv[kUnroll];
-          pull_terms(a, pos, mode, tv);
+          pull_terms(a, pos, lim, low, mode, tv);
   #pragma unroll
           for (int s = 0; s < kUnroll; ++s) {
             const float y = seg_min_scan(tv[s], row[s]);
@@ -339,95 +356,102 @@ __device__ void sssp_pull(const SsspArgs &a, int *mark, int mode, int &fc, int &
           }
         }
         bool improved = false;
-        if (act && best < a.dist[v]) {  // only this wave writes row v in a pull round
+        if (act && best < dv) {
           a.dist[v] = best;
           a.fd_nxt[v] = best;
           improved = true;
-          const int pd = a.same_csr ? deg0 : a.push.rp[v + 1] - a.push.rp[v];
-          fc += 1;
-          fd += pd;
-          fl += pd > kPushSplit ? 1 : 0;
+          nx.add(a.same_csr ? deg0 : a.push.rp[v + 1] - a.push.rp[v]);
+          nx.low = fminf(nx.low, best);
         }
         const uint64_t ib = __ballot(improved);
         if (ib && ln == 0) atomicOr((unsigned long long *)&a.fnxt[w], (unsigned long long)ib);
       }
     }
   }
-  // pieces of long rows: each piece's minimum is combined with atomicMin;
-  // two active pieces are loaded at once so their latencies overlap
-  for (int64_t hb = gw; hb < a.pull.nsplit; hb += 64 * nwaves) {
-    const int64_t h = hb + (int64_t)ln * nwaves;
+  // pieces of long rows: a wave takes a run of consecutive pieces, and what it
+  // has found of a row bounds the row's later pieces; the run's minimum goes
+  // into the row with atomicMin
+  const int64_t per = (a.pull.nsplit + nwaves - 1) / nwaves;
+  const int64_t hlo = gw * per, hhi = min(hlo + per, a.pull.nsplit);
+  int open = -1;                 // the row the wave is in (wave-uniform, -1: none),
+  float found = inf, had = 0.0f;  // its minimum so far, its distance when read
+  auto close = [&]() {
+    if (open >= 0 && found < had && ln == 0) {
+      const int old = atomicMin((int *)&a.dist[open], __float_as_int(found));
+      if (found < __int_as_float(old)) {
+        atomicMin((int *)&a.fd_nxt[open], __float_as_int(found));
+        nx.low = fminf(nx.low, found);
+        mark_improved(a, open, nx);
+      }
+    }
+  };
+  for (int64_t hb = hlo; hb < hhi; hb += 64) {
+    const int64_t h = hb + ln;
     int r = -1, b = 0, e = 0;
-    if (h < a.pull.nsplit) {
+    float dr = 0.0f;
+    if (h < hhi) {
       r = a.pull.split[2 * h];
       b = a.pull.split[2 * h + 1];
       e = min(b + kPushSplit, rp[r + 1]);
+      dr = a.dist[r];  // a bound: other waves lower it
     }
-    uint64_t act = __ballot(r >= 0);
-    while (act) {
-      int pr[2], pb[2], pe[2];
-#pragma unroll
-      for (int q = 0; q < 2; ++q) {
-        pr[q] = -1;
-        pb[q] = pe[q] = 0;
-        if (act) {
-          const int k = __ffsll((unsigned long long)act) - 1;
-          act &= act - 1;
-          pr[q] = __shfl(r, k);
-          pb[q] = __shfl(b, k);
-          pe[q] = __shfl(e, k);
-        }
+    // rows at or below the frontier are settled
+    for (uint64_t act = __ballot(r >= 0 && low < dr); act; act &= act - 1) {
+      const int k = __ffsll((unsigned long long)act) - 1;
+      const int pr = __shfl(r, k), pb = __shfl(b, k), pe = __shfl(e, k);
+      const float pd = __shfl(dr, k);
+      if (pr != open) {
+        close();
+        open = pr;
+        found = inf;
+        had = pd;
       }
-      int pos[2][kUnroll];
+      const float bound = fminf(pd, found);
+      int pos[kUnroll];
+      float lim[kUnroll], tv[kUnroll];
 #pragma unroll
-      for (int q = 0; q < 2; ++q)
-#pragma unroll
-        for (int s = 0; s < kUnroll; ++s) {
-          const int ps = pb[q] + s * 64 + ln;
-          pos[q][s] = ps < pe[q] ? ps : -1;
-        }
-      float tv[2][kUnroll];
-#pragma unroll
-      for (int q = 0; q < 2; ++q) pull_terms(a, pos[q], mode, tv[q]);
-      float best[2];
-#pragma unroll
-      for (int q = 0; q < 2; ++q) {
-        best[q] = inf;
-#pragma unroll
-        for (int s = 0; s < kUnroll; ++s) best[q] = fminf(best[q], tv[q][s]);
+      for (int s = 0; s < kUnroll; ++s) {
+        const int ps = pb + s * 64 + ln;
+        pos[s] = ps < pe ? ps : -1;
+        lim[s] = bound;
       }
-      best[0] = wave_min(best[0]);
-      best[1] = wave_min(best[1]);
-      // lane q relaxes piece q's row
-      const int myr = ln == 0 ? pr[0] : (ln == 1 ? pr[1] : -1);
-      const float myb = ln == 0 ? best[0] : best[1];
-      if (myr >= 0 && myb < inf) {
-        const int old = atomicMin((int *)&a.dist[myr], __float_as_int(myb));
-        if (myb < __int_as_float(old)) {
-          atomicMin((int *)&a.fd_nxt[myr], __float_as_int(myb));
-          mark_improved(a, myr, fc, fd, fl);
-        }
-      }
+      pull_terms(a, pos, lim, low, mode, tv);
+      float best = inf;
+#pragma unroll
+      for (int s = 0; s < kUnroll; ++s) best = fminf(best, tv[s]);
+      found = fminf(found, wave_min(best));
     }
   }
+  close();
 }
 
-__global__ __launch_bounds__(kBlock) void k_sssp_round(SsspArgs a) {
+// Bound by the gathers of the pull rounds (5 ps an edge for a bare gather of
+// RMAT-22's columns), which is why an edge is first held against its row's
+// distance.  RMAT-22 (128M edges, weights 1 to 64), the five pull rounds of a
+// search: 922 + 888 + 877 + 689 + 52 us; with the test, rows at or below the
+// frontier left out and 1536 workgroups 800 + 338 + 173 + 126 + 41; with the
+// pieces of a row in one wave 580 + 339 + 193 + 125 + 41.  Loading the column
+// ids only of the edges that pass: 835 + 412 + 219 + 155 at 1024 workgroups,
+// where loading them with the weights took 815 + 387 + 212 + 154.
+__global__ __launch_bounds__(kBlock, 6) void k_sssp_round(SsspArgs a) {
   __shared__ int s_mark[kWavesPerBlock][64];
   __shared__ int s_count, s_sumdeg, s_long;
-  __shared__ int s_red[kWavesPerBlock][kCntFields];
+  __shared__ float s_low;
+  __shared__ int s_red[kWavesPerBlock][kSsspFields];
   if (threadIdx.x == 0) {
-    int c = 0, sd = 0, lr = 0;
+    int c = 0, sd = 0, lr = 0, lo = 0;
     for (int t = 0; t < kCntStripes; ++t) {
-      c += a.cnt_cur[kCntFields * t];
-      sd += a.cnt_cur[kCntFields * t + 1];
-      lr += a.cnt_cur[kCntFields * t + 2];
+      c += a.cnt_cur[kSsspFields * t];
+      sd += a.cnt_cur[kSsspFields * t + 1];
+      lr += a.cnt_cur[kSsspFields * t + 2];
+      lo = max(lo, a.cnt_cur[kSsspFields * t + 3]);
     }
+    s_low = __int_as_float(0x7f800000 - lo);
     s_count = c;
     s_sumdeg = sd;
     s_long = lr;
     if (blockIdx.x == 0) {
-      for (int i = 0; i < kCntSlots; ++i) a.cnt_clr[i] = 0;
+      for (int i = 0; i < kSsspSlots; ++i) a.cnt_clr[i] = 0;
       if (c > 0) {
         a.ctrl->nlev = a.d + 1;
         if (a.stats && a.d < kStatsCap) {
@@ -441,35 +465,40 @@ __global__ __launch_bounds__(kBlock) void k_sssp_round(SsspArgs a) {
   __syncthreads();
   if (s_count == 0) return;
   const int dir = decide(a, s_count, s_sumdeg);
-  int fc = 0, fd = 0, fl = 0;
-  if (dir == GRB_DIR_PUSH) sssp_push(a, s_mark[threadIdx.x >> 6], s_long > 0, fc, fd, fl);
+  Next nx;
+  if (dir == GRB_DIR_PUSH) sssp_push(a, s_mark[threadIdx.x >> 6], s_long > 0, nx);
   else {
     const int64_t e = s_sumdeg;  // edges that leave the frontier
     const int mode = e * kSparseDen < a.nnz ? kProbeSparse
                      : e * kProbeDen < a.nnz ? kProbe : kGatherAll;
-    sssp_pull(a, s_mark[threadIdx.x >> 6], mode, fc, fd, fl);
+    sssp_pull(a, s_mark[threadIdx.x >> 6], mode, s_low, nx);
   }
-  fc = wave_sum(fc);
-  fd = wave_sum(fd);
-  fl = wave_sum(fl);
+  nx.count = wave_sum(nx.count);
+  nx.edges = wave_sum(nx.edges);
+  nx.longs = wave_sum(nx.longs);
+  nx.low = wave_min(nx.low);
   if ((threadIdx.x & 63) == 0) {
-    s_red[threadIdx.x >> 6][0] = fc;
-    s_red[threadIdx.x >> 6][1] = fd;
-    s_red[threadIdx.x >> 6][2] = fl;
+    s_red[threadIdx.x >> 6][0] = nx.count;
+    s_red[threadIdx.x >> 6][1] = nx.edges;
+    s_red[threadIdx.x >> 6][2] = nx.longs;
+    s_red[threadIdx.x >> 6][3] = 0x7f800000 - __float_as_int(nx.low);
   }
   __syncthreads();
   if (threadIdx.x == 0) {
-    int c = 0, sd = 0, lr = 0;
+    int c = 0, sd = 0, lr = 0, lo = 0;
     for (int i = 0; i < kWavesPerBlock; ++i) {
       c += s_red[i][0];
       sd += s_red[i][1];
       lr += s_red[i][2];
+      lo = max(lo, s_red[i][3]);
     }
+    const int t = blockIdx.x % kCntStripes;
+    // a block may improve vertices that another one counts
+    if (lo) atomicMax(&a.cnt_nxt[kSsspFields * t + 3], lo);
     if (c) {
-      const int t = blockIdx.x % kCntStripes;
-      atomicAdd(&a.cnt_nxt[kCntFields * t], c);
-      atomicAdd(&a.cnt_nxt[kCntFields * t + 1], sd);
-      if (lr) atomicAdd(&a.cnt_nxt[kCntFields * t + 2], lr);
+      atomicAdd(&a.cnt_nxt[kSsspFields * t], c);
+      atomicAdd(&a.cnt_nxt[kSsspFields * t + 1], sd);
+      if (lr) atomicAdd(&a.cnt_nxt[kSsspFields * t + 2], lr);
     }
   }
 }
@@ -499,7 +528,7 @@ __global__ __launch_bounds__(kBlock) void k_sssp_start(SsspArgs a, int32_t sourc
     }
   }
   if (blockIdx.x == 0 && threadIdx.x == 0) {
-    for (int i = 0; i < kCntSlots; ++i) {
+    for (int i = 0; i < kSsspSlots; ++i) {
       a.cnt_cur[i] = 0;
       a.cnt_nxt[i] = 0;
       a.cnt_clr[i] = 0;
@@ -509,6 +538,7 @@ __global__ __launch_bounds__(kBlock) void k_sssp_start(SsspArgs a, int32_t sourc
     a.cnt_cur[0] = 1;
     a.cnt_cur[1] = ds;
     a.cnt_cur[2] = ds > kPushSplit ? 1 : 0;
+    a.cnt_cur[3] = 0x7f800000;  // the source's distance is 0
   }
 }
 
@@ -523,7 +553,7 @@ void launch_sssp_start(const SsspArgs &a, int32_t source, uint64_t *f1, uint64_t
 }
 
 void launch_sssp_round(const SsspArgs &a, void *stream) {
-  hipLaunchKernelGGL(k_sssp_round, dim3(kExpandGrid), dim3(kBlock), 0, (hipStream_t)stream, a);
+  hipLaunchKernelGGL(k_sssp_round, dim3(kSsspGrid), dim3(kBlock), 0, (hipStream_t)stream, a);
 }
 
 }  // namespace grb
