@@ -251,7 +251,7 @@ PrWs pr_layout(void *ws, int64_t n, const Csr &pull, int esize) {
 struct MxvWs {
   Ctrl *ctrl;
   int64_t *part, *blk_part;
-  uint64_t *status, *status_out, *status_list, *t_bm, *t_vb;
+  uint64_t *status, *status_out, *status_list, *t_bm;
   int32_t *list, *degpre, *rowstart, *tiles;
   int64_t tiles_cap;
   void *t_val, *hp_val;
@@ -279,8 +279,9 @@ MxvWs mxv_layout(void *ws, int64_t n_in, int64_t n_out, int64_t nnz, int64_t npi
   t.tiles_cap = (n_in + nnz) / kPushTile + 3;
   t.tiles = c.take<int32_t>((size_t)t.tiles_cap);
   t.t_bm = c.take<uint64_t>((size_t)std::max<int64_t>(words_of(n_out), 1));
-  t.t_vb = c.take<uint64_t>((size_t)std::max<int64_t>(words_of(n_out), 1));
-  t.t_val = c.take<char>((size_t)std::max<int64_t>(n_out, 1) * 8);
+  // values, or the OR push's kOrCopies pairs of bitmaps
+  t.t_val = c.take<char>(std::max((size_t)std::max<int64_t>(n_out, 1) * 8,
+                                  (size_t)(2 * kOrCopies * words_of(n_out)) * 8));
   t.hp_val = c.take<char>((size_t)std::max<int64_t>(npieces, 1) * 8);
   t.hp_has = c.take<uint8_t>((size_t)std::max<int64_t>(npieces, 1));
   t.settled = c.take<uint8_t>((size_t)std::max<int64_t>(n_out, 1));
@@ -2018,7 +2019,6 @@ grb_info run_product(bool is_vxm, grb_vector w, grb_vector mask, grb_binop accum
   }
   a.t_val = t.t_val;
   a.t_bm = t.t_bm;
-  a.t_vb = t.t_vb;
   a.hp_val = t.hp_val;
   a.hp_has = t.hp_has;
   a.settled = t.settled;

@@ -305,13 +305,17 @@ __device__ __forceinline__ double atomic_min_f64(double *a, double v) {
 // the word an earlier kernel of the product left; forced directions and
 // single-orientation matrices need neither.  All 64 lanes must be active;
 // every lane gets the same answer.
-__device__ __forceinline__ int gate_dir(const DirGate &g) {
+// `full` (optional): whether the counted input holds every index (false where
+// nothing was counted).
+__device__ __forceinline__ int gate_dir(const DirGate &g, bool *full = nullptr) {
+  if (full) *full = false;
   if (g.forced) return g.forced;
   if (!g.can_pull) return GRB_DIR_PUSH;
   if (!g.can_push) return GRB_DIR_PULL;
   if (g.decided) {  // left by an earlier kernel of the product
     const int dd = *g.decided;
-    if (dd) return dd;
+    if (full) *full = (dd & kGateFull) != 0;
+    if (dd) return dd & ~kGateFull;
   }
   const int ln = threadIdx.x & 63;
   int64_t c = 0, d = 0;
@@ -327,7 +331,8 @@ __device__ __forceinline__ int gate_dir(const DirGate &g) {
   const int dir = pull ? GRB_DIR_PULL : GRB_DIR_PUSH;
   // every evaluating wave stores the same value; a kernel launched later in
   // the product reads it
-  if (g.decided && ln == 0) *g.decided = dir;
+  if (g.decided && ln == 0) *g.decided = dir | (c == g.n_in ? kGateFull : 0);
+  if (full) *full = c == g.n_in;
   return dir;
 }
 

@@ -138,6 +138,8 @@ class NoAllocScope {
 // partials (kMxvParts (count, degree sum) pairs); every later kernel of the
 // product evaluates the rule itself, so no kernel waits on the host.
 constexpr int kMxvParts = 256;     // workgroups of the generic product's first kernel
+constexpr int kOrCopies = 8;         // OR push: copies of its temporary bitmaps
+constexpr int kMxvMergeGrid = 4096;  // ... of its last one, at most
 constexpr int kMxvPartThreads = 1024;
 constexpr int kMxvListChunk = 4096;  // list entries per workgroup of the list preparation
 struct DirGate {
@@ -151,6 +153,8 @@ struct DirGate {
   int rule = 0, denom = 10;
   int64_t nnz = 0, n_in = 0;
 };
+
+constexpr int kGateFull = 4;  // beside the direction in *decided: every index is present
 
 // ---- kernel launch interfaces (implemented in grb_kernels.hip) -------------
 struct CompactArgs {
@@ -469,7 +473,7 @@ struct MxvArgs {
   const int32_t *w_list_in = nullptr, *w_cnt_in = nullptr;  // output given only as a list
   // workspace
   void *t_val = nullptr;
-  uint64_t *t_bm = nullptr, *t_vb = nullptr;
+  uint64_t *t_bm = nullptr;     // presence in t_val (OR: its bitmaps lie in t_val)
   void *hp_val = nullptr;       // per pull piece partial value
   uint8_t *hp_has = nullptr;    // per pull piece: any contribution
   uint8_t *settled = nullptr;   // OR pull: long row settled by its first two entries (by row)

@@ -62,20 +62,31 @@ __global__ __launch_bounds__(kCompactThreads) void k_compact(CompactArgs a) {
   const int64_t nbits = a.nbits > 0 ? a.nbits : a.nw * 64;
   const int64_t wlast = (nbits - 1) >> 6;
   const uint64_t mlast = mask_below((int)(nbits - wlast * 64));
+  // the wave's words, then its entries' row extents, are loaded all at once
+  // and kept: a load inside each word's branch is waited for word by word
+  // (RMAT-22, 1 % of the indices: 20.1 us then, 15.6 so)
+  uint64_t words[WPW];
+  int rows[WPW], degs[WPW];
 #pragma unroll
   for (int k = 0; k < WPW; ++k) {
     const int64_t w = w0 + k;
-    const uint64_t word = w < a.nw ? (a.nb[w] & (w == wlast ? mlast : ~0ull)) : 0ull;
-    int deg = 0;
-    if ((word >> ln) & 1ull) {
-      const int64_t v = w * 64 + ln;
-      if (a.rp) deg = a.rp[v + 1] - a.rp[v];
-    }
-    const int ds = word ? wave_sum(deg) : 0;  // the word is the same in every lane
+    words[k] = w < a.nw ? (a.nb[w] & (w == wlast ? mlast : ~0ull)) : 0ull;
+  }
+#pragma unroll
+  for (int k = 0; k < WPW; ++k) {
+    const bool bit = a.rp && ((words[k] >> ln) & 1ull);
+    const int64_t v = bit ? (w0 + k) * 64 + ln : 0;
+    rows[k] = bit ? a.rp[v] : 0;
+    degs[k] = bit ? a.rp[v + 1] : 0;
+  }
+#pragma unroll
+  for (int k = 0; k < WPW; ++k) {
+    degs[k] -= rows[k];
+    const int ds = words[k] ? wave_sum(degs[k]) : 0;  // the word is the same in every lane
     if (ln == 0) {
-      s_cnt[wid * WPW + k] = __popcll(word);
+      s_cnt[wid * WPW + k] = __popcll(words[k]);
       s_deg[wid * WPW + k] = ds;
-      if (a.clear && w < a.nw) a.clear[w] = 0ull;
+      if (a.clear && w0 + k < a.nw) a.clear[w0 + k] = 0ull;
     }
   }
   __syncthreads();
@@ -154,17 +165,12 @@ __global__ __launch_bounds__(kCompactThreads) void k_compact(CompactArgs a) {
   const int bc = s_base_c, bd = s_base_d;
 #pragma unroll
   for (int k = 0; k < WPW; ++k) {
-    const int64_t w = w0 + k;
-    const uint64_t word = w < a.nw ? (a.nb[w] & (w == wlast ? mlast : ~0ull)) : 0ull;
+    const uint64_t word = words[k];
     if (word == 0ull) continue;
     const bool bit = (word >> ln) & 1ull;
     const int rank = __popcll(word & mask_below(ln));
-    const int64_t v = w * 64 + ln;
-    int deg = 0, rs = 0;
-    if (bit && a.rp) {  // second read of the same row extents: a cache hit
-      rs = a.rp[v];
-      deg = a.rp[v + 1] - rs;
-    }
+    const int64_t v = (w0 + k) * 64 + ln;
+    const int deg = degs[k], rs = rows[k];
     const int dinc = wave_incl_scan(deg);
     const int idx = bc + s_cnt[wid * WPW + k] + rank;
     const int dex = bd + s_deg[wid * WPW + k] + dinc - deg;

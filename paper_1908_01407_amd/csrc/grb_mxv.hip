@@ -1,11 +1,13 @@
 // Generic masked semiring products w<mask> = accum(w, A' u) (Section 3.3 of
 // the paper; operand decomposition per its mxv figure), over the closed set
 // of semirings of grb.h, in either direction:
-// * the first kernel clears the control block and, for the automatic
-//   choice, leaves per-workgroup partials of the input's entry count and
-//   degree sum; every later kernel evaluates the switch rule (Section 4.3.1,
-//   Table 5) from them and returns at once when its direction is not taken,
-//   so the input is compacted only when the product really pushes;
+// * the first kernel clears the control block and the push's temporary and,
+//   for the automatic choice, leaves per-workgroup partials of the input's
+//   entry count and degree sum; every later kernel evaluates the switch rule
+//   (Section 4.3.1, Table 5) from them.  The product itself and what follows it
+//   are one kernel each for both directions (a kernel that only finds its
+//   direction not taken costs 4.5 us); the input is compacted only when the
+//   product really pushes;
 // * push (SpMSpV): the input as a sorted list with degree prefix (the
 //   compaction kernel for a bitmap input; a list input is used as it is, its
 //   prefix built by a look-back scan over the list); merge-path tiles over
@@ -20,7 +22,9 @@
 //   and stops a row at its first true product, the other semirings find each
 //   position's row by bisection so that several steps' loads are in flight,
 //   and reduce each row's segments in a fixed order (floating-point results
-//   repeat bit for bit).  Rows longer than kPushSplit are cut into pieces
+//   repeat bit for bit); an input counted full is not tested for presence (a
+//   gather per entry: PLUS_TIMES fp32 over 1,000,003 shuffled R-MAT rows, 30M
+//   entries, 260 -> 194 us).  Rows longer than kPushSplit are cut into pieces
 //   that any wave takes; a fix-up kernel (a wave per long row) combines a
 //   row's pieces in a fixed order and applies the epilogue.
 #include <hip/hip_runtime.h>
@@ -173,13 +177,18 @@ __global__ __launch_bounds__(kMxvPartThreads) void k_mxv_init(MxvArgs a) {
   for (int64_t i = gt; i < 2 * (int64_t)a.nblk; i += nthr) a.status[i] = 0ull;
   for (int64_t i = gt; i < 2 * (int64_t)a.nblk_out; i += nthr) a.status_out[i] = 0ull;
   for (int64_t i = gt; i < (int64_t)a.nblk_list; i += nthr) a.status_list[i] = 0ull;
-  // the OR push's temporary bitmaps (other semirings clear theirs only
-  // when they push: their value array is n elements)
-  if (Sr<SR>::lor && a.gate.can_push && a.gate.forced != GRB_DIR_PULL)
-    for (int64_t i = gt; i < a.nw_out; i += nthr) {
-      a.t_bm[i] = 0ull;
-      a.t_vb[i] = 0ull;
+  // the push's temporary product: clearing it here whatever the direction
+  // (2 us at a million fp32 outputs) costs less than a kernel of its own that
+  // only a push would need
+  if (a.gate.can_push && a.gate.forced != GRB_DIR_PULL) {
+    if constexpr (Sr<SR>::lor) {
+      for (int64_t i = gt; i < kOrCopies * 2 * a.nw_out; i += nthr) ((uint64_t *)a.t_val)[i] = 0ull;
+    } else {
+      for (int64_t i = gt; i < a.nw_out; i += nthr) a.t_bm[i] = 0ull;
+      for (int64_t i = gt; i < a.n_out; i += nthr)
+        ((typename Sr<SR>::T *)a.t_val)[i] = Sr<SR>::identity();
     }
+  }
   // OR pull: long rows' "settled by the probes" flags
   if (Sr<SR>::lor && a.gate.can_pull && a.gate.forced != GRB_DIR_PUSH)
     for (int64_t k = gt; k < a.pull.nsplit_rows; k += nthr) a.settled[a.pull.split_rows[3 * k]] = 0;
@@ -198,15 +207,19 @@ __global__ __launch_bounds__(kMxvPartThreads) void k_mxv_init(MxvArgs a) {
     int64_t tc = 0, td = 0;  // this workgroup's totals (thread 0)
     for (int64_t b = blockIdx.x; b < a.nblk; b += gridDim.x) {
       int wc = 0, wdg = 0;
-#pragma unroll 4
+      uint64_t words[WPW];
+#pragma unroll
       for (int k = 0; k < WPW; ++k) {
         const int64_t w = b * kCompactWords + wv * WPW + k;
-        const uint64_t word = w < a.nw_in ? (a.u_bm[w] & (w == wlast ? mlast : ~0ull)) : 0ull;
-        if ((word >> ln) & 1ull) {
-          const int64_t v = w * 64 + ln;
-          wc += 1;
-          wdg += rp[v + 1] - rp[v];
-        }
+        words[k] = w < a.nw_in ? (a.u_bm[w] & (w == wlast ? mlast : ~0ull)) : 0ull;
+      }
+#pragma unroll
+      for (int k = 0; k < WPW; ++k) {
+        const bool bit = (words[k] >> ln) & 1ull;
+        const int64_t v = bit ? (b * kCompactWords + wv * WPW + k) * 64 + ln : 0;
+        const int r0 = bit ? rp[v] : 0, r1 = bit ? rp[v + 1] : 0;
+        wc += bit ? 1 : 0;
+        wdg += r1 - r0;
       }
       if (__ballot(wc != 0)) {
         wc = wave_sum(wc);
@@ -250,7 +263,9 @@ __global__ __launch_bounds__(kMxvPartThreads) void k_mxv_init(MxvArgs a) {
         if (v >= 0 && v < a.n_in) d += rp[v + 1] - rp[v];
       }
   } else if (!exact) {
-    for (int64_t w = gt; w < a.nw_in; w += nthr) c += __popcll(a.u_bm[w]);
+    const int64_t wlast = (a.n_in - 1) >> 6;
+    for (int64_t w = gt; w < a.nw_in; w += nthr)
+      c += __popcll(a.u_bm[w] & (w == wlast ? mask_below((int)(a.n_in - wlast * 64)) : ~0ull));
   } else {
     // a wave per word (lane = row), four words in flight
     const int64_t gwv = gt >> 6, nwv = nthr >> 6;
@@ -396,90 +411,116 @@ __global__ __launch_bounds__(kCompactThreads) void k_mxv_list_prep(MxvArgs a) {
   }
 }
 
-template <int SR>
-__global__ __launch_bounds__(kBlock) void k_mxv_prep(MxvArgs a) {
-  using T = typename Sr<SR>::T;
-  if (mxv_dir(a) != GRB_DIR_PUSH) return;
-  const int ln = threadIdx.x & 63;
-  const int64_t gw = (int64_t)blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6);
-  const int64_t nwaves = (int64_t)gridDim.x * kWavesPerBlock;
-  for (int64_t w = gw; w < a.nw_out; w += nwaves) {
-    if (ln == 0) {
-      a.t_bm[w] = 0ull;
-      a.t_vb[w] = 0ull;
-    }
-    const int64_t i = w * 64 + ln;
-    if (i < a.n_out) ((T *)a.t_val)[i] = Sr<SR>::identity();
+// The OR push's temporary: kOrCopies pairs of bitmaps (false products, then
+// true ones) in the place of the value array, which OR does not use.  An
+// atomic is done at the memory side, those on one word one after the other,
+// and hubs make a few words hot: with one pair the tiles below spent 12 us of
+// their 68 on everything else (RMAT-22, 1 % of the indices, 1.3M entries, half
+// the outputs masked: 230,000 atomics).  Eight workgroups in turn share a copy:
+// 4 copies 47 us, 8 40, 16 37 (and 5 us more for clearing and reading them);
+// a copy per XCD 58, the bitmaps' words spread over the lines 82, the tile's
+// words gathered in LDS first 70.
+__device__ __forceinline__ uint64_t *or_copy(const MxvArgs &a, int c) {
+  return (uint64_t *)a.t_val + c * 2 * a.nw_out;
+}
+__device__ __forceinline__ void or_word(const MxvArgs &a, int64_t wd, uint64_t &th, uint64_t &tv) {
+  th = tv = 0ull;
+#pragma unroll
+  for (int c = 0; c < kOrCopies; ++c) {
+    th |= or_copy(a, c)[wd];
+    tv |= or_copy(a, c)[a.nw_out + wd];
   }
+  th |= tv;
 }
 
+// One merge-path tile a workgroup at a time, kPushTile / kBlock edges a thread:
+// its row searches, then its column ids, mask words and target words go in one
+// after the other for all of them, so a tile waits for each once (all but the
+// atomics, above: 12 us).
+template <class T>
+struct PushTile {
+  int deg[kPushTile + 1], rs[kPushTile + 1];
+  T val[kPushTile + 1];
+};
+
 template <int SR>
-__global__ __launch_bounds__(kBlock) void k_mxv_push(MxvArgs a) {
+__device__ __forceinline__ void mxv_push(const MxvArgs &a, PushTile<typename Sr<SR>::T> &tile) {
   using T = typename Sr<SR>::T;
-  __shared__ int s_deg[kPushTile + 1], s_rs[kPushTile + 1];
-  __shared__ T s_val[kPushTile + 1];
-  if (mxv_dir(a) != GRB_DIR_PUSH) return;
+  constexpr int K = kPushTile / kBlock;
   const int ntiles = a.ctrl->ntiles, sumdeg = a.ctrl->sumdeg;
   for (int t = blockIdx.x; t < ntiles; t += gridDim.x) {
     const int i0 = a.tiles[t], i1 = a.tiles[t + 1];
     const int ne = i1 - i0 + 1;
     for (int k = threadIdx.x; k < ne; k += kBlock) {
       const int j = a.list[i0 + k];
-      s_deg[k] = a.degpre[i0 + k];
-      s_rs[k] = a.rowstart[i0 + k];
-      s_val[k] = (j >= 0 && j < a.n_in) ? u_at<T>(a, j) : (T)0;
+      tile.deg[k] = a.degpre[i0 + k];
+      tile.rs[k] = a.rowstart[i0 + k];
+      tile.val[k] = (j >= 0 && j < a.n_in) ? u_at<T>(a, j) : (T)0;
     }
     __syncthreads();
     const int64_t e0 = (int64_t)t * kPushTile - i0;
     int64_t e1 = (int64_t)(t + 1) * kPushTile - i1;
     if (e1 > sumdeg) e1 = sumdeg;
+    int i[K];
+    int64_t pos[K];
+    T u[K];
+#pragma unroll
+    for (int q = 0; q < K; ++q) {
+      const int64_t e = e0 + q * kBlock + threadIdx.x;
+      int lo = 0, hi = ne - 1;
+      while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (tile.deg[mid] <= e) lo = mid; else hi = mid - 1;
+      }
+      pos[q] = e < e1 ? tile.rs[lo] + (e - tile.deg[lo]) : -1;
+      u[q] = tile.val[lo];
+    }
+#pragma unroll
+    for (int q = 0; q < K; ++q) i[q] = pos[q] >= 0 ? a.push.ci[pos[q]] : -1;
+#pragma unroll
+    for (int q = 0; q < K; ++q)
+      if (i[q] >= 0 && !mask_allowed(a, i[q])) i[q] = -1;
     if constexpr (Sr<SR>::lor) {
       // One OR per run of lanes whose edges hit the same word of the same
-      // bitmap (t_vb: a true product, t_bm: a false one; the merge reads
-      // presence as either): a long row's sorted targets share words.  The
-      // loop is wave-uniform so that the whole wave combines its runs.
-      const int ln = threadIdx.x & 63;
-      for (int64_t eb = e0 + (threadIdx.x & ~63); eb < e1; eb += kBlock) {
-        const int64_t e = eb + ln;
-        int lo = 0, hi = ne - 1;
-        while (lo < hi) {
-          const int mid = (lo + hi + 1) >> 1;
-          if (s_deg[mid] <= e) lo = mid; else hi = mid - 1;
-        }
-        int i = -1;
-        int64_t pos = 0;
-        if (e < e1) {
-          pos = s_rs[lo] + (e - s_deg[lo]);
-          i = a.push.ci[pos];
-          if (!mask_allowed(a, i)) i = -1;
-        }
-        const bool tru = i >= 0 && s_val[lo] != 0 && mat_true(a.push, pos);
-        const int64_t key = i >= 0 ? (((int64_t)(i >> 6) << 1) | (tru ? 1 : 0)) : -1;
+      // bitmap (a true product, or a false one; the merge reads presence as
+      // either): a long row's sorted targets share words.  The whole wave
+      // combines its runs.
+      uint64_t run[K], w[K];
+      bool tru[K];
+#pragma unroll
+      for (int q = 0; q < K; ++q) {
+        tru[q] = i[q] >= 0 && u[q] != 0 && mat_true(a.push, pos[q]);
+        const int64_t key = i[q] >= 0 ? (((int64_t)(i[q] >> 6) << 1) | (tru[q] ? 1 : 0)) : -1;
         int tail;
-        const uint64_t run = run_tail_or(key, i >= 0 ? 1ull << (i & 63) : 0ull, tail);
-        if (key >= 0 && run) {
-          const int64_t wd = key >> 1;
-          if (key & 1) {
-            if (~a.t_vb[wd] & run) atomicOr((unsigned long long *)&a.t_vb[wd], run);
-          } else {
-            if (~a.t_bm[wd] & run) atomicOr((unsigned long long *)&a.t_bm[wd], run);
-          }
-        }
+        run[q] = run_tail_or(key, i[q] >= 0 ? 1ull << (i[q] & 63) : 0ull, tail);
+        if (i[q] < 0) run[q] = 0ull;
       }
+      uint64_t *copy = or_copy(a, (blockIdx.x / 8) % kOrCopies);
+      int64_t at[K];
+#pragma unroll
+      for (int q = 0; q < K; ++q) {
+        at[q] = (i[q] >> 6) + (tru[q] ? a.nw_out : 0);
+        w[q] = run[q] ? copy[at[q]] : 0ull;
+      }
+#pragma unroll
+      for (int q = 0; q < K; ++q)
+        if (run[q] & ~w[q])
+          atomicOr((unsigned long long *)&copy[at[q]], (unsigned long long)run[q]);
     } else {
-      for (int64_t e = e0 + threadIdx.x; e < e1; e += kBlock) {
-        int lo = 0, hi = ne - 1;
-        while (lo < hi) {
-          const int mid = (lo + hi + 1) >> 1;
-          if (s_deg[mid] <= e) lo = mid; else hi = mid - 1;
-        }
-        const int64_t pos = s_rs[lo] + (e - s_deg[lo]);
-        const int i = a.push.ci[pos];
-        if (!mask_allowed(a, i)) continue;
-        const uint64_t b = 1ull << (i & 63);
-        const T prod = Sr<SR>::mul(mat_value<T>(a.push, pos), s_val[lo], a.pick_vec);
-        atomic_add_sr<SR>(&((T *)a.t_val)[i], prod);
-        if (!(a.t_bm[i >> 6] & b)) atomicOr((unsigned long long *)&a.t_bm[i >> 6], b);
+      T prod[K];
+      uint64_t w[K];
+#pragma unroll
+      for (int q = 0; q < K; ++q) {
+        prod[q] = i[q] >= 0 ? Sr<SR>::mul(mat_value<T>(a.push, pos[q]), u[q], a.pick_vec)
+                            : Sr<SR>::identity();
+        w[q] = i[q] >= 0 ? a.t_bm[i[q] >> 6] : 0ull;
+      }
+#pragma unroll
+      for (int q = 0; q < K; ++q) {
+        if (i[q] < 0) continue;
+        const unsigned long long b = 1ull << (i[q] & 63);
+        atomic_add_sr<SR>(&((T *)a.t_val)[i[q]], prod[q]);
+        if (!(w[q] & b)) atomicOr((unsigned long long *)&a.t_bm[i[q] >> 6], b);
       }
     }
     __syncthreads();
@@ -487,9 +528,8 @@ __global__ __launch_bounds__(kBlock) void k_mxv_push(MxvArgs a) {
 }
 
 template <int SR>
-__global__ __launch_bounds__(kBlock) void k_mxv_merge(MxvArgs a) {
+__device__ __forceinline__ void mxv_merge(const MxvArgs &a) {
   using T = typename Sr<SR>::T;
-  if (mxv_dir(a) != GRB_DIR_PUSH) return;
   const int ln = threadIdx.x & 63;
   const int64_t gw = (int64_t)blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6);
   const int64_t nwaves = (int64_t)gridDim.x * kWavesPerBlock;
@@ -509,8 +549,8 @@ __global__ __launch_bounds__(kBlock) void k_mxv_merge(MxvArgs a) {
         if (wd < a.nw_out) {
           const uint64_t valid = wd == wlast ? mlast : ~0ull;
           const uint64_t A = allowed_word(a, wd), W = a.w_bm[wd];
-          tvb = a.t_vb[wd];
-          const uint64_t th = a.t_bm[wd] | tvb;
+          uint64_t th;
+          or_word(a, wd, th, tvb);
           const uint64_t keep = a.replace ? 0ull : (~A & W);
           plain = A & (acc ? ~W : ~0ull);          // w = t where t is present
           const uint64_t accw = acc ? (A & W) : 0ull;  // w = w (+) t, present either way
@@ -533,15 +573,14 @@ __global__ __launch_bounds__(kBlock) void k_mxv_merge(MxvArgs a) {
   for (int64_t wd = gw; wd < a.nw_out; wd += nwaves) {
     const int64_t i = wd * 64 + ln;
     bool has = false;
+    uint64_t thw = 0ull, tvw = 0ull;
+    if constexpr (Sr<SR>::lor) or_word(a, wd, thw, tvw);
+    else thw = a.t_bm[wd];
     if (i < a.n_out) {
-      bool t_has = bit_of(a.t_bm, i);
+      const bool t_has = (thw >> ln) & 1ull;
       T tv;
-      if constexpr (Sr<SR>::lor) {
-        tv = (T)bit_of(a.t_vb, i);
-        t_has = t_has || tv;
-      } else {
-        tv = ((const T *)a.t_val)[i];
-      }
+      if constexpr (Sr<SR>::lor) tv = (T)((tvw >> ln) & 1ull);
+      else tv = ((const T *)a.t_val)[i];
       T out = tv;
       has = epilogue<SR>(a, i, mask_allowed(a, i), t_has, tv, &out);
       if (has) w[i] = out;
@@ -557,7 +596,8 @@ __global__ __launch_bounds__(kBlock) void k_mxv_merge(MxvArgs a) {
 // here; allowed longer rows are left to the fix-up kernel (their bits of
 // the output word are kept).
 template <int SR>
-__device__ void pull_word(const MxvArgs &a, int64_t wd, int *mark, int *s_end, int *s_base) {
+__device__ void pull_word(const MxvArgs &a, int64_t wd, bool full, int *mark, int *s_end,
+                          int *s_base) {
   using T = typename Sr<SR>::T;
   const int ln = threadIdx.x & 63;
   const int32_t *rp = a.pull.rp, *ci = a.pull.ci;
@@ -653,8 +693,13 @@ __device__ void pull_word(const MxvArgs &a, int64_t wd, int *mark, int *s_end, i
 #pragma unroll
       for (int s = 0; s < kUnroll; ++s) jv[s] = pos[s] >= 0 ? ci[pos[s]] : -1;
       bool pres[kUnroll];
+      if (full) {
 #pragma unroll
-      for (int s = 0; s < kUnroll; ++s) pres[s] = jv[s] >= 0 && bit_of(a.u_bm, jv[s]);
+        for (int s = 0; s < kUnroll; ++s) pres[s] = jv[s] >= 0;
+      } else {
+#pragma unroll
+        for (int s = 0; s < kUnroll; ++s) pres[s] = jv[s] >= 0 && bit_of(a.u_bm, jv[s]);
+      }
       T prod[kUnroll];
 #pragma unroll
       for (int s = 0; s < kUnroll; ++s)
@@ -912,7 +957,7 @@ __device__ void pull_or_pieces4(const MxvArgs &a, const int64_t (&rk)[4], const 
 // One piece (positions [b, e), at most kPushSplit = 64 * kUnroll) of a long
 // row, reduced by the wave in a fixed order; every lane gets the result.
 template <int SR>
-__device__ __forceinline__ void pull_piece(const MxvArgs &a, int64_t b, int64_t e,
+__device__ __forceinline__ void pull_piece(const MxvArgs &a, int64_t b, int64_t e, bool full,
                                            typename Sr<SR>::T &acc, bool &has) {
   using T = typename Sr<SR>::T;
   const int ln = threadIdx.x & 63;
@@ -958,28 +1003,43 @@ __device__ __forceinline__ void pull_piece(const MxvArgs &a, int64_t b, int64_t 
       jv[s] = pos < e ? ci[pos] : -1;
     }
     bool pres[kUnroll];
+    if (full) {
 #pragma unroll
-    for (int s = 0; s < kUnroll; ++s) pres[s] = jv[s] >= 0 && bit_of(a.u_bm, jv[s]);
+      for (int s = 0; s < kUnroll; ++s) pres[s] = jv[s] >= 0;
+    } else {
 #pragma unroll
-    for (int s = 0; s < kUnroll; ++s) {
-      const int64_t pos = b + s * 64 + ln;
-      const T prod = pres[s] ? Sr<SR>::mul(mat_value<T>(a.pull, pos), u_at<T>(a, jv[s]),
-                                           a.pick_vec)
-                             : Sr<SR>::identity();
-      if (__ballot(pres[s])) has = true;
-      acc = Sr<SR>::add(acc, lane_last(wave_scan(prod, Sr<SR>::identity(), SrAdd<SR>())));
+      for (int s = 0; s < kUnroll; ++s) pres[s] = jv[s] >= 0 && bit_of(a.u_bm, jv[s]);
     }
+    T prod[kUnroll];
+#pragma unroll
+    for (int s = 0; s < kUnroll; ++s)
+      prod[s] = pres[s] ? Sr<SR>::mul(mat_value<T>(a.pull, b + s * 64 + ln), u_at<T>(a, jv[s]),
+                                      a.pick_vec)
+                        : Sr<SR>::identity();
+    // a lane's products first, in pairs, then the lanes: one scan a piece
+    static_assert(kUnroll == 4, "two pairs");
+    acc = Sr<SR>::add(Sr<SR>::add(prod[0], prod[1]), Sr<SR>::add(prod[2], prod[3]));
+    has = __ballot(pres[0] || pres[1] || pres[2] || pres[3]) != 0ull;
+    acc = lane_last(wave_scan(acc, Sr<SR>::identity(), SrAdd<SR>()));
   }
 }
 
+// The product: the push's tiles, or the pull sweep.
 template <int SR>
-__global__ __launch_bounds__(kBlock) void k_mxv_sweep(MxvArgs a) {
+__global__ __launch_bounds__(kBlock) void k_mxv_product(MxvArgs a) {
   using T = typename Sr<SR>::T;
-  __shared__ int s_mark[kWavesPerBlock][64];
-  __shared__ int s_end[kWavesPerBlock][64];
-  __shared__ int s_base[kWavesPerBlock][64];
-  __shared__ uint8_t s_res[kWavesPerBlock][4][64];
-  if (mxv_dir(a) != GRB_DIR_PULL) return;
+  __shared__ union {
+    PushTile<T> tile;
+    struct {
+      int mark[kWavesPerBlock][64], end[kWavesPerBlock][64], base[kWavesPerBlock][64];
+      uint8_t res[kWavesPerBlock][4][64];
+    } sweep;
+  } s;
+  bool full;
+  if (gate_dir(a.gate, &full) != GRB_DIR_PULL) {
+    mxv_push<SR>(a, s.tile);
+    return;
+  }
   const int wid = threadIdx.x >> 6, ln = threadIdx.x & 63;
   const int64_t gw = (int64_t)blockIdx.x * kWavesPerBlock + wid;
   const int64_t nwaves = (int64_t)gridDim.x * kWavesPerBlock;
@@ -1016,12 +1076,12 @@ __global__ __launch_bounds__(kBlock) void k_mxv_sweep(MxvArgs a) {
             wds[nq++] = w0 + __ffsll((unsigned long long)todo) - 1;
             todo &= todo - 1;
           }
-          pull_or_words(a, wds, nq, s_mark[wid], s_res[wid]);
+          pull_or_words(a, wds, nq, s.sweep.mark[wid], s.sweep.res[wid]);
         }
       } else {
         for (; todo; todo &= todo - 1) {
           const int k = __ffsll((unsigned long long)todo) - 1;
-          pull_word<SR>(a, w0 + k, s_mark[wid], s_end[wid], s_base[wid]);
+          pull_word<SR>(a, w0 + k, full, s.sweep.mark[wid], s.sweep.end[wid], s.sweep.base[wid]);
         }
       }
     }
@@ -1062,7 +1122,7 @@ __global__ __launch_bounds__(kBlock) void k_mxv_sweep(MxvArgs a) {
         const int64_t ek = min(bk + (int64_t)kPushSplit, (int64_t)a.pull.rp[rk + 1]);
         T acc;
         bool has;
-        pull_piece<SR>(a, bk, ek, acc, has);
+        pull_piece<SR>(a, bk, ek, full, acc, has);
         if (ln == 0) {
           const int64_t hk = hb + (int64_t)k * nwaves;
           hv[hk] = acc;
@@ -1104,10 +1164,14 @@ __device__ __forceinline__ void long_row_out(const MxvArgs &a, int64_t r, bool h
 // l + 64, ..., then the lanes in a fixed order).  One fixed order per row.
 constexpr int kFixLanePieces = 32;
 
+// After a push the merge of t into the output, after a pull the long rows.
 template <int SR>
-__global__ __launch_bounds__(kBlock) void k_mxv_fixup(MxvArgs a) {
+__global__ __launch_bounds__(kBlock) void k_mxv_finish(MxvArgs a) {
   using T = typename Sr<SR>::T;
-  if (mxv_dir(a) != GRB_DIR_PULL) return;
+  if (mxv_dir(a) != GRB_DIR_PULL) {
+    mxv_merge<SR>(a);
+    return;
+  }
   const T *hv = (const T *)a.hp_val;
   const int ln = threadIdx.x & 63;
   const int64_t gw = (int64_t)blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6);
@@ -1213,8 +1277,6 @@ __global__ __launch_bounds__(kBlock) void k_mxv_fixup(MxvArgs a) {
 
 template <int SR>
 void run_mxv(const MxvArgs &a, hipStream_t s) {
-  const int gw_out = (int)std::max<int64_t>(
-      1, std::min<int64_t>((a.nw_out + kWavesPerBlock - 1) / kWavesPerBlock, 1 << 16));
   hipLaunchKernelGGL(k_mxv_init<SR>, dim3(kMxvParts), dim3(kMxvPartThreads), 0, s, a);
   const bool want_push = a.gate.can_push && a.gate.forced != GRB_DIR_PULL;
   const bool want_pull = a.gate.can_pull && a.gate.forced != GRB_DIR_PUSH;
@@ -1240,24 +1302,21 @@ void run_mxv(const MxvArgs &a, hipStream_t s) {
       ca.blk_part = a.n_in > 0 ? a.blk_part : nullptr;  // left by the first kernel
       launch_compact(ca, s);
     }
-    if (!Sr<SR>::lor) hipLaunchKernelGGL(k_mxv_prep<SR>, dim3(gw_out), dim3(kBlock), 0, s, a);
-    hipLaunchKernelGGL(k_mxv_push<SR>, dim3(kExpandGrid), dim3(kBlock), 0, s, a);
+  }
+  if (want_pull && a.u_from_list)
+    launch_list_to_bitmap(a.u_list, a.u_cnt, a.n_in, const_cast<uint64_t *>(a.u_bm), s, &a.gate);
+  hipLaunchKernelGGL(k_mxv_product<SR>, dim3(want_pull ? kSweepGrid : kExpandGrid), dim3(kBlock), 0,
+                     s, a);
+  int64_t g = 0;  // workgroups of the last kernel
+  if (want_push) {
     // the OR semiring's word form takes 64 output words per wave
     const bool word_merge = Sr<SR>::lor && (!a.has_mask || a.mask_struct || !a.m_val);
-    const int gm = word_merge ? (int)std::max<int64_t>(
-                                    1, (a.nw_out + 64 * kWavesPerBlock - 1) / (64 * kWavesPerBlock))
-                              : gw_out;
-    hipLaunchKernelGGL(k_mxv_merge<SR>, dim3(std::min(gm, 1 << 16)), dim3(kBlock), 0, s, a);
+    const int64_t per = word_merge ? 64 * kWavesPerBlock : kWavesPerBlock;
+    g = std::max<int64_t>(1, std::min<int64_t>((a.nw_out + per - 1) / per, kMxvMergeGrid));
   }
-  if (want_pull) {
-    if (a.u_from_list)
-      launch_list_to_bitmap(a.u_list, a.u_cnt, a.n_in, const_cast<uint64_t *>(a.u_bm), s, &a.gate);
-    hipLaunchKernelGGL(k_mxv_sweep<SR>, dim3(kSweepGrid), dim3(kBlock), 0, s, a);
-    if (a.pull.nsplit_rows > 0) {
-      const int gf = (int)std::min<int64_t>((a.pull.nsplit_rows + kBlock - 1) / kBlock, kExpandGrid);
-      hipLaunchKernelGGL(k_mxv_fixup<SR>, dim3(gf), dim3(kBlock), 0, s, a);
-    }
-  }
+  if (want_pull)
+    g = std::max(g, std::min<int64_t>((a.pull.nsplit_rows + kBlock - 1) / kBlock, kExpandGrid));
+  if (g > 0) hipLaunchKernelGGL(k_mxv_finish<SR>, dim3((unsigned)g), dim3(kBlock), 0, s, a);
 }
 
 }  // namespace
