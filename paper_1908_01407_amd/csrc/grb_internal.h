@@ -356,6 +356,7 @@ struct PrArgs {
 // of the updated vertices, dangling mass of the vertices frozen now,
 // vertices active after the iteration, vertices and in-edges updated
 constexpr int kPrFields = 6;
+constexpr int kPrLongGrid = 1024;
 int pr_long_grid(int64_t nsplit_rows);  // workgroups of the long-row kernel
 void launch_pr_init(int is_fp64, const PrArgs &a, void *stream);
 void launch_pr_iter(int is_fp64, const PrArgs &a, void *stream);  // adaptive iff a.act_cur

@@ -29,6 +29,8 @@
 // kept as a running sum on the device.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "grb_device.h"
 #include "grb_internal.h"
 
@@ -258,10 +260,14 @@ __global__ __launch_bounds__(kBlock) void k_pr_iter(PrArgs a) {
 }
 
 // Long rows: one wave per row adds the row's pieces (lane l the pieces
-// l, l + 64, ... in order, then a fixed-order reduction over the lanes) and
-// updates its rank; per-workgroup partials follow those of the SpMV kernel.
+// l, l + 64, ... in order, then a fixed-order reduction over the lanes), four
+// rows at a time so that their loads overlap, and lane q updates row q's
+// rank; per-workgroup partials follow those of the SpMV kernel.  A workgroup
+// for every four rows took 16 us an iteration on RMAT-22 (fp32), and the kernel
+// below 11 to read the partials of all of them; at most kPrLongGrid: 12 and 8.7.
 template <class T, bool AD>
 __global__ __launch_bounds__(kBlock) void k_pr_long(PrArgs a) {
+  constexpr int K = 4;
   if (a.ctrl->converged) return;
   const T dn = (T)(a.ctrl->D / (double)a.n);
   const T *hp = (const T *)a.heavy_part;
@@ -269,32 +275,65 @@ __global__ __launch_bounds__(kBlock) void k_pr_long(PrArgs a) {
   T *xn = (T *)a.xn;
   const int ln = threadIdx.x & 63;
   double delta = 0, dang = 0, dfz = 0, after = 0;
-  const int64_t i = (int64_t)blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6);
-  if (i < a.pull.nsplit_rows) {
-    const int r = a.pull.split_rows[3 * i], first = a.pull.split_rows[3 * i + 1],
-              cnt = a.pull.split_rows[3 * i + 2];
-    if (!AD || bit_of(a.act_cur, r)) {
-      T part = (T)0;
-      for (int k = ln; k < cnt; k += 64) part += hp[first + k];
-      const T acc = lane_last(wave_scan(part, (T)0, OpAdd()));
-      if (ln == 0) {
-        const T po = p[r];
-        const T pn = rank_update<T>(a, acc, dn);
-        const double ch = fabs((double)pn - (double)po);
-        delta = ch;
-        p[r] = pn;
-        const int od = a.out_rp[r + 1] - a.out_rp[r];
-        if (od == 0) {
-          xn[r] = (T)0;
-          dang = (double)pn;
-        } else {
-          xn[r] = pn / (T)od;
+  const int64_t gw = (int64_t)blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6);
+  const int64_t nwaves = (int64_t)gridDim.x * kWavesPerBlock;
+  for (int64_t i0 = gw; i0 < a.pull.nsplit_rows; i0 += K * nwaves) {
+    int r[K], first[K], cnt[K], most = 0;
+#pragma unroll
+    for (int q = 0; q < K; ++q) {
+      const int64_t i = i0 + q * nwaves;
+      const bool in = i < a.pull.nsplit_rows;
+      r[q] = in ? a.pull.split_rows[3 * i] : -1;
+      first[q] = in ? a.pull.split_rows[3 * i + 1] : 0;
+      cnt[q] = in ? a.pull.split_rows[3 * i + 2] : 0;
+    }
+    if (AD) {
+#pragma unroll
+      for (int q = 0; q < K; ++q)
+        if (r[q] >= 0 && !bit_of(a.act_cur, r[q])) {
+          r[q] = -1;
+          cnt[q] = 0;
         }
-        if (AD && ch <= a.eps * (double)po) {  // freezes: clear its bit
-          atomicAnd((unsigned long long *)&a.act_nxt[r >> 6], ~(1ull << (r & 63)));
-          after = -1.0;
-          if (od == 0) dfz = (double)pn;
-        }
+    }
+#pragma unroll
+    for (int q = 0; q < K; ++q) most = max(most, cnt[q]);
+    T part[K];
+#pragma unroll
+    for (int q = 0; q < K; ++q) part[q] = (T)0;
+    for (int k = ln; k < most; k += 64) {
+      T v[K];
+#pragma unroll
+      for (int q = 0; q < K; ++q) v[q] = k < cnt[q] ? hp[first[q] + k] : (T)0;
+#pragma unroll
+      for (int q = 0; q < K; ++q) part[q] += v[q];
+    }
+    int mine = -1;
+    T acc = (T)0;
+#pragma unroll
+    for (int q = 0; q < K; ++q) {
+      const T t = lane_last(wave_scan(part[q], (T)0, OpAdd()));
+      if (ln == q) {
+        mine = r[q];
+        acc = t;
+      }
+    }
+    if (mine >= 0) {
+      const T po = p[mine];
+      const T pn = rank_update<T>(a, acc, dn);
+      const double ch = fabs((double)pn - (double)po);
+      delta += ch;
+      p[mine] = pn;
+      const int od = a.out_rp[mine + 1] - a.out_rp[mine];
+      if (od == 0) {
+        xn[mine] = (T)0;
+        dang += (double)pn;
+      } else {
+        xn[mine] = pn / (T)od;
+      }
+      if (AD && ch <= a.eps * (double)po) {  // freezes: clear its bit
+        atomicAnd((unsigned long long *)&a.act_nxt[mine >> 6], ~(1ull << (mine & 63)));
+        after -= 1.0;
+        if (od == 0) dfz += (double)pn;
       }
     }
   }
@@ -359,7 +398,8 @@ __global__ __launch_bounds__(1024) void k_pr_fixup(PrArgs a, int init) {
 }  // namespace
 
 int pr_long_grid(int64_t nsplit_rows) {
-  return (int)((nsplit_rows + kWavesPerBlock - 1) / kWavesPerBlock);  // a wave per row
+  // a wave per row, up to what is resident at once
+  return (int)std::min<int64_t>((nsplit_rows + kWavesPerBlock - 1) / kWavesPerBlock, kPrLongGrid);
 }
 
 void launch_pr_init(int is_fp64, const PrArgs &a, void *stream) {
