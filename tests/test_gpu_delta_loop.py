@@ -66,3 +66,22 @@ def test_delta_loop(grb, name, flags):
             assert np.all(got >= ref) and got[s] == 0
             if cap == 40:
                 assert np.isfinite(got).sum() > 50
+
+
+@pytest.mark.parametrize("count", [3000, 4096, 4200, 6000])
+def test_delta_loop_long_lists(grb, count):
+    """`count` vertices of one workgroup become pending together: near ones in
+    a wide bucket, far ones in narrow buckets (lists of 4,096 and 3,072)."""
+    n = 100003
+    a, b = np.arange(10, 30), np.arange(1000, 2000)
+    c = np.arange(40000, 40000 + count)
+    path = np.arange(n - 300, n)
+    s = np.concatenate([np.zeros(20, int), a[np.arange(1000) % 20], b[np.arange(count) % 1000],
+                        [c[-1]], path[:-1]])
+    d = np.concatenate([a, b, c, [path[0]], path[1:]])
+    g = graphgen.from_edges(f"fan{count}", n, s, d, 1 + (s * 7 + d) % 64)
+    ref = oracle.sssp(oracle.Adjacency.from_raw(g), 0)[0]
+    A = grb.Matrix.from_raw(g)
+    for delta in (7.5, 64.0, 1e6):
+        dist = grb.sssp(A, 0, delta=delta)
+        assert np.array_equal(dist.cpu().numpy(), ref), (count, delta)
