@@ -300,6 +300,17 @@ __device__ __forceinline__ double atomic_min_f64(double *a, double v) {
       (unsigned long long *)a, (unsigned long long)__double_as_longlong(v)));
 }
 
+// whether those change a word that holds cur
+__device__ __forceinline__ bool min_lowers(float v, float cur) {
+  return !(v < 0.0f) ? __float_as_int(v) < __float_as_int(cur)
+                     : __float_as_uint(v) > __float_as_uint(cur);
+}
+__device__ __forceinline__ bool min_lowers(double v, double cur) {
+  const long long x = __double_as_longlong(v), y = __double_as_longlong(cur);
+  return !(v < 0.0) ? x < y : (unsigned long long)x > (unsigned long long)y;
+}
+__device__ __forceinline__ bool min_lowers(int32_t v, int32_t cur) { return v < cur; }
+
 // Direction of a generic product (Section 4.3.1, Table 5), evaluated by a
 // wave from the first kernel's (count, degree sum) partials, or read from
 // the word an earlier kernel of the product left; forced directions and

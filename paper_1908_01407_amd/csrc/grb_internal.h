@@ -139,6 +139,7 @@ class NoAllocScope {
 // product evaluates the rule itself, so no kernel waits on the host.
 constexpr int kMxvParts = 256;     // workgroups of the generic product's first kernel
 constexpr int kOrCopies = 8;         // OR push: copies of its temporary bitmaps
+constexpr int kOrOneCopy = 64;       // ... fewer tiles than this use one of them
 constexpr int kMxvMergeGrid = 4096;  // ... of its last one, at most
 constexpr int kMxvPartThreads = 1024;
 constexpr int kMxvListChunk = 4096;  // list entries per workgroup of the list preparation

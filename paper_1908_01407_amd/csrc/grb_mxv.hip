@@ -41,13 +41,13 @@ namespace {
 template <int SR> struct Sr;
 template <> struct Sr<GRB_LOR_LAND_BOOL> {
   using T = uint8_t;
-  static constexpr bool lor = true;
+  static constexpr bool lor = true, min = false;
   __device__ static T identity() { return 0; }
   __device__ static T add(T a, T b) { return (T)(a || b); }
 };
 template <class V, bool MIN_ADD, bool MUL_PLUS> struct SrArith {
   using T = V;
-  static constexpr bool lor = false;
+  static constexpr bool lor = false, min = MIN_ADD;
   __device__ static T identity() {
     if (MIN_ADD) return (T)__builtin_huge_val();
     return (T)0;
@@ -61,7 +61,7 @@ template <> struct Sr<GRB_PLUS_TIMES_FP32> : SrArith<float, false, false> {};
 template <> struct Sr<GRB_PLUS_TIMES_FP64> : SrArith<double, false, false> {};
 struct SrMinSel {
   using T = int32_t;
-  static constexpr bool lor = false;
+  static constexpr bool lor = false, min = true;
   __device__ static T identity() { return INT_MAX; }
   __device__ static T add(T a, T b) { return a < b ? a : b; }
   __device__ static T mul(T m, T u, bool pick_vec) { return pick_vec ? u : m; }
@@ -423,20 +423,30 @@ __global__ __launch_bounds__(kCompactThreads) void k_mxv_list_prep(MxvArgs a) {
 __device__ __forceinline__ uint64_t *or_copy(const MxvArgs &a, int c) {
   return (uint64_t *)a.t_val + c * 2 * a.nw_out;
 }
-__device__ __forceinline__ void or_word(const MxvArgs &a, int64_t wd, uint64_t &th, uint64_t &tv) {
-  th = tv = 0ull;
+// A push of few tiles has little to spread and keeps to one copy: reading the
+// others costs the merge 3 of a product's 39 us (RMAT-22, 1e-4 of the indices).
+// Below 64 tiles; below 256, 1 % of 2^18 vertices takes 49 us instead of 44.
+__device__ __forceinline__ bool or_one_copy(const MxvArgs &a) { return a.ctrl->ntiles < kOrOneCopy; }
+__device__ __forceinline__ void or_word(const MxvArgs &a, bool one, int64_t wd, uint64_t &th,
+                                        uint64_t &tv) {
+  if (one) {
+    th = or_copy(a, 0)[wd];
+    tv = or_copy(a, 0)[a.nw_out + wd];
+  } else {
+    th = tv = 0ull;
 #pragma unroll
-  for (int c = 0; c < kOrCopies; ++c) {
-    th |= or_copy(a, c)[wd];
-    tv |= or_copy(a, c)[a.nw_out + wd];
+    for (int c = 0; c < kOrCopies; ++c) {
+      th |= or_copy(a, c)[wd];
+      tv |= or_copy(a, c)[a.nw_out + wd];
+    }
   }
   th |= tv;
 }
 
 // One merge-path tile a workgroup at a time, kPushTile / kBlock edges a thread:
-// its row searches, then its column ids, mask words and target words go in one
-// after the other for all of them, so a tile waits for each once (all but the
-// atomics, above: 12 us).
+// its row searches, then its column ids, mask words and (OR) target words go in
+// one after the other for all of them, so a tile waits for each once (all but
+// the atomics, above: 12 us).
 template <class T>
 struct PushTile {
   int deg[kPushTile + 1], rs[kPushTile + 1];
@@ -495,7 +505,7 @@ __device__ __forceinline__ void mxv_push(const MxvArgs &a, PushTile<typename Sr<
         run[q] = run_tail_or(key, i[q] >= 0 ? 1ull << (i[q] & 63) : 0ull, tail);
         if (i[q] < 0) run[q] = 0ull;
       }
-      uint64_t *copy = or_copy(a, (blockIdx.x / 8) % kOrCopies);
+      uint64_t *copy = or_copy(a, ntiles < kOrOneCopy ? 0 : (blockIdx.x / 8) % kOrCopies);
       int64_t at[K];
 #pragma unroll
       for (int q = 0; q < K; ++q) {
@@ -508,19 +518,29 @@ __device__ __forceinline__ void mxv_push(const MxvArgs &a, PushTile<typename Sr<
           atomicOr((unsigned long long *)&copy[at[q]], (unsigned long long)run[q]);
     } else {
       T prod[K];
-      uint64_t w[K];
 #pragma unroll
-      for (int q = 0; q < K; ++q) {
+      for (int q = 0; q < K; ++q)
         prod[q] = i[q] >= 0 ? Sr<SR>::mul(mat_value<T>(a.push, pos[q]), u[q], a.pick_vec)
                             : Sr<SR>::identity();
-        w[q] = i[q] >= 0 ? a.t_bm[i[q] >> 6] : 0ull;
-      }
+      // one edge after the other, so that what is read before an atomic has
+      // seen the earlier edges' (RMAT-22, 1 % of the indices, plus-times: 131
+      // us a call; the presence words read for all four at once 193).  A
+      // product that cannot lower its target is dropped, and a target already
+      // lowered leaves its presence to the one that lowered it first (min-plus:
+      // 126 us with the atomic always, 103 so).
 #pragma unroll
       for (int q = 0; q < K; ++q) {
         if (i[q] < 0) continue;
+        T *t = (T *)a.t_val + i[q];
+        if constexpr (Sr<SR>::min) {
+          const T cur = *t;
+          if (min_lowers(prod[q], cur)) atomic_add_sr<SR>(t, prod[q]);
+          if (cur != Sr<SR>::identity()) continue;
+        } else {
+          atomic_add_sr<SR>(t, prod[q]);
+        }
         const unsigned long long b = 1ull << (i[q] & 63);
-        atomic_add_sr<SR>(&((T *)a.t_val)[i[q]], prod[q]);
-        if (!(w[q] & b)) atomicOr((unsigned long long *)&a.t_bm[i[q] >> 6], b);
+        if (!(a.t_bm[i[q] >> 6] & b)) atomicOr((unsigned long long *)&a.t_bm[i[q] >> 6], b);
       }
     }
     __syncthreads();
@@ -534,6 +554,7 @@ __device__ __forceinline__ void mxv_merge(const MxvArgs &a) {
   const int64_t gw = (int64_t)blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6);
   const int64_t nwaves = (int64_t)gridDim.x * kWavesPerBlock;
   T *w = (T *)a.w_val;
+  const bool one = Sr<SR>::lor && or_one_copy(a);
   if constexpr (Sr<SR>::lor) {
     if (!a.has_mask || a.mask_struct || !a.m_val) {
       // one output word per lane, 64 words per wave: presence by word
@@ -550,7 +571,7 @@ __device__ __forceinline__ void mxv_merge(const MxvArgs &a) {
           const uint64_t valid = wd == wlast ? mlast : ~0ull;
           const uint64_t A = allowed_word(a, wd), W = a.w_bm[wd];
           uint64_t th;
-          or_word(a, wd, th, tvb);
+          or_word(a, one, wd, th, tvb);
           const uint64_t keep = a.replace ? 0ull : (~A & W);
           plain = A & (acc ? ~W : ~0ull);          // w = t where t is present
           const uint64_t accw = acc ? (A & W) : 0ull;  // w = w (+) t, present either way
@@ -574,7 +595,7 @@ __device__ __forceinline__ void mxv_merge(const MxvArgs &a) {
     const int64_t i = wd * 64 + ln;
     bool has = false;
     uint64_t thw = 0ull, tvw = 0ull;
-    if constexpr (Sr<SR>::lor) or_word(a, wd, thw, tvw);
+    if constexpr (Sr<SR>::lor) or_word(a, one, wd, thw, tvw);
     else thw = a.t_bm[wd];
     if (i < a.n_out) {
       const bool t_has = (thw >> ln) & 1ull;

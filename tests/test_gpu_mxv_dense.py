@@ -94,3 +94,38 @@ def test_or_push_copies(grb, masked):
     grb.vxm(w, m, None, "lor_land", u, A, desc=grb.descriptor(direction=1))
     got = w.to_dict()
     assert {i: bool(b) for i, b in got.items()} == {int(i): bool(tru[i]) for i in np.flatnonzero(has)}
+
+
+@pytest.mark.parametrize("semiring,dt", [("min_plus_fp32", "float32"), ("min_plus_fp64", "float64"),
+                                         ("min_second_int32", "int32")])
+@pytest.mark.parametrize("hub", [1, 300])
+def test_min_push(grb, semiring, dt, hub):
+    """Pushes onto `hub` targets hit by every row and others hit by few, with
+    products of either sign and some that equal the identity: a target whose
+    only product is the identity is present all the same."""
+    rng = np.random.default_rng(hub)
+    n, vdt = 5000, np.dtype(dt)
+    top = np.iinfo(np.int32).max if dt == "int32" else np.inf
+    cols = [np.unique(np.concatenate([np.arange(hub), rng.integers(0, n, 12)])) for _ in range(n)]
+    lens = [c.size for c in cols]
+    rp = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    ci = np.concatenate(cols).astype(np.int32)
+    row = np.repeat(np.arange(n), lens)
+    v = rng.integers(-50, 50, ci.size).astype(vdt)
+    x = rng.integers(-1000, 1000, n).astype(vdt)
+    x[rng.random(n) < 0.3] = top
+    x[rng.random(n) < 0.001] = top
+    present = rng.random(n) < 0.4
+    A = grb.Matrix(n, n, rp, ci, v)
+    u = _vector(grb, n, getattr(torch, dt), x, present)
+    w = grb.Vector(n, getattr(torch, dt))
+    # w(j) = min over i of u(i) (x) A(i, j): the rows of A are pushed
+    grb.mxv(w, None, None, semiring, A, u,
+            desc=grb.descriptor(direction=1, flags=grb.GRB_TRAN_A))
+    keep = present[row]
+    ref = np.full(n, top, vdt)
+    np.minimum.at(ref, ci[keep], x[row[keep]] + (v[keep] if semiring[4] == "p" else 0))
+    has = np.zeros(n, bool)
+    has[ci[keep]] = True
+    assert (ref[has] == top).any()
+    assert w.to_dict() == {int(i): ref[i].item() for i in np.flatnonzero(has)}
