@@ -615,7 +615,7 @@ grb_info run_bfs(grb_matrix A, int32_t source, int32_t *levels, int32_t *parents
   const int64_t n = A->nrows;
   const bool can_pull = A->at.valid();
   if (!can_pull && (desc.direction == GRB_DIR_PULL || parents)) return GRB_NOT_IMPLEMENTED;
-  // (a barrier that one workgroup alone arrives at is never unfinished)
+  // (an exchange with one workgroup alone is never unfinished)
   BfsWs w = bfs_layout(ws, n, (desc.flags & GRB_LOOP_NO_WAIT) ? kOwnTestGroups : 1);
   grb_info info = check_ws(ws, ws_bytes, w.bytes);
   if (info != GRB_SUCCESS) return info;
@@ -660,7 +660,7 @@ grb_info run_bfs(grb_matrix A, int32_t source, int32_t *levels, int32_t *parents
   std::vector<int64_t> launch_level;  // first level of each launch
   // High-diameter, low-degree graphs: levels run back to back in the
   // multi-workgroup loop while the frontier is small (no launch per level);
-  // a frontier that outgrows it, or a barrier it gave up, continues with the
+  // a frontier that outgrows it, or an exchange it gave up, continues with the
   // level kernel below.
   const bool small = A->a.max_deg <= kCoopMaxDeg && desc.direction != GRB_DIR_PULL &&
                      w.own.groups > 0;
@@ -785,6 +785,7 @@ grb_info run_sssp(grb_matrix A, int32_t source, float *dist, const grb_descripto
   sa.rule = desc.switch_rule;
   sa.denom = desc.switch_denominator;
   sa.forced = desc.direction;
+  sa.grid = A->a.max_deg <= kCoopMaxDeg ? kSsspGridLow : kSsspGrid;
   int32_t *cnt = w.ctrl->lists;
   auto at_round = [&](int64_t d) {
     const int i = (int)(d % 3), j = (int)((d + 1) % 3), k = (int)((d + 2) % 3);
@@ -878,7 +879,7 @@ grb_info run_sssp_delta(grb_matrix A, int32_t source, float *dist, float delta,
   at_round(0);
   // low-degree graphs: rounds back to back in the multi-workgroup loop while
   // the pending set is small (no launch per round); a larger set, or a
-  // barrier the loop gave up, continues with the round kernel
+  // wait the loop gave up, continues with the round kernel
   const bool small = A->a.max_deg <= kCoopMaxDeg;
   if (small) {
     sa.own = sw.own;

@@ -266,7 +266,7 @@ void launch_bfs_level(const BfsArgs &a, void *stream);
 constexpr int kCoopMaxDeg = 64;  // graphs whose rows are at most this long use the loop
 // BFS levels in own.groups workgroups while the frontier fits their queues
 // and pushes; starts at level 0 after launch_bfs_start, then two hand-over
-// kernels leave a frontier that outgrew the loop (or a given-up barrier's
+// kernels leave a frontier that outgrew the loop (or a given-up exchange's
 // next frontier) as the bitmap and counters of level ctrl->small_levels.
 // Parents are left to the parents pass.
 void launch_bfs_own(const BfsArgs &a, int32_t source, int64_t max_levels, uint64_t *const F[3],
@@ -280,6 +280,9 @@ constexpr int kSsspSlots = kSsspFields * kCntStripes;
 // workgroups of a round: what the kernel's registers keep resident, 6 per CU
 // (RMAT-22, all rounds: 1024 1.85 ms, 1536 1.72, 2048 1.87, 4096 1.86)
 constexpr int kSsspGrid = 1536;
+// ... of graphs without rows longer than kCoopMaxDeg, whose rounds push a few
+// rows each: 1024 (1000 x 1000 grid: 1024 27.6 ms, 1536 28.7)
+constexpr int kSsspGridLow = 1024;
 struct SsspArgs {
   int64_t n = 0, nw = 0, nnz = 0;
   Csr push, pull;
@@ -298,6 +301,7 @@ struct SsspArgs {
   int64_t *stats = nullptr;
   int32_t d = 0;
   int32_t rule = 0, denom = 10, forced = 0;
+  int grid = kSsspGrid;
   // bucketed rounds in a multi-workgroup loop: own (groups > 0), or the shared
   // state and the two round queues (entries: vertex, and row start | degree <<
   // 32; queue d & 1 at offset (d & 1) * kCoopSegsMax * qseg, segment s of a

@@ -435,24 +435,25 @@ __device__ void sssp_pull(const SsspArgs &a, int *mark, int mode, float low, Nex
 // where loading them with the weights took 815 + 387 + 212 + 154.
 __global__ __launch_bounds__(kBlock, 6) void k_sssp_round(SsspArgs a) {
   __shared__ int s_mark[kWavesPerBlock][64];
-  __shared__ int s_count, s_sumdeg, s_long;
-  __shared__ float s_low;
+  __shared__ int s_cur[kSsspFields];  // count, degree sum, long rows, low
   __shared__ int s_red[kWavesPerBlock][kSsspFields];
-  if (threadIdx.x == 0) {
-    int c = 0, sd = 0, lr = 0, lo = 0;
-    for (int t = 0; t < kCntStripes; ++t) {
-      c += a.cnt_cur[kSsspFields * t];
-      sd += a.cnt_cur[kSsspFields * t + 1];
-      lr += a.cnt_cur[kSsspFields * t + 2];
-      lo = max(lo, a.cnt_cur[kSsspFields * t + 3]);
+  // a lane adds the stripes of one field; one thread adding them all cost a
+  // small round 1.5 of its 15 us (1000 x 1000 grid: 31.8 ms, 28.7 so)
+  static_assert(kSsspSlots == 128 && 64 % kSsspFields == 0, "two stripes a lane");
+  if (threadIdx.x < 64) {
+    const int ln = threadIdx.x, f = ln % kSsspFields;
+    const int x0 = a.cnt_cur[ln], x1 = a.cnt_cur[ln + 64];
+    int x = f == 3 ? max(x0, x1) : x0 + x1;
+#pragma unroll
+    for (int off = kSsspFields; off < 64; off *= 2) {
+      const int y = __shfl_xor(x, off);
+      x = f == 3 ? max(x, y) : x + y;
     }
-    s_low = __int_as_float(0x7f800000 - lo);
-    s_count = c;
-    s_sumdeg = sd;
-    s_long = lr;
+    if (ln < kSsspFields) s_cur[ln] = x;
+    const int c = __shfl(x, 0), sd = __shfl(x, 1);
     if (blockIdx.x == 0) {
-      for (int i = 0; i < kSsspSlots; ++i) a.cnt_clr[i] = 0;
-      if (c > 0) {
+      a.cnt_clr[ln] = a.cnt_clr[ln + 64] = 0;
+      if (ln == 0 && c > 0) {
         a.ctrl->nlev = a.d + 1;
         if (a.stats && a.d < kStatsCap) {
           a.stats[a.d * kStatFields + 0] = c;
@@ -463,6 +464,8 @@ __global__ __launch_bounds__(kBlock, 6) void k_sssp_round(SsspArgs a) {
     }
   }
   __syncthreads();
+  const int s_count = s_cur[0], s_sumdeg = s_cur[1], s_long = s_cur[2];
+  const float s_low = __int_as_float(0x7f800000 - s_cur[3]);
   if (s_count == 0) return;
   const int dir = decide(a, s_count, s_sumdeg);
   Next nx;
@@ -473,19 +476,23 @@ __global__ __launch_bounds__(kBlock, 6) void k_sssp_round(SsspArgs a) {
                      : e * kProbeDen < a.nnz ? kProbe : kGatherAll;
     sssp_pull(a, s_mark[threadIdx.x >> 6], mode, s_low, nx);
   }
-  nx.count = wave_sum(nx.count);
-  nx.edges = wave_sum(nx.edges);
-  nx.longs = wave_sum(nx.longs);
-  nx.low = wave_min(nx.low);
+  int lo = 0x7f800000 - __float_as_int(nx.low);
+  if (__ballot(nx.count != 0 || lo != 0)) {
+    nx.count = wave_sum(nx.count);
+    nx.edges = wave_sum(nx.edges);
+    nx.longs = wave_sum(nx.longs);
+    lo = 0x7f800000 - __float_as_int(wave_min(nx.low));
+  }
   if ((threadIdx.x & 63) == 0) {
     s_red[threadIdx.x >> 6][0] = nx.count;
     s_red[threadIdx.x >> 6][1] = nx.edges;
     s_red[threadIdx.x >> 6][2] = nx.longs;
-    s_red[threadIdx.x >> 6][3] = 0x7f800000 - __float_as_int(nx.low);
+    s_red[threadIdx.x >> 6][3] = lo;
   }
   __syncthreads();
   if (threadIdx.x == 0) {
-    int c = 0, sd = 0, lr = 0, lo = 0;
+    int c = 0, sd = 0, lr = 0;
+    lo = 0;
     for (int i = 0; i < kWavesPerBlock; ++i) {
       c += s_red[i][0];
       sd += s_red[i][1];
@@ -495,9 +502,9 @@ __global__ __launch_bounds__(kBlock, 6) void k_sssp_round(SsspArgs a) {
     const int t = blockIdx.x % kCntStripes;
     // a block may improve vertices that another one counts
     if (lo) atomicMax(&a.cnt_nxt[kSsspFields * t + 3], lo);
-    if (c) {
-      atomicAdd(&a.cnt_nxt[kSsspFields * t], c);
-      atomicAdd(&a.cnt_nxt[kSsspFields * t + 1], sd);
+    if (c) {  // count and degree sum in one: neither carries (both below 2^31)
+      atomicAdd((unsigned long long *)&a.cnt_nxt[kSsspFields * t],
+                ((unsigned long long)(uint32_t)sd << 32) | (uint32_t)c);
       if (lr) atomicAdd(&a.cnt_nxt[kSsspFields * t + 2], lr);
     }
   }
@@ -553,7 +560,7 @@ void launch_sssp_start(const SsspArgs &a, int32_t source, uint64_t *f1, uint64_t
 }
 
 void launch_sssp_round(const SsspArgs &a, void *stream) {
-  hipLaunchKernelGGL(k_sssp_round, dim3(kSsspGrid), dim3(kBlock), 0, (hipStream_t)stream, a);
+  hipLaunchKernelGGL(k_sssp_round, dim3(a.grid), dim3(kBlock), 0, (hipStream_t)stream, a);
 }
 
 }  // namespace grb
