@@ -715,25 +715,32 @@ __global__ __launch_bounds__(kBlock) void k_bfs_parents(BfsArgs a) {
 
 __global__ __launch_bounds__(kBlock) void k_bfs_level(BfsArgs a) {
   __shared__ int s_mark[kWavesPerBlock][64];
-  __shared__ int s_count, s_sumdeg, s_long, s_open, s_prev_sd;
-  __shared__ int s_red[kWavesPerBlock][kCntFields];
-  if (threadIdx.x == 0) {
-    s_open = a.parents ? a.ctrl->pushed[a.d % 3] : 0;
-    s_prev_sd = s_open ? a.ctrl->pushed_sd[a.d % 3] : 0;
-    int c = 0, sd = 0, lr = 0;
-    for (int t = 0; t < kCntStripes; ++t) {
-      c += a.cnt_cur[kCntFields * t];
-      sd += a.cnt_cur[kCntFields * t + 1];
-      lr += a.cnt_cur[kCntFields * t + 2];
+  __shared__ int s_cur[kCntFields];  // count, degree sum, long rows, (unused)
+  __shared__ int s_open, s_prev_sd;
+  __shared__ int s_red[kWavesPerBlock][3];
+  // A lane adds the stripes of one field, and a workgroup ends with one 8-byte
+  // add for count and degree sum: one thread reading, and clearing, all of them
+  // and two adds made RMAT-14 from three sources 75, 60 and 70 us (71, 56 and 67
+  // so) and RMAT-22 184, 187 and 217 (175, 177 and 210).
+  static_assert(kCntSlots == 128 && 64 % kCntFields == 0, "two stripes a lane");
+  if (threadIdx.x < 64) {
+    const int ln = threadIdx.x;
+    int x = a.cnt_cur[ln] + a.cnt_cur[ln + 64];
+    const int open = a.parents ? a.ctrl->pushed[a.d % 3] : 0;
+    const int prev_sd = a.parents ? a.ctrl->pushed_sd[a.d % 3] : 0;
+#pragma unroll
+    for (int off = kCntFields; off < 64; off *= 2) x += __shfl_xor(x, off);
+    if (ln < kCntFields) s_cur[ln] = x;
+    const int c = __shfl(x, 0), sd = __shfl(x, 1);
+    if (ln == 0) {
+      s_open = open;
+      s_prev_sd = open ? prev_sd : 0;
     }
-    s_count = c;
-    s_sumdeg = sd;
-    s_long = lr;
     if (blockIdx.x == 0) {
       // the buffer two levels ahead is cleared even when this level is
       // empty: it still holds the counts of the previous level
-      for (int i = 0; i < kCntSlots; ++i) a.cnt_clr[i] = 0;
-      if (c > 0) {
+      a.cnt_clr[ln] = a.cnt_clr[ln + 64] = 0;
+      if (ln == 0 && c > 0) {
         a.ctrl->nlev = a.d + 1;
         // the next frontier's parents stay open when a push of several
         // vertices finds it
@@ -748,7 +755,7 @@ __global__ __launch_bounds__(kBlock) void k_bfs_level(BfsArgs a) {
     }
   }
   __syncthreads();
-  const int count = s_count;
+  const int count = s_cur[0], s_sumdeg = s_cur[1], s_long = s_cur[2];
   if (count == 0) return;
   const int dir = decide(a, count, s_sumdeg);
   int fc = 0, fd = 0, fl = 0;
@@ -766,9 +773,11 @@ __global__ __launch_bounds__(kBlock) void k_bfs_level(BfsArgs a) {
     bfs_push(a, s_mark[threadIdx.x >> 6], s_long > 0, count == 1, offer, fc, fd, fl);
   else
     bfs_pull(a, s_mark[threadIdx.x >> 6], fc, fd, fl);
-  fc = wave_sum(fc);
-  fd = wave_sum(fd);
-  fl = wave_sum(fl);
+  if (__ballot(fc != 0)) {
+    fc = wave_sum(fc);
+    fd = wave_sum(fd);
+    fl = wave_sum(fl);
+  }
   if ((threadIdx.x & 63) == 0) {
     s_red[threadIdx.x >> 6][0] = fc;
     s_red[threadIdx.x >> 6][1] = fd;
@@ -784,8 +793,9 @@ __global__ __launch_bounds__(kBlock) void k_bfs_level(BfsArgs a) {
     }
     if (c) {
       const int t = blockIdx.x % kCntStripes;
-      atomicAdd(&a.cnt_nxt[kCntFields * t], c);
-      atomicAdd(&a.cnt_nxt[kCntFields * t + 1], sd);
+      // count and degree sum in one: neither carries (both below 2^31)
+      atomicAdd((unsigned long long *)&a.cnt_nxt[kCntFields * t],
+                ((unsigned long long)(uint32_t)sd << 32) | (uint32_t)c);
       if (lr) atomicAdd(&a.cnt_nxt[kCntFields * t + 2], lr);
     }
   }
@@ -833,18 +843,17 @@ __global__ __launch_bounds__(kBlock) void k_bfs_start(BfsArgs a, int32_t source,
     f2[w] = 0ull;
   }
   for (int64_t i = tid; i < a.own.nrec; i += nt) a.own.rec[i] = 0ull;  // no tag
+  static_assert(kCntSlots <= kBlock, "a thread per counter");
+  if (tid < kCntSlots) {
+    const int ds = a.push.rp[source + 1] - a.push.rp[source];
+    // level 0 = {source}: count, degree sum, long rows
+    a.cnt_cur[tid] = tid == 0 ? 1 : tid == 1 ? ds : tid == 2 && ds > kPushSplit ? 1 : 0;
+    a.cnt_nxt[tid] = 0;
+    a.cnt_clr[tid] = 0;
+  }
   if (tid == 0) {
-    for (int i = 0; i < kCntSlots; ++i) {
-      a.cnt_cur[i] = 0;
-      a.cnt_nxt[i] = 0;
-      a.cnt_clr[i] = 0;
-    }
     a.ctrl->nlev = 0;
     a.ctrl->pushed[0] = a.ctrl->pushed[1] = a.ctrl->pushed[2] = 0;
-    const int ds = a.push.rp[source + 1] - a.push.rp[source];
-    a.cnt_cur[0] = 1;  // level 0 = {source}
-    a.cnt_cur[1] = ds;
-    a.cnt_cur[2] = ds > kPushSplit ? 1 : 0;
     a.ctrl->small_levels = INT_MAX;
     a.ctrl->spilled = 0;
   }
@@ -1019,6 +1028,14 @@ __device__ __forceinline__ void own_expand(const BfsArgs &a, OwnShared &sh, int 
   own_queue(a, sh, cnt, q, fn, level, c, won);
 }
 
+// Levels of a low-degree graph back to back: 6,000 dependent levels on the
+// 3000 x 3000 grid, bound by each level's chain (the queue, two loads of the
+// rows, the exchange).  Every workgroup owns a run of vertices and keeps
+// their visited bits and its queue in LDS, so a claim is an LDS atomic and
+// only targets of other owners leave the workgroup.  3000 x 3000 grid from a
+// corner: 16.3 ms, 2.7 us a level (from inside 2.2); a loop over shared queues
+// in device memory (claims by device atomics, a counter barrier) 36.2 ms, 6.0
+// us a level.
 // R: polled records per lane of wave 0 (G <= 64 R).  `most`: a frontier of at
 // most this many vertices is within the edge limit and one the rule pushes;
 // `share`: a level in which no workgroup found and sent more than this keeps

@@ -240,9 +240,9 @@ struct OwnLoop {
   uint64_t *box64 = nullptr;
 };
 // BFS with one kernel per level (grb_bfs.hip).  Each of the three rotating
-// frontier buffers has kCntStripes (count, degree sum) counter pairs.
-// per stripe: frontier size, its degree sum, its rows longer than kPushSplit
-constexpr int kCntFields = 3;
+// frontier buffers has kCntStripes stripes of counters: frontier size, its
+// degree sum, its rows longer than kPushSplit
+constexpr int kCntFields = 4;  // (one unused: the first two are added as one 8-byte word)
 constexpr int kCntSlots = kCntFields * kCntStripes;
 struct BfsArgs {
   int64_t n = 0, nw = 0, nnz = 0;

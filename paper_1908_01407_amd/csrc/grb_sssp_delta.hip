@@ -511,9 +511,9 @@ __device__ __forceinline__ int wave_add(int x) { return lane_last(wave_incl_scan
 // Bucket rounds back to back, bound by each round's chain as the BFS loop's
 // levels are: the owner of a run of vertices keeps their distances in LDS, an
 // improvement of another owner's vertex is a message.  2003 x 1009 grid, width
-// 512, 64 workgroups: 14.5 ms; the queue loop below, whose distances are in
-// device memory, 21.5 ms (7.3 us a round; one workgroup on graphs that fit it
-// takes 2.6 us).
+// 512, 62 workgroups, from two sources: 12.5 and 19.4 ms; the queue loop below,
+// whose distances are in device memory, 18.9 and 26.4 ms (about 8 us a round;
+// one workgroup on graphs that fit it takes 2.6 us).
 __global__ __launch_bounds__(kOwnThreads) void k_sssp_delta_own(SsspArgs a, int32_t source,
                                                                 int max_rounds,
                                                                 uint64_t wait_ticks,
