@@ -226,8 +226,7 @@ def serve_report(paths):
 
 
 MXV_STAGES = [("k_mxv_init", "mxv_init"), ("k_compact", "compact"), ("k_mxv_list_prep", "list_prep"),
-              ("k_mxv_prep", "mxv_prep"), ("k_mxv_push", "mxv_push"), ("k_mxv_merge", "mxv_merge"),
-              ("k_mxv_sweep", "mxv_pull"), ("k_mxv_fixup", "mxv_pull_fixup")]
+              ("k_mxv_product", "mxv_product"), ("k_mxv_finish", "mxv_finish")]
 
 
 def mxv_trace_summary(d, counter=None):
@@ -516,26 +515,22 @@ def bench_extras(grb, graphgen, torch, args):
         "expand_ms_pull": round(st["expand_ms_pull"], 4),
         "per_round_ms": [round(x, 4) for x in st["kernel_ms"]],
         "direction": st["direction"], "frontier": st["frontier"], "edges": st["edges"]}
-    # SSSP pull as masked SpMV over the whole graph: bytes of one full pull round
-    # (col + weight of every stored entry, row extents, frontier bitmap, distances)
+    # SSSP with every round pulled.  No bandwidth from a byte model: a round leaves
+    # out the rows it finds settled and the distances an edge's weight rules out,
+    # how many depends on the run (the counted traffic is in profiles/)
     dpull = grb.descriptor(direction=2, flags=grb.GRB_PROFILE)
     grb.sssp(A, 0, desc=dpull, ws=ws)
     st = grb.last_stats()
-    n = A.nrows
     if st["kernel_ms"]:
         rounds = len(st["kernel_ms"])
         tot_ms = sum(st["kernel_ms"])
-        bytes_round = 8 * A.nnz + 4 * (n + 1) + 4 * n + 4 * n + n / 4
         ex[f"sssp_rmat{args.scale}_forced_pull"] = {
             "rounds": rounds, "ms": round(tot_ms, 4),
-            "bytes_per_round_model": bytes_round,
-            "gbs": round(bytes_round * rounds / (tot_ms / 1e3) / 1e9, 1),
-            "frac_hbm": round(bytes_round * rounds / (tot_ms / 1e3) / 1e9 / HBM_PEAK_GBS, 4),
-            "note": "per round: col_idx + weight of every stored entry (8 B), row extents, "
-                    "frontier distances (gathered, counted once), distances read, candidate "
-                    "and next-frontier bitmaps"}
+            "per_round_ms": [round(x, 4) for x in st["kernel_ms"]],
+            "note": "rows at or below the frontier's smallest distance are left out, and so "
+                    "are the gathers of edges whose weight already rules them out"}
     del ws
-    # connected components (FastSV on the generic product) on the same graph
+    # connected components (FastSV) on the same graph
     wsc = grb.workspace(grb.OP_CC, A)
     grb.cc(A, ws=wsc)
     ms = timed(lambda: grb.cc(A, ws=wsc), args.extra_steps, torch)
@@ -544,7 +539,7 @@ def bench_extras(grb, graphgen, torch, args):
     ex[f"cc_rmat{args.scale}"] = {
         "ms": round(ms, 4), "iterations": it,
         "components": int((lab == np.arange(lab.size)).sum()),
-        "note": "FastSV: per iteration one MIN_SECOND pull product with MIN accumulate, "
+        "note": "FastSV: per iteration one min pull product, "
                 "hooking, shortcutting and grandparents; the last iteration finds no change"}
     del wsc, lab
     # grid 3000 x 3000

@@ -102,7 +102,7 @@ typedef enum grb_binop {
 #define GRB_REPLACE     0x8u /* clear output entries outside the mask */
 #define GRB_PROFILE     0x10u /* drivers: time expand kernels with HIP events */
 /* drivers, test hook for the failure path of the multi-workgroup level loop
- * of BFS / bucketed SSSP on low-degree graphs: every barrier of the loop is
+ * of BFS / bucketed SSSP on low-degree graphs: every exchange of the loop is
  * given up at its first unfinished poll (as when some of the loop's
  * workgroups are not resident), so the search continues in the level
  * kernels from there; results are unchanged. */
@@ -417,10 +417,12 @@ grb_info grb_sssp(float *dist, grb_matrix A, int32_t source, const grb_descripto
  * delta not finite and positive: GRB_INVALID_VALUE.  Stats record per round
  * the pending count, the near degree sum, direction 1 and the bucket.  On
  * graphs whose rows are short (at most 64 entries) the rounds run back to
- * back inside one kernel of 32 workgroups (the device-side loop of
- * grb_bfs, with its barrier, limits and hand-over) while the pending set
- * is small; on the 3000 x 3000 grid a width of 384-512 keeps every round
- * there.
+ * back inside one kernel while the pending set is small, as the levels of
+ * grb_bfs do: up to about 2.09 million vertices in 1 to 64 workgroups that
+ * own the distances of a run of vertices each, above that in 32 workgroups
+ * sharing a queue (on the 3000 x 3000 grid a width of 384-512 keeps every
+ * round there).  A wait of either form is bounded; one given up hands the
+ * pending set to one kernel per round.
  */
 grb_info grb_sssp_delta(float *dist, grb_matrix A, int32_t source, float delta,
                         const grb_descriptor *d, void *ws, size_t ws_bytes, void *stream);
