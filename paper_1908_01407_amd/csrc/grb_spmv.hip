@@ -265,77 +265,90 @@ __global__ __launch_bounds__(kBlock) void k_pr_iter(PrArgs a) {
 // rank; per-workgroup partials follow those of the SpMV kernel.  A workgroup
 // for every four rows took 16 us an iteration on RMAT-22 (fp32), and the kernel
 // below 11 to read the partials of all of them; at most kPrLongGrid: 12 and 8.7.
+// A wave left with one row takes it alone, which is every wave of a graph with
+// few long rows: 300,000 vertices, fp64, 1,140 us a call with four rows' steps
+// for one, 1,132 so.
+template <int K, class T, bool AD>
+__device__ __forceinline__ void pr_long_rows(const PrArgs &a, int64_t i0, int64_t nwaves, T dn,
+                                             double &delta, double &dang, double &dfz,
+                                             double &after) {
+  const T *hp = (const T *)a.heavy_part;
+  T *p = (T *)a.p;
+  T *xn = (T *)a.xn;
+  const int ln = threadIdx.x & 63;
+  int r[K], first[K], cnt[K], most = 0;
+#pragma unroll
+  for (int q = 0; q < K; ++q) {
+    const int64_t i = i0 + q * nwaves;
+    const bool in = i < a.pull.nsplit_rows;
+    r[q] = in ? a.pull.split_rows[3 * i] : -1;
+    first[q] = in ? a.pull.split_rows[3 * i + 1] : 0;
+    cnt[q] = in ? a.pull.split_rows[3 * i + 2] : 0;
+  }
+  if (AD) {
+#pragma unroll
+    for (int q = 0; q < K; ++q)
+      if (r[q] >= 0 && !bit_of(a.act_cur, r[q])) {
+        r[q] = -1;
+        cnt[q] = 0;
+      }
+  }
+#pragma unroll
+  for (int q = 0; q < K; ++q) most = max(most, cnt[q]);
+  T part[K];
+#pragma unroll
+  for (int q = 0; q < K; ++q) part[q] = (T)0;
+  for (int k = ln; k < most; k += 64) {
+    T v[K];
+#pragma unroll
+    for (int q = 0; q < K; ++q) v[q] = k < cnt[q] ? hp[first[q] + k] : (T)0;
+#pragma unroll
+    for (int q = 0; q < K; ++q) part[q] += v[q];
+  }
+  int mine = -1;
+  T acc = (T)0;
+#pragma unroll
+  for (int q = 0; q < K; ++q) {
+    const T t = lane_last(wave_scan(part[q], (T)0, OpAdd()));
+    if (ln == q) {
+      mine = r[q];
+      acc = t;
+    }
+  }
+  if (mine >= 0) {
+    const T po = p[mine];
+    const T pn = rank_update<T>(a, acc, dn);
+    const double ch = fabs((double)pn - (double)po);
+    delta += ch;
+    p[mine] = pn;
+    const int od = a.out_rp[mine + 1] - a.out_rp[mine];
+    if (od == 0) {
+      xn[mine] = (T)0;
+      dang += (double)pn;
+    } else {
+      xn[mine] = pn / (T)od;
+    }
+    if (AD && ch <= a.eps * (double)po) {  // freezes: clear its bit
+      atomicAnd((unsigned long long *)&a.act_nxt[mine >> 6], ~(1ull << (mine & 63)));
+      after -= 1.0;
+      if (od == 0) dfz += (double)pn;
+    }
+  }
+}
+
 template <class T, bool AD>
 __global__ __launch_bounds__(kBlock) void k_pr_long(PrArgs a) {
   constexpr int K = 4;
   if (a.ctrl->converged) return;
   const T dn = (T)(a.ctrl->D / (double)a.n);
-  const T *hp = (const T *)a.heavy_part;
-  T *p = (T *)a.p;
-  T *xn = (T *)a.xn;
-  const int ln = threadIdx.x & 63;
   double delta = 0, dang = 0, dfz = 0, after = 0;
   const int64_t gw = (int64_t)blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6);
   const int64_t nwaves = (int64_t)gridDim.x * kWavesPerBlock;
   for (int64_t i0 = gw; i0 < a.pull.nsplit_rows; i0 += K * nwaves) {
-    int r[K], first[K], cnt[K], most = 0;
-#pragma unroll
-    for (int q = 0; q < K; ++q) {
-      const int64_t i = i0 + q * nwaves;
-      const bool in = i < a.pull.nsplit_rows;
-      r[q] = in ? a.pull.split_rows[3 * i] : -1;
-      first[q] = in ? a.pull.split_rows[3 * i + 1] : 0;
-      cnt[q] = in ? a.pull.split_rows[3 * i + 2] : 0;
-    }
-    if (AD) {
-#pragma unroll
-      for (int q = 0; q < K; ++q)
-        if (r[q] >= 0 && !bit_of(a.act_cur, r[q])) {
-          r[q] = -1;
-          cnt[q] = 0;
-        }
-    }
-#pragma unroll
-    for (int q = 0; q < K; ++q) most = max(most, cnt[q]);
-    T part[K];
-#pragma unroll
-    for (int q = 0; q < K; ++q) part[q] = (T)0;
-    for (int k = ln; k < most; k += 64) {
-      T v[K];
-#pragma unroll
-      for (int q = 0; q < K; ++q) v[q] = k < cnt[q] ? hp[first[q] + k] : (T)0;
-#pragma unroll
-      for (int q = 0; q < K; ++q) part[q] += v[q];
-    }
-    int mine = -1;
-    T acc = (T)0;
-#pragma unroll
-    for (int q = 0; q < K; ++q) {
-      const T t = lane_last(wave_scan(part[q], (T)0, OpAdd()));
-      if (ln == q) {
-        mine = r[q];
-        acc = t;
-      }
-    }
-    if (mine >= 0) {
-      const T po = p[mine];
-      const T pn = rank_update<T>(a, acc, dn);
-      const double ch = fabs((double)pn - (double)po);
-      delta += ch;
-      p[mine] = pn;
-      const int od = a.out_rp[mine + 1] - a.out_rp[mine];
-      if (od == 0) {
-        xn[mine] = (T)0;
-        dang += (double)pn;
-      } else {
-        xn[mine] = pn / (T)od;
-      }
-      if (AD && ch <= a.eps * (double)po) {  // freezes: clear its bit
-        atomicAnd((unsigned long long *)&a.act_nxt[mine >> 6], ~(1ull << (mine & 63)));
-        after -= 1.0;
-        if (od == 0) dfz += (double)pn;
-      }
-    }
+    if (i0 + nwaves < a.pull.nsplit_rows)
+      pr_long_rows<K, T, AD>(a, i0, nwaves, dn, delta, dang, dfz, after);
+    else
+      pr_long_rows<1, T, AD>(a, i0, nwaves, dn, delta, dang, dfz, after);
   }
   double pv[kPrFields] = {delta, dang, dfz, after, 0.0, 0.0};
   block_partials(pv, a.blk_part + kPrFields * a.nblk);
