@@ -353,12 +353,11 @@ __global__ __launch_bounds__(kBlock) void k_sssp_delta_start(SsspArgs a, int32_t
 // A round's near vertices read their distance after leaving the list, so one
 // improved again later in the round is queued again.  Messages are path
 // lengths: applying one late or twice changes nothing, and a workgroup whose
-// list or box is full marks the vertex (the target, or the vertex whose edge
-// it could not send) in the pending bitmap and the loop hands over.  The same
-// goes for an exchange given up: each workgroup leaves with its distances and
-// lists written back, whatever round it reached, the hand-over applies every
-// message still in the boxes, and the round kernels continue from the pending
-// bitmap.
+// list or box is full marks the target in the pending bitmap (relaxed at once
+// where it is another owner's) and the loop hands over.  The same goes for an
+// exchange given up: each workgroup leaves with its distances and lists
+// written back, whatever round it reached, the hand-over applies every message
+// still in the boxes, and the round kernels continue from the pending bitmap.
 // List entries per workgroup (LDS: 160 KB in all; 16 bits each).  A front that
 // lies along a workgroup's rows puts it all there: up to 1,672 near vertices
 // and 776 far ones on the 2003 x 1009 grid, more with those queued again.
@@ -421,6 +420,7 @@ __device__ __forceinline__ void list_add(DeltaShared &sh, uint64_t *pend, int lo
     } else {
       const int c = lo + l[k];
       atomicOr((unsigned long long *)&pend[c >> 6], 1ull << (c & 63));
+      __builtin_amdgcn_s_waitcnt(0);  // the next round may read it
       sh.ovf = 1;
     }
   }
@@ -453,9 +453,9 @@ __device__ __forceinline__ void improved(DeltaShared &sh, uint64_t *pend, int lo
   list_add<K>(sh, pend, lo, add_f, l, &sh.nfar, sh.far, kFarCap);
 }
 
-// Relaxes the targets c[0..4) (none: -1) of vertex v with distances nd.
+// Relaxes the targets c[0..4) (none: -1) with distances nd.
 __device__ __forceinline__ void delta_expand(const SsspArgs &a, DeltaShared &sh, uint64_t *pend, int lo,
-                                             int nv, int w, int v, float limit, int *cnt, uint16_t *list,
+                                             int nv, int w, float limit, int *cnt, uint16_t *list,
                                              uint64_t *box, const int (&c)[4],
                                              const float (&nd)[4]) {
   float old[4];
@@ -490,8 +490,9 @@ __device__ __forceinline__ void delta_expand(const SsspArgs &a, DeltaShared &sh,
       } else if (slot < cap) {
         store_relaxed_u64(&box[((int64_t)w * G + o) * cap + slot],
                           ((uint64_t)(uint32_t)m << 32) | __float_as_uint(nd[k]));
-      } else {  // box full: the vertex stays pending
-        atomicOr((unsigned long long *)&pend[v >> 6], 1ull << (v & 63));
+      } else {  // box full: relaxed in device memory; the target stays pending
+        atomicMin((int *)&a.dist[c[k]], __float_as_int(nd[k]));
+        atomicOr((unsigned long long *)&pend[c[k] >> 6], 1ull << (c[k] & 63));
         sh.ovf = 1;
       }
     }
@@ -554,7 +555,7 @@ __global__ __launch_bounds__(kOwnThreads) void k_sssp_delta_own(SsspArgs a, int3
   uint64_t *put1 = put + (int64_t)G * G * 2, *get1 = get + (int64_t)G * G * 2;
   uint32_t tag = delta_tag(0);
   int cur = 0, d = 0, slow = 0;  // near list, round, second exchanges so far
-  bool spill = false;
+  bool spill = false, over = false;  // over: near vertices beyond the list's end
   for (;;) {
     const int nxt = cur ^ 1;
     const bool rec_round = d < kStatsCap;
@@ -591,16 +592,43 @@ __global__ __launch_bounds__(kOwnThreads) void k_sssp_delta_own(SsspArgs a, int3
         float nd[4];
 #pragma unroll
         for (int q = 0; q < 4; ++q) nd[q] = dv + x[q];
-        delta_expand(a, sh, pend, lo, nv, w, lo + l, limit, &sh.cnt[nxt], sh.near[nxt], box,
-                           c, nd);
+        delta_expand(a, sh, pend, lo, nv, w, limit, &sh.cnt[nxt], sh.near[nxt], box, c, nd);
         for (int q0 = 4; __ballot(q0 < dg) != 0ull; q0 += 4) {
 #pragma unroll
           for (int q = 0; q < 4; ++q) {
             c[q] = q0 + q < dg ? ci[rs + q0 + q] : -1;
             nd[q] = dv + (q0 + q < dg ? wt[rs + q0 + q] : 0.0f);
           }
-          delta_expand(a, sh, pend, lo, nv, w, lo + l, limit, &sh.cnt[nxt], sh.near[nxt],
-                             box, c, nd);
+          delta_expand(a, sh, pend, lo, nv, w, limit, &sh.cnt[nxt], sh.near[nxt], box, c, nd);
+        }
+      }
+      if (over) {
+        // Near vertices that the messages of the last round left beyond the
+        // list's end: the loop hands over after this round, which still takes
+        // them (a round cap counts it).  They are marked pending; marks lie
+        // below nv.
+        for (int i0 = et & ~63; i0 < nv; i0 += T) {
+          const int l = i0 + ln;
+          int rs = 0, dg = 0;
+          float dv = 0.0f;
+          if ((load_relaxed_u64(&pend[(lo + l) >> 6]) >> ln) & 1ull) {
+            dv = *(volatile float *)&sh.dist[l];
+            if (dv < limit) {
+              rs = rp[lo + l];
+              dg = rp[lo + l + 1] - rs;
+            }
+          }
+          esum += dg;
+          for (int q0 = 0; __ballot(q0 < dg) != 0ull; q0 += 4) {
+            int c[4];
+            float nd[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+              c[q] = q0 + q < dg ? ci[rs + q0 + q] : -1;
+              nd[q] = dv + (q0 + q < dg ? wt[rs + q0 + q] : 0.0f);
+            }
+            delta_expand(a, sh, pend, lo, nv, w, limit, &sh.cnt[nxt], sh.near[nxt], box, c, nd);
+          }
         }
       }
       if (rec_round) {
@@ -760,6 +788,7 @@ __global__ __launch_bounds__(kOwnThreads) void k_sssp_delta_own(SsspArgs a, int3
       __syncthreads();
     }
     n = min(sh.n_new, kNearCap);
+    over = sh.n_new > kNearCap;
     cur = nxt;
     {
       uint64_t *b = box, *p = put, *g = get;
@@ -866,9 +895,14 @@ __global__ __launch_bounds__(kOwnThreads) void k_sssp_delta_own(SsspArgs a, int3
     if (tid == 0) sh.nfar = sh.nkeep;
     __syncthreads();
   }
-  // distances and, where the loop hands over, the pending vertices
-  for (int i = tid; i < nv; i += kOwnThreads) a.dist[lo + i] = sh.dist[i];
-  if (spill) {
+  // Distances and, where the loop hands over, the pending vertices.  A message
+  // that found its box full lowered the distance in device memory: every
+  // workgroup saw its sender's flag and spills, also at the round cap.
+  if (!spill) {
+    for (int i = tid; i < nv; i += kOwnThreads) a.dist[lo + i] = sh.dist[i];
+  } else {
+    for (int i = tid; i < nv; i += kOwnThreads)
+      atomicMin((int *)&a.dist[lo + i], __float_as_int(sh.dist[i]));
     const int nf = min(sh.nfar, kFarCap);
     for (int i = tid; i < n + nf; i += kOwnThreads) {
       const int c = lo + (i < n ? sh.near[cur][i] : sh.far[i - n]);
