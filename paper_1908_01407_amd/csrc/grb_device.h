@@ -285,14 +285,22 @@ __device__ __forceinline__ int coop_barrier(unsigned long long *bar, int groups,
   }
 }
 
+// Which integer comparison orders v against any float: values at or below
+// -0.0 by their unsigned bits, downwards; the others (and NaN) by their signed
+// ones.  (Testing v < 0 alone puts -0.0, INT_MIN, below every negative value.)
+__device__ __forceinline__ bool below_zero(float v) { return v <= 0.0f && __float_as_int(v) < 0; }
+__device__ __forceinline__ bool below_zero(double v) {
+  return v <= 0.0 && __double_as_longlong(v) < 0;
+}
+
 // atomic min for floats of either sign (returns the previous value)
 __device__ __forceinline__ float atomic_min_f32(float *a, float v) {
-  if (!(v < 0.0f)) return __int_as_float(atomicMin((int *)a, __float_as_int(v)));
+  if (!below_zero(v)) return __int_as_float(atomicMin((int *)a, __float_as_int(v)));
   return __uint_as_float(atomicMax((unsigned *)a, __float_as_uint(v)));
 }
 
 __device__ __forceinline__ double atomic_min_f64(double *a, double v) {
-  if (!(v < 0.0)) {
+  if (!below_zero(v)) {
     return __longlong_as_double(
         atomicMin((long long *)a, (long long)__double_as_longlong(v)));
   }
@@ -302,12 +310,12 @@ __device__ __forceinline__ double atomic_min_f64(double *a, double v) {
 
 // whether those change a word that holds cur
 __device__ __forceinline__ bool min_lowers(float v, float cur) {
-  return !(v < 0.0f) ? __float_as_int(v) < __float_as_int(cur)
-                     : __float_as_uint(v) > __float_as_uint(cur);
+  return !below_zero(v) ? __float_as_int(v) < __float_as_int(cur)
+                        : __float_as_uint(v) > __float_as_uint(cur);
 }
 __device__ __forceinline__ bool min_lowers(double v, double cur) {
   const long long x = __double_as_longlong(v), y = __double_as_longlong(cur);
-  return !(v < 0.0) ? x < y : (unsigned long long)x > (unsigned long long)y;
+  return !below_zero(v) ? x < y : (unsigned long long)x > (unsigned long long)y;
 }
 __device__ __forceinline__ bool min_lowers(int32_t v, int32_t cur) { return v < cur; }
 
