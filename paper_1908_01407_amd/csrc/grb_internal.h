@@ -108,7 +108,7 @@ struct Ctrl {
   int32_t small_levels;       // BFS / SSSP: levels or rounds run by the multi-workgroup loop
   int32_t spilled;            // ... which then handed a frontier to the wide kernels
   int32_t pushed_sd[3];       // BFS: degree sum of the push that found the buffer's frontier
-  int32_t pad32;
+  float limit;                // bucketed SSSP: the limit of the last round
   int64_t pad[2];
 };
 
@@ -213,7 +213,7 @@ struct CoopCtl {
   int32_t cnt[2][kCoopSegsMax];   // entries queued
   int32_t esum[2][kCoopSegsMax];  // degree sum of the near ones
   int32_t near[2][kCoopSegsMax];  // entries below the round's limit
-  int32_t far[2][kCoopSegsMax];   // smallest bucket of the others (INT_MAX: none)
+  int32_t far[2][kCoopSegsMax];   // bits of the others' smallest distance (INT_MAX: none)
 };
 constexpr int64_t kCoopMaxLevels = int64_t(1) << 24;  // arrivals stay below 2^32
 
@@ -317,7 +317,7 @@ void launch_sssp_start(const SsspArgs &a, int32_t source, uint64_t *f1, uint64_t
 void launch_sssp_round(const SsspArgs &a, void *stream);
 
 // Bucketed SSSP (near-far rounds, push only): per stripe the next round's
-// near count, its degree sum, its rows with pieces, the smallest far bucket
+// near count, its degree sum, its rows with pieces, the smallest far distance (bits)
 // and the pending count
 constexpr int kDeltaFields = 5;
 constexpr int kDeltaSlots = kDeltaFields * kCntStripes;

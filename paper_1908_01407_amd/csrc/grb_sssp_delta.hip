@@ -3,9 +3,10 @@
 // paper's Bellman-Ford rounds relax every improved vertex at once, which on
 // high-diameter graphs (road networks, grids) relaxes each edge over a
 // hundred times; here a round relaxes only the pending vertices whose
-// distance lies below the current bucket's limit (B + 1) * delta, and the
-// others wait in the pending set.  The bucket advances to the smallest
-// pending bucket once no vertex is left below the limit.  Any order of
+// distance lies below the current limit, the end of a bucket of width delta,
+// and the others wait in the pending set.  Once no vertex is left below the
+// limit it moves to the end of the bucket of the smallest pending distance,
+// which lies above that distance (grb_bucket.h).  Any order of
 // relaxations reaches the same fixed point, so the distances are the exact
 // shortest distances, identical to the Bellman-Ford rounds.
 //
@@ -18,11 +19,12 @@
 //   carried into the next set;
 // * the first setter of a bit counts the new member: near (below the
 //   limit: size, degree sum, rows with pieces) or far (the smallest far
-//   bucket), plus the pending total, all in striped counters.
+//   distance's bits), plus the pending total, all in striped counters.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
 
+#include "grb_bucket.h"
 #include "grb_device.h"
 #include "grb_internal.h"
 
@@ -37,23 +39,21 @@ constexpr int kCoopSegsPerLane = kCoopSegs / 64;
 static_assert(kCoopSegs % 64 == 0 && kCoopSegs <= kCoopSegsMax,
               "segment counts are read by one wave");
 
+// far: bits of the smallest far distance (INT_MAX: none)
 struct DCount {
   int near = 0, sd = 0, lng = 0, far = INT_MAX, pend = 0;
 };
 
-__device__ __forceinline__ int bucket_of(float d, float delta) { return (int)(d / delta); }
-
 // Counts a new member of the next pending set with distance nd and out-
 // degree pd.
-__device__ __forceinline__ void count_new(const SsspArgs &a, int pd, float nd, float limit,
-                                          DCount &c) {
+__device__ __forceinline__ void count_new(int pd, float nd, float limit, DCount &c) {
   c.pend += 1;
   if (nd < limit) {
     c.near += 1;
     c.sd += pd;
     c.lng += pd > kPushSplit ? 1 : 0;
   } else {
-    c.far = min(c.far, bucket_of(nd, a.delta));
+    c.far = min(c.far, __float_as_int(nd));
   }
 }
 
@@ -91,7 +91,7 @@ __device__ __forceinline__ void relax_near(const SsspArgs &a, const int (&c)[kUn
   }
 #pragma unroll
   for (int s = 0; s < kUnroll; ++s)
-    if (c[s] >= 0 && !(o[s] & (1ull << (c[s] & 63)))) count_new(a, r1[s] - r0[s], nd[s], limit, cnt);
+    if (c[s] >= 0 && !(o[s] & (1ull << (c[s] & 63)))) count_new(r1[s] - r0[s], nd[s], limit, cnt);
 }
 
 __device__ void delta_push(const SsspArgs &a, int *mark, float limit, bool pieces, DCount &cnt) {
@@ -124,7 +124,7 @@ __device__ void delta_push(const SsspArgs &a, int *mark, float limit, bool piece
       oldw = __shfl(oldw, tail);
       if (carry && !((oldw >> (u & 63)) & 1ull)) {
         cnt.pend += 1;
-        cnt.far = min(cnt.far, bucket_of(du, a.delta));
+        cnt.far = min(cnt.far, __float_as_int(du));
       }
       int cur = 0, end = 0;
       if (active) {
@@ -209,10 +209,13 @@ __device__ void delta_push(const SsspArgs &a, int *mark, float limit, bool piece
 
 __global__ __launch_bounds__(kBlock) void k_sssp_delta_round(SsspArgs a) {
   __shared__ int s_mark[kWavesPerBlock][64];
-  __shared__ int s_bucket, s_pend, s_pieces;
+  __shared__ int s_pend, s_pieces;
+  __shared__ float s_limit;
   __shared__ int s_red[kWavesPerBlock][kDeltaFields];
   if (threadIdx.x == 0) {
     int nr = 0, sd = 0, lg = 0, far = INT_MAX, pend = 0;
+    int bucket = a.ctrl->bucket;
+    float limit = a.ctrl->limit;
     for (int t = 0; t < kCntStripes; ++t) {
       nr += a.cnt_cur[kDeltaFields * t];
       sd += a.cnt_cur[kDeltaFields * t + 1];
@@ -221,9 +224,12 @@ __global__ __launch_bounds__(kBlock) void k_sssp_delta_round(SsspArgs a) {
       pend += a.cnt_cur[kDeltaFields * t + 4];
     }
     // stay in the bucket while it has members, else move to the nearest
-    // pending bucket
-    const int bucket = nr > 0 ? a.ctrl->bucket : far;
-    s_bucket = bucket;
+    // pending one
+    if (nr == 0) {
+      bucket = bucket_of(__int_as_float(far), a.delta);
+      limit = bucket_end(__int_as_float(far), a.delta);
+    }
+    s_limit = limit;
     s_pend = pend;
     // a row below the limit may be long although no long row was counted
     // near (its distance can drop after its first insertion), so the pieces
@@ -237,6 +243,7 @@ __global__ __launch_bounds__(kBlock) void k_sssp_delta_round(SsspArgs a) {
       if (pend > 0) {
         a.ctrl->nlev = a.d + 1;
         a.ctrl->bucket = bucket;
+        a.ctrl->limit = limit;
         if (a.stats && a.d < kStatsCap) {
           a.stats[a.d * kStatFields + 0] = pend;
           a.stats[a.d * kStatFields + 1] = sd;
@@ -248,7 +255,7 @@ __global__ __launch_bounds__(kBlock) void k_sssp_delta_round(SsspArgs a) {
   }
   __syncthreads();
   if (s_pend == 0) return;
-  const float limit = (float)(s_bucket + 1) * a.delta;
+  const float limit = s_limit;
   DCount c;
   delta_push(a, s_mark[threadIdx.x >> 6], limit, s_pieces != 0, c);
   c.near = wave_sum(c.near);
@@ -316,6 +323,7 @@ __global__ __launch_bounds__(kBlock) void k_sssp_delta_start(SsspArgs a, int32_t
     a.cnt_cur[4] = 1;
     a.ctrl->nlev = 0;
     a.ctrl->bucket = 0;
+    a.ctrl->limit = bucket_end(0.0f, a.delta);
     a.ctrl->small_levels = INT_MAX;
     a.ctrl->spilled = 0;
     if (a.coop) {  // the multi-workgroup loop's first queue: {source}, near
@@ -548,7 +556,8 @@ __global__ __launch_bounds__(kOwnThreads) void k_sssp_delta_own(SsspArgs a, int3
   int n = mine ? 1 : 0, npre = 0;
   int prs = 0, pdg = 0, pc[4] = {-1, -1, -1, -1};
   float pw[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-  float limit = a.delta;
+  float limit = bucket_end(0.0f, a.delta);
+  int bucket = 0;
   uint64_t *box = a.own.box64, *box1 = box + (int64_t)G * G * cap;
   uint64_t *put = a.own.rec + 2 * ((int64_t)ln * G + w);
   uint64_t *get = a.own.rec + 2 * ((int64_t)w * G + ln);
@@ -722,9 +731,6 @@ __global__ __launch_bounds__(kOwnThreads) void k_sssp_delta_own(SsspArgs a, int3
         if (rec_round) sh.edges = 0;
         if (w == 0 && !gave_up && any_n) {
           a.ctrl->nlev = d + 1;
-          const float bk = floorf(limit / a.delta) - 1.0f;
-          const int bucket = bk < 2.0e9f ? (int)bk : INT_MAX;
-          a.ctrl->bucket = bucket;
           if (rec_round && a.stats) {
             a.stats[d * kStatFields + 0] = np;
             a.stats[d * kStatFields + 1] = ne;
@@ -867,8 +873,12 @@ __global__ __launch_bounds__(kOwnThreads) void k_sssp_delta_own(SsspArgs a, int3
     }
     if (!(mm < inf)) break;  // nothing pending anywhere: done
     const float was = limit;
-    limit = (floorf(mm / a.delta) + 1.0f) * a.delta;
-    if (!(mm < limit)) limit = __uint_as_float(__float_as_uint(mm) + 1u);  // rounding: past mm
+    limit = bucket_end(mm, a.delta);
+    bucket = bucket_of(mm, a.delta);
+    if (w == 0 && tid == 0) {
+      a.ctrl->bucket = bucket;
+      a.ctrl->limit = limit;
+    }
     // split the far list in place, kOwnThreads entries at a time
     if (tid == 0) sh.cnt[cur] = 0;
     for (int b = 0; b < nf; b += kOwnThreads) {
@@ -948,7 +958,7 @@ __global__ __launch_bounds__(kBlock) void k_sssp_delta_own_handover(SsspArgs a, 
   if (!a.ctrl->spilled) return;
   const int h = a.ctrl->small_levels;
   uint64_t *const F[3] = {F0, F1, F2};
-  const float limit = (float)(a.ctrl->bucket + 1) * a.delta;
+  const float limit = a.ctrl->limit;
   const int ln = threadIdx.x & 63;
   const int64_t gw = (int64_t)blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6);
   const int64_t nwaves = (int64_t)gridDim.x * kWavesPerBlock;
@@ -964,7 +974,7 @@ __global__ __launch_bounds__(kBlock) void k_sssp_delta_own_handover(SsspArgs a, 
       const int k = __ffsll((unsigned long long)any) - 1;
       const uint64_t xk = __shfl(x, k);
       const int64_t v = (w0 + k) * 64 + ln;
-      if ((xk >> ln) & 1ull) count_new(a, a.push.rp[v + 1] - a.push.rp[v], a.dist[v], limit, c);
+      if ((xk >> ln) & 1ull) count_new(a.push.rp[v + 1] - a.push.rp[v], a.dist[v], limit, c);
     }
   }
   c.near = wave_sum(c.near);
@@ -993,13 +1003,13 @@ __global__ __launch_bounds__(kBlock) void k_sssp_delta_own_handover(SsspArgs a, 
 // on the float bits, the target's row extents loaded beside) and queues
 // every target it improved, a member above it is queued again (carried).
 // Per wave: entries queued, near ones (below the limit), their degree sum,
-// the smallest bucket of the others.  The bucket moves to the nearest
-// pending one when no near member is left.  A pending set that outgrows
+// the smallest distance of the others.  The limit moves to the end of that
+// one's bucket when no near member is left.  A pending set that outgrows
 // the segments (or the loop's edge limit) goes to the round kernel.
 // Queues in the wave's segment of the next queue (slots counted in wcnt);
 // every queued vertex gets its membership bit, also past the segment's end.
 __device__ __forceinline__ void coop_queue(bool want, int x, int rs, int dg, float dx, float limit,
-                                           float delta, uint64_t *fill, int32_t *qv, uint64_t *qe,
+                                           uint64_t *fill, int32_t *qv, uint64_t *qe,
                                            int seg, int &wcnt, int &wnear, int &wsd, int &wfar) {
   const int ln = threadIdx.x & 63;
   const uint64_t m = __ballot(want);
@@ -1007,7 +1017,7 @@ __device__ __forceinline__ void coop_queue(bool want, int x, int rs, int dg, flo
   const bool nr = want && dx < limit;
   wnear += wave_sum(nr ? 1 : 0);
   wsd += wave_sum(nr ? dg : 0);
-  const int far = (want && !nr) ? bucket_of(dx, delta) : INT_MAX;
+  const int far = (want && !nr) ? __float_as_int(dx) : INT_MAX;
   wfar = min(wfar, lane_last(wave_scan(far, INT_MAX, [](int p, int q) { return p < q ? p : q; })));
   if (want) {
     const int slot = wcnt + __popcll(m & mask_below(ln));
@@ -1032,8 +1042,8 @@ __global__ __launch_bounds__(kCoopThreads) void k_sssp_delta_coop(SsspArgs a, in
   const int w = (int)blockIdx.x;
   const int my_seg = w * (kCoopThreads / 64) + (tid >> 6);
   const int seg = a.qseg, qsize = kCoopSegs * seg;
-  const float delta = a.delta;
   int bucket = 0;
+  float limit = bucket_end(0.0f, a.delta);
   int64_t d = 0;
   bool spill = false;
   for (;;) {
@@ -1078,10 +1088,14 @@ __global__ __launch_bounds__(kCoopThreads) void k_sssp_delta_coop(SsspArgs a, in
       spill = true;
       break;
     }
-    bucket = s_near > 0 ? bucket : s_far;
+    if (s_near == 0) {
+      bucket = bucket_of(__int_as_float(s_far), a.delta);
+      limit = bucket_end(__int_as_float(s_far), a.delta);
+    }
     if (w == 0 && tid == 0) {
       a.ctrl->nlev = (int)d + 1;
       a.ctrl->bucket = bucket;
+      a.ctrl->limit = limit;
       if (a.stats && d < kStatsCap) {
         a.stats[d * kStatFields + 0] = n;
         a.stats[d * kStatFields + 1] = s_sd;
@@ -1089,7 +1103,6 @@ __global__ __launch_bounds__(kCoopThreads) void k_sssp_delta_coop(SsspArgs a, in
         a.stats[d * kStatFields + 3] = bucket;
       }
     }
-    const float limit = (float)(bucket + 1) * delta;
     uint64_t *const cons = sl ? F1 : F0, *const fill = sl ? F0 : F1;
     const int qin = sl * qsize, qout = (sl ^ 1) * qsize + my_seg * seg;
     int32_t *const qvo = a.qv + qout;
@@ -1134,7 +1147,7 @@ __global__ __launch_bounds__(kCoopThreads) void k_sssp_delta_coop(SsspArgs a, in
       }
       const bool relax = take && dv < limit;
       // carried: a member above the limit stays pending
-      coop_queue(take && !relax, v, rs, dg, dv, limit, delta, fill, qvo, qeo, seg, wcnt, wnear,
+      coop_queue(take && !relax, v, rs, dg, dv, limit, fill, qvo, qeo, seg, wcnt, wnear,
                  wsd, wfar);
       for (int q0 = 0; __ballot(relax && q0 < dg) != 0ull; q0 += 4) {
         int c[4];
@@ -1159,7 +1172,7 @@ __global__ __launch_bounds__(kCoopThreads) void k_sssp_delta_coop(SsspArgs a, in
 #pragma unroll
         for (int q = 0; q < 4; ++q)
           coop_queue(c[q] >= 0 && nd[q] < __int_as_float(old[q]), c[q], r0[q], r1[q] - r0[q],
-                     nd[q], limit, delta, fill, qvo, qeo, seg, wcnt, wnear, wsd, wfar);
+                     nd[q], limit, fill, qvo, qeo, seg, wcnt, wnear, wsd, wfar);
       }
     }
     // the wave's segment counters go with its entries; the barrier follows
