@@ -193,7 +193,7 @@ struct MsWs {
   Ctrl *ctrl;
   int64_t *stats;
   unsigned long long *cnt;
-  uint64_t *V, *S, *F[2], *act[3];
+  uint64_t *V, *B[3], *act[3];  // B: frontier blocks, one of them S in the two-kernel form
   // sessions: start level per query, three "has a frontier bit" arrays of W
   // words, the joining queries' bits per word, lane / source staging
   int32_t *start, *lanes, *sources;
@@ -209,14 +209,13 @@ MsWs ms_layout(void *ws, int64_t n, int64_t k) {
   t.ctrl = c.take<Ctrl>(1);
   t.stats = c.take<int64_t>((size_t)kStatsCap * kStatFields);
   t.cnt = c.take<unsigned long long>((size_t)6 * kCntStripes);
+  t.alive = c.take<unsigned long long>((size_t)3 * std::max<int64_t>(W, 1));  // read back with cnt
   t.V = c.take<uint64_t>((size_t)nb);
-  t.S = c.take<uint64_t>((size_t)nb);
-  for (int i = 0; i < 2; ++i) t.F[i] = c.take<uint64_t>((size_t)nb);
+  for (int i = 0; i < 3; ++i) t.B[i] = c.take<uint64_t>((size_t)nb);
   for (int i = 0; i < 3; ++i) t.act[i] = c.take<uint64_t>((size_t)std::max<int64_t>(nw, 1));
   t.start = c.take<int32_t>((size_t)std::max<int64_t>(k, 1));
   t.lanes = c.take<int32_t>((size_t)std::max<int64_t>(k, 1));
   t.sources = c.take<int32_t>((size_t)std::max<int64_t>(k, 1));
-  t.alive = c.take<unsigned long long>((size_t)3 * std::max<int64_t>(W, 1));
   t.clr = c.take<uint64_t>((size_t)std::max<int64_t>(W, 1));
   t.bytes = c.off;
   return t;
@@ -1464,6 +1463,99 @@ grb_info grb_sssp_delta(float *dist, grb_matrix A, int32_t source, float delta,
   return run_sssp_delta(A, source, dist, delta, desc, ws, ws_bytes, stream);
 }
 
+}  // extern "C"
+
+namespace {
+
+// The frontier blocks of a batched BFS and the form of its levels.  Two kernels a
+// level: the frontier, the previous one (cleared by the level, then the next
+// one) and S.  One kernel: the frontier, the next one (clear), the previous one.
+// `act` and the counters rotate by the level in both.
+struct MsBlocks {
+  uint64_t *cur, *prev, *third;  // third: S or the clear block
+  bool direct;
+  MsBlocks() = default;
+  MsBlocks(const MsWs &w, bool d) : cur(w.B[0]), prev(w.B[1]), third(w.B[2]), direct(d) {}
+  void at_level(MsbfsArgs &ma, const MsWs &w, int64_t dd) const {
+    const int i = (int)(dd % 3), j = (int)((dd + 1) % 3), q = (int)((dd + 2) % 3);
+    ma.F = cur;
+    ma.Fn = direct ? third : prev;
+    ma.Fc = direct ? prev : nullptr;
+    ma.S = direct ? nullptr : third;
+    ma.act = w.act[i];
+    ma.actn = w.act[j];
+    ma.actc = w.act[q];
+    ma.cnt_cur = w.cnt + (size_t)i * 2 * kCntStripes;
+    ma.cnt_nxt = w.cnt + (size_t)j * 2 * kCntStripes;
+    ma.cnt_clr = w.cnt + (size_t)q * 2 * kCntStripes;
+    ma.d = (int32_t)std::min<int64_t>(dd, INT32_MAX);
+  }
+  void advance() {  // after a level
+    uint64_t *c = cur;
+    if (direct) {  // the cleared block is the next level's clear one
+      cur = third;
+      third = prev;
+    } else {
+      cur = prev;
+    }
+    prev = c;
+  }
+  // whether the form changed: the caller then fills the third block
+  // (launch_msbfs_form) before the next level
+  bool set_direct(bool d) {
+    const bool changed = d != direct;
+    direct = d;
+    return changed;
+  }
+};
+
+// Which form a batch of levels takes.  The two-kernel one pays where a vertex is
+// reached over many edges, the one-kernel one where a level is little more than
+// its launches.  All levels in two kernels / in one: k 2, 64 and 256 on the 300 x
+// 300 grid 7.2 / 5.4, 9.8 / 8.1 and 22.6 / 16.7 ms, on the 1000 x 1000 one 31.5 /
+// 21.0, 60.3 / 40.0 and 152 / 98 ms; a random graph of 1M vertices and 16M entries
+// 600 / 528, 2063 / 3230 and 6250 / 12537 us; R-MAT graphs of 2^14 to 2^20
+// vertices two kernels, by up to 2.8 (k 2 to 256).  Hence on low-degree graphs one
+// kernel from the start where k times the entries is small, else once the
+// frontier's out-edges are a third of a level's (an eighth within the first
+// levels, which grow), and on the others only for a long tail.
+bool ms_small(grb_matrix A, int32_t k) {
+  return A->a.max_deg <= kCoopMaxDeg && (int64_t)k * A->nnz <= (int64_t)1 << 26;
+}
+
+// edges: out-edges of the frontier's (vertex, query word) pairs; d: levels run;
+// now: the form of the last batch (left only at twice the bound)
+bool ms_direct_next(grb_matrix A, int32_t k, unsigned long long edges, int64_t d, bool now) {
+  if (ms_small(A, k)) return true;
+  const bool low = A->a.max_deg <= kCoopMaxDeg;
+  if (!low && d < 8) return now;
+  const unsigned long long full = (unsigned long long)A->nnz * (unsigned long long)((k + 63) / 64);
+  const unsigned long long f = !low ? 16 : (d < 8 ? 8 : 3);
+  return (now ? f : 2 * f) * edges < full;
+}
+
+// ... of a session's levels: its queries join at different times, and by the time
+// a large frontier is seen it may be past its largest level.  So two kernels only
+// for most of a level's edges, and not at all where rows average 8 entries or
+// fewer (64 lanes, four levels a step: random graphs of 6 entries a row 3.56 ms
+// in one kernel, 4.5 so chosen, 4.9 in two; of 16 entries 17.8, 15.1 and 14.1).
+bool ms_direct_session(grb_matrix A, int W, unsigned long long edges, bool now) {
+  if (A->a.max_deg > kCoopMaxDeg) return false;
+  const unsigned long long full = (unsigned long long)A->nnz * (unsigned long long)W;
+  return A->nnz <= 8 * A->nrows || 3 * edges < (now ? 2 : 1) * full;
+}
+
+// out-edges of the frontier of level d, from the counters read back
+unsigned long long ms_edges(const unsigned long long *cnt, int64_t d) {
+  unsigned long long e = 0;
+  for (int t = 0; t < kCntStripes; ++t) e += cnt[(size_t)(d % 3) * 2 * kCntStripes + 2 * t + 1];
+  return e;
+}
+
+}  // namespace
+
+extern "C" {
+
 grb_info grb_msbfs(int32_t *levels, grb_matrix A, const int32_t *sources, int32_t k,
                    const grb_msbfs_tile *tile, const grb_descriptor *d, void *ws, size_t ws_bytes,
                    void *stream) {
@@ -1503,42 +1595,33 @@ grb_info grb_msbfs(int32_t *levels, grb_matrix A, const int32_t *sources, int32_
   ma.can_pull = can_pull;
   ma.levels = levels;
   ma.V = w.V;
-  ma.S = w.S;
   ma.cnt_base = w.cnt;
   ma.ctrl = w.ctrl;
   ma.stats = w.stats;
   ma.rule = desc.switch_rule;
   ma.denom = desc.switch_denominator;
   ma.forced = desc.direction;
-  auto at_level = [&](int64_t dd) {
-    const int i = (int)(dd % 3), j = (int)((dd + 1) % 3), q = (int)((dd + 2) % 3);
-    ma.F = w.F[dd & 1];
-    ma.Fn = w.F[(dd + 1) & 1];
-    ma.act = w.act[i];
-    ma.actn = w.act[j];
-    ma.actc = w.act[q];
-    ma.cnt_cur = w.cnt + (size_t)i * 2 * kCntStripes;
-    ma.cnt_nxt = w.cnt + (size_t)j * 2 * kCntStripes;
-    ma.cnt_clr = w.cnt + (size_t)q * 2 * kCntStripes;
-    ma.d = (int32_t)std::min<int64_t>(dd, INT32_MAX);
-  };
-  at_level(0);
+  MsBlocks blk(w, ms_small(A, k));
+  blk.at_level(ma, w, 0);
   launch_msbfs_start(ma, sources, w.act[1], w.act[2], stream);
   const int64_t cap = desc.max_iter > 0 ? desc.max_iter : INT64_MAX;
   int64_t dlev = 0;
   // a search deeper than the first batch usually ends a level or two later, and
-  // an empty level still costs its launches (16 us with the gaps), so the second
-  // batch is short and the next ones double
+  // an empty level of two kernels still costs 16 us with the gaps (of one 4.5), so
+  // the second batch of those is short and the next ones double, up to where the
+  // empty levels of a batch cost what the read-backs (18 us) of shorter ones
+  // would: about the root of 16 times the levels run
   int chunk = 6;
   bool first_batch = true;
   std::vector<unsigned long long> hcnt((size_t)6 * kCntStripes);
   Ctrl hc{};
   for (;;) {
     for (int i = 0; i < chunk && dlev < cap; ++i, ++dlev) {
-      at_level(dlev);
+      blk.at_level(ma, w, dlev);
       if (profile) (void)hipEventRecord(g_events.get(2 * (size_t)dlev), s);
       launch_msbfs_level(ma, grid, stream);
       if (profile) (void)hipEventRecord(g_events.get(2 * (size_t)dlev + 1), s);
+      blk.advance();
     }
     if ((info = check_launch()) != GRB_SUCCESS) return info;
     if (!read_back({{hcnt.data(), w.cnt, hcnt.size() * sizeof(unsigned long long)},
@@ -1548,7 +1631,12 @@ grb_info grb_msbfs(int32_t *levels, grb_matrix A, const int32_t *sources, int32_
     unsigned long long next = 0;
     for (int t = 0; t < kCntStripes; ++t) next += hcnt[(size_t)(dlev % 3) * 2 * kCntStripes + 2 * t];
     if (next == 0 || dlev >= cap) break;
-    chunk = first_batch ? 2 : std::min(chunk * 2, 256);
+    if (blk.set_direct(ms_direct_next(A, k, ms_edges(hcnt.data(), dlev), dlev, blk.direct))) {
+      blk.at_level(ma, w, dlev);
+      launch_msbfs_form(ma, stream);
+    }
+    chunk = first_batch && !blk.direct ? 2 : 2 * chunk;
+    chunk = std::min(chunk, std::max(12, (int)std::sqrt(16.0 * (double)dlev)));
     first_batch = false;
   }
   const int iters = hc.nlev;
@@ -1579,6 +1667,7 @@ struct grb_msbfs_session_s {
   grb_matrix A = nullptr;
   MsWs w{};
   MsbfsArgs ma;
+  MsBlocks blk;
   int64_t d = 0;  // levels run so far
   int grid = 0;
   std::vector<uint64_t> busy;  // queries joined and not yet retired
@@ -1587,19 +1676,10 @@ struct grb_msbfs_session_s {
 namespace {
 
 void session_level(grb_msbfs_session_s &ss, int64_t dd) {
-  const int i = (int)(dd % 3), j = (int)((dd + 1) % 3), q = (int)((dd + 2) % 3);
   MsbfsArgs &ma = ss.ma;
-  ma.F = ss.w.F[dd & 1];
-  ma.Fn = ss.w.F[(dd + 1) & 1];
-  ma.act = ss.w.act[i];
-  ma.actn = ss.w.act[j];
-  ma.actc = ss.w.act[q];
-  ma.cnt_cur = ss.w.cnt + (size_t)i * 2 * kCntStripes;
-  ma.cnt_nxt = ss.w.cnt + (size_t)j * 2 * kCntStripes;
-  ma.cnt_clr = ss.w.cnt + (size_t)q * 2 * kCntStripes;
-  ma.alive_nxt = ss.w.alive + (size_t)j * ma.W;
-  ma.alive_clr = ss.w.alive + (size_t)q * ma.W;
-  ma.d = (int32_t)std::min<int64_t>(dd, INT32_MAX);
+  ss.blk.at_level(ma, ss.w, dd);
+  ma.alive_nxt = ss.w.alive + (size_t)((dd + 1) % 3) * ma.W;
+  ma.alive_clr = ss.w.alive + (size_t)((dd + 2) % 3) * ma.W;
 }
 
 }  // namespace
@@ -1656,7 +1736,6 @@ grb_info grb_msbfs_session_create(grb_msbfs_session *ss, grb_matrix A, int32_t k
   ma.can_pull = can_pull;
   ma.levels = levels;
   ma.V = w.V;
-  ma.S = w.S;
   ma.cnt_base = w.cnt;
   ma.ctrl = w.ctrl;
   ma.stats = nullptr;
@@ -1664,6 +1743,7 @@ grb_info grb_msbfs_session_create(grb_msbfs_session *ss, grb_matrix A, int32_t k
   ma.denom = desc.switch_denominator;
   ma.forced = desc.direction;
   ma.start = w.start;
+  x->blk = MsBlocks(w, A->a.max_deg <= kCoopMaxDeg);
   session_level(*x, 0);
   launch_msbfs_session_init(ma, w.act[1], w.act[2], w.alive, stream);
   if ((info = check_launch()) != GRB_SUCCESS) {
@@ -1720,16 +1800,24 @@ grb_info grb_msbfs_session_step(grb_msbfs_session ss, int32_t max_levels, uint64
     for (; ran < max_levels; ++ran, ++ss->d) {
       session_level(*ss, ss->d);
       launch_msbfs_level(ss->ma, ss->grid, stream);
+      ss->blk.advance();
     }
   }
   grb_info info = check_launch();
   if (info != GRB_SUCCESS) return info;
-  std::vector<uint64_t> alive((size_t)W, 0ull);
-  if (!read_back({{alive.data(), ss->w.alive + (size_t)(ss->d % 3) * W, (size_t)W * 8}}, s))
-    return GRB_PANIC;
+  // the counters and the "has a frontier bit" words, in one copy
+  const size_t nc = (size_t)((ss->w.alive - ss->w.cnt) + 3 * W);
+  std::vector<unsigned long long> rb(nc, 0ull);
+  if (!read_back({{rb.data(), ss->w.cnt, nc * sizeof(unsigned long long)}}, s)) return GRB_PANIC;
+  const unsigned long long *alive = rb.data() + (nc - 3 * (size_t)W) + (size_t)(ss->d % 3) * W;
+  if (ss->blk.set_direct(ms_direct_session(ss->A, W, ms_edges(rb.data(), ss->d), ss->blk.direct))) {
+    session_level(*ss, ss->d);
+    launch_msbfs_form(ss->ma, stream);
+    if ((info = check_launch()) != GRB_SUCCESS) return info;
+  }
   for (int j = 0; j < W; ++j) {
-    done[j] = ss->busy[(size_t)j] & ~alive[(size_t)j];
-    ss->busy[(size_t)j] &= alive[(size_t)j];
+    done[j] = ss->busy[(size_t)j] & ~alive[j];
+    ss->busy[(size_t)j] &= alive[j];
   }
   if (levels_run) *levels_run = ran;
   return GRB_SUCCESS;

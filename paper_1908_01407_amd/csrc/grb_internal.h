@@ -412,8 +412,10 @@ struct MsbfsArgs {
   bool can_pull = true;
   int32_t *levels = nullptr;  // n x k, vertex-major
   uint64_t *V = nullptr;      // visited, n x W
-  uint64_t *S = nullptr;      // visited or found by the running level; V between levels
-  uint64_t *F = nullptr, *Fn = nullptr;                       // frontier blocks
+  // two-kernel form: S, visited or found by the running level (V between levels);
+  // one-kernel form: S null, Fc in its place
+  uint64_t *S = nullptr;
+  uint64_t *F = nullptr, *Fn = nullptr, *Fc = nullptr;        // frontier blocks
   uint64_t *act = nullptr, *actn = nullptr, *actc = nullptr;  // vertex has a frontier bit
   unsigned long long *cnt_cur = nullptr, *cnt_nxt = nullptr, *cnt_clr = nullptr, *cnt_base = nullptr;
   Ctrl *ctrl = nullptr;
@@ -429,6 +431,8 @@ struct MsbfsArgs {
 void launch_msbfs_start(const MsbfsArgs &a, const int32_t *sources, uint64_t *act1, uint64_t *act2,
                         void *stream);
 void launch_msbfs_level(const MsbfsArgs &a, int grid_x, void *stream);
+// after a change of form, before the next level: fills the block that changed roles
+void launch_msbfs_form(const MsbfsArgs &a, void *stream);
 // sessions: every query idle (its bits set in V and S), blocks and counters cleared
 void launch_msbfs_session_init(const MsbfsArgs &a, uint64_t *act1, uint64_t *act2,
                                unsigned long long *alive3, void *stream);

@@ -5,8 +5,9 @@
 //
 // F (frontier), V (visited before this level) and S (seen: V and what the
 // running level has found) are n x W blocks of uint64 words, vertex major:
-// word j of vertex v holds queries 64j .. 64j+63.  A level is two kernels.
-// The expansion, over a 2-D grid (blockIdx.y picks a tile of kt query words),
+// word j of vertex v holds queries 64j .. 64j+63.  A level is two kernels, or
+// one where frontiers are small (the host chooses per batch of levels).
+// Two kernels: the expansion, over a 2-D grid (blockIdx.y picks a tile of kt query words),
 // only adds to S and to the bitmap of the vertices it found:
 // * pull: each wave owns 64 consecutive vertices; for the tile's words of
 //   every vertex with an unvisited query, the in-edges are streamed as one
@@ -33,6 +34,12 @@
 // 44 us.  Of the 785 us the stream's bookkeeping and loads are 180, the
 // gather 250 and the atomics 280; more workgroups do not change it, and
 // reading V and the next frontier in place of S, two gathers, took 900.
+//
+// One kernel: each claim is an atomicOr on the visited word itself, whose winner
+// writes the levels, sets the next frontier and counts.  A level of few vertices
+// is mostly launches, and the commit's walk over the found vertices adds to it:
+// 1000 x 1000 grid, 64 queries, 20 us a level in one kernel and 30 in two; 256
+// queries 49 and 76.  The pull and the push's pieces are the same in both.
 #include <hip/hip_runtime.h>
 
 #include "grb_device.h"
@@ -40,10 +47,6 @@
 
 namespace grb {
 namespace {
-
-__device__ __forceinline__ uint64_t wave_seg_or(uint64_t x, int row) {
-  return wave_seg_scan(x, row, (uint64_t)0, OpOr());
-}
 
 // valid queries of word j (the last word may be partial)
 __device__ __forceinline__ uint64_t qmask(const MsbfsArgs &a, int j) {
@@ -87,6 +90,54 @@ __device__ __forceinline__ void claim_batch(const MsbfsArgs &a, const int (&tv)[
   }
 }
 
+// ---- levels in one kernel (small frontiers) ---------------------------------------
+// What a wave of the one-kernel form has found: (vertex, query) pairs, out-edges of
+// (vertex, query word) pairs; s_alive: the workgroup's "has a frontier bit" words
+// (session; indexed by word - first word of the pass).
+struct MsFound {
+  int64_t pairs = 0, edges = 0;
+  unsigned long long *s_alive = nullptr;
+};
+
+// Writes level d + 1 (in a session relative to the query's start level) for the
+// new bits of (v, word j) held by each lane: the wave visits every lane with new
+// bits and stores its 64 levels with one coalesced store.
+__device__ __forceinline__ void write_levels(const MsbfsArgs &a, int64_t v, int j, uint64_t newbits,
+                                             MsFound &fo) {
+  const int ln = threadIdx.x & 63;
+  const int j0 = blockIdx.y * a.kt;
+  for (uint64_t todo = __ballot(newbits != 0ull); todo; todo &= todo - 1) {
+    const int r = __ffsll((unsigned long long)todo) - 1;
+    const int64_t rv = __shfl(v, r);
+    const int rj = __shfl(j, r);
+    const uint64_t nb = __shfl(newbits, r);
+    const int64_t q = (int64_t)rj * 64 + ln;
+    if (((nb >> ln) & 1ull) && q < a.k)
+      a.levels[rv * a.k + q] = a.d + 1 - (a.start ? a.start[q] : 0);
+    if (a.alive_nxt && ln == 0) atomicOr(&fo.s_alive[rj - j0], (unsigned long long)nb);
+  }
+}
+
+// Claims the query bits of vertex v, word j, for the next level: the first
+// atomicOr on the visited word that sets a bit wins it.
+__device__ __forceinline__ uint64_t claim_bits(const MsbfsArgs &a, int64_t v, int j, uint64_t bits,
+                                               MsFound &fo) {
+  if (bits == 0ull) return 0ull;
+  uint64_t *vw = &a.V[v * a.W + j];
+  bits &= ~*vw;  // plain read: a filter, the atomic decides
+  if (bits == 0ull) return 0ull;
+  const uint64_t old = atomicOr((unsigned long long *)vw, (unsigned long long)bits);
+  const uint64_t nb = bits & ~old;
+  if (nb) {
+    const uint64_t pf = atomicOr((unsigned long long *)&a.Fn[v * a.W + j], (unsigned long long)nb);
+    if (pf == 0ull) fo.edges += a.push.rp[v + 1] - a.push.rp[v];
+    fo.pairs += __popcll(nb);
+    atomicOr((unsigned long long *)&a.actn[v >> 6], 1ull << (v & 63));
+  }
+  return nb;
+}
+
+// ---- both forms ---------------------------------------------------------------------
 // Pull over the pass's query words j0 .. j0 + nj - 1 (nj <= L <= 8): an edge
 // occupies L consecutive lanes, one per query word, so the frontier words of
 // a neighbour (consecutive in the vertex-major block) come in one coalesced
@@ -94,9 +145,9 @@ __device__ __forceinline__ void claim_batch(const MsbfsArgs &a, const int (&tv)[
 // (lanes of the row layout, 64 per bitmap word) keep their unvisited and
 // found bits per word and stop once every unvisited query of the pass is
 // found.  Rows longer than kPushSplit are left to the pieces below, which
-// claim with atomics like push.
-template <int L>
-__device__ void ms_pull_rows(const MsbfsArgs &a, int *mark) {
+// claim with atomics like push.  DIRECT: the one-kernel form.
+template <int L, bool DIRECT>
+__device__ void ms_pull_rows(const MsbfsArgs &a, int *mark, MsFound &fo) {
   constexpr int S = 64 / L;
   const int ln = threadIdx.x & 63;
   const int sl = ln / L, jl = ln % L;
@@ -194,9 +245,17 @@ __device__ void ms_pull_rows(const MsbfsArgs &a, int *mark) {
       for (int q = 0; q < L; ++q) {
         const uint64_t nb = acc[q] & need[q];
         if (nb) {
-          a.S[v * a.W + j0 + q] = ~(need[q] & ~nb);  // V | nb
+          if constexpr (DIRECT) {
+            a.V[v * a.W + j0 + q] |= nb;
+            a.Fn[v * a.W + j0 + q] = nb;
+            fo.pairs += __popcll(nb);
+            fo.edges += a.push.rp[v + 1] - a.push.rp[v];
+          } else {
+            a.S[v * a.W + j0 + q] = ~(need[q] & ~nb);  // V | nb
+          }
           anyb = true;
         }
+        if constexpr (DIRECT) write_levels(a, v, j0 + q, nb, fo);
       }
       const uint64_t ab = __ballot(anyb);
       if (ab && ln == 0) atomicOr((unsigned long long *)&a.actn[w], (unsigned long long)ab);
@@ -226,18 +285,97 @@ __device__ void ms_pull_rows(const MsbfsArgs &a, int *mark) {
     // OR over the slots (lanes L apart), into the words by lanes 0 .. L-1
 #pragma unroll
     for (int off = L; off < 64; off <<= 1) acc |= __shfl_xor(acc, off);
-    const uint64_t nb = sl == 0 && jv ? acc & need : 0ull;
-    if (nb) atomicOr((unsigned long long *)&a.S[(int64_t)r * a.W + j0 + jl], (unsigned long long)nb);
-    if (__ballot(nb != 0ull) && ln == 0)
-      atomicOr((unsigned long long *)&a.actn[r >> 6], 1ull << (r & 63));
+    uint64_t nb = sl == 0 && jv ? acc & need : 0ull;
+    if constexpr (DIRECT) {
+      nb = claim_bits(a, r, j0 + jl, nb, fo);
+      write_levels(a, r, j0 + jl, nb, fo);
+    } else {
+      if (nb)
+        atomicOr((unsigned long long *)&a.S[(int64_t)r * a.W + j0 + jl], (unsigned long long)nb);
+      if (__ballot(nb != 0ull) && ln == 0)
+        atomicOr((unsigned long long *)&a.actn[r >> 6], 1ull << (r & 63));
+    }
   }
 }
 
-__device__ void ms_pull(const MsbfsArgs &a, int *mark) {
-  if (a.kt <= 1) ms_pull_rows<1>(a, mark);
-  else if (a.kt <= 2) ms_pull_rows<2>(a, mark);
-  else if (a.kt <= 4) ms_pull_rows<4>(a, mark);
-  else ms_pull_rows<8>(a, mark);
+template <bool DIRECT>
+__device__ void ms_pull(const MsbfsArgs &a, int *mark, MsFound &fo) {
+  if (a.kt <= 1) ms_pull_rows<1, DIRECT>(a, mark, fo);
+  else if (a.kt <= 2) ms_pull_rows<2, DIRECT>(a, mark, fo);
+  else if (a.kt <= 4) ms_pull_rows<4, DIRECT>(a, mark, fo);
+  else ms_pull_rows<8, DIRECT>(a, mark, fo);
+}
+
+// Push of the one-kernel form: a wave per word of active vertices, 64 edges a step.
+__device__ void ms_push_direct(const MsbfsArgs &a, int *mark, MsFound &fo) {
+  const int ln = threadIdx.x & 63;
+  const int64_t gw = (int64_t)blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6);
+  const int64_t nwaves = (int64_t)gridDim.x * kWavesPerBlock;
+  const int32_t *rp = a.push.rp, *ci = a.push.ci;
+  const int j0 = blockIdx.y * a.kt;
+  const int nj = min(a.kt, a.W - j0);
+  for (int64_t w = gw; w < a.nw; w += nwaves) {
+    const uint64_t aw = a.act[w];
+    if (aw == 0ull) continue;
+    const int64_t u = w * 64 + ln;
+    int rs = 0, re = 0;
+    if ((aw >> ln) & 1ull) {
+      rs = rp[u];
+      re = rp[u + 1];
+      if (re - rs > kPushSplit) re = rs;  // long rows: static pieces below
+    }
+    for (int j = j0; j < j0 + nj; ++j) {
+      const uint64_t fu = (re > rs) ? a.F[u * a.W + j] : 0ull;
+      int cur = rs;
+      const int end = fu ? re : rs;
+      for (;;) {
+        const int len = end - cur;
+        const int incl = wave_incl_scan(len);
+        const int total = lane_last(incl);
+        if (total == 0) break;
+        const int excl = incl - len;
+        const bool starts = len > 0 && excl < 64;
+        const int r = slot_rows(mark, starts, excl);
+        const int rcur = __shfl(cur, r), rexcl = __shfl(excl, r);
+        const uint64_t rf = __shfl(fu, r);
+        int64_t tv = -1;
+        uint64_t nb = 0ull;
+        if (ln < total) {
+          tv = ci[rcur + (ln - rexcl)];
+          nb = claim_bits(a, tv, j, rf, fo);
+        }
+        write_levels(a, tv, j, nb, fo);
+        if (starts) cur += min(incl, 64) - excl;
+      }
+    }
+  }
+  for (int64_t hb = gw; hb < a.push.nsplit; hb += 64 * nwaves) {
+    const int64_t h = hb + (int64_t)ln * nwaves;
+    int u = -1, b = 0, e = 0;
+    if (h < a.push.nsplit) {
+      u = a.push.split[2 * h];
+      b = a.push.split[2 * h + 1];
+      if (bit_of(a.act, u)) e = min(b + kPushSplit, rp[u + 1]);
+      else u = -1;
+    }
+    for (uint64_t act = __ballot(u >= 0); act; act &= act - 1) {
+      const int kk = __ffsll((unsigned long long)act) - 1;
+      const int pu = __shfl(u, kk), pb = __shfl(b, kk), pe = __shfl(e, kk);
+      for (int j = j0; j < j0 + nj; ++j) {
+        const uint64_t fu = a.F[(int64_t)pu * a.W + j];
+        if (fu == 0ull) continue;
+        for (int base = pb; base < pe; base += 64) {
+          int64_t tv = -1;
+          uint64_t nb = 0ull;
+          if (base + ln < pe) {
+            tv = ci[base + ln];
+            nb = claim_bits(a, tv, j, fu, fo);
+          }
+          write_levels(a, tv, j, nb, fo);
+        }
+      }
+    }
+  }
 }
 
 // Active vertices are dealt out in groups of 16, a quarter of a bitmap word:
@@ -335,9 +473,36 @@ __device__ void ms_push(const MsbfsArgs &a, int *mark) {
   }
 }
 
+// Adds a workgroup's (pairs, edges), already summed over each wave, to the next
+// level's counters.
+__device__ __forceinline__ void ms_count(const MsbfsArgs &a, int64_t (*s_red)[2], int64_t pairs,
+                                         int64_t edges) {
+  if ((threadIdx.x & 63) == 0) {
+    s_red[threadIdx.x >> 6][0] = pairs;
+    s_red[threadIdx.x >> 6][1] = edges;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    int64_t c = 0, e = 0;
+    for (int i = 0; i < kWavesPerBlock; ++i) {
+      c += s_red[i][0];
+      e += s_red[i][1];
+    }
+    if (c) {
+      const int t = (blockIdx.x + blockIdx.y * 7) % kCntStripes;
+      atomicAdd((unsigned long long *)&a.cnt_nxt[2 * t], (unsigned long long)c);
+      atomicAdd((unsigned long long *)&a.cnt_nxt[2 * t + 1], (unsigned long long)e);
+    }
+  }
+}
+
+template <bool DIRECT>
 __global__ __launch_bounds__(kBlock) void k_ms_level(MsbfsArgs a) {
   __shared__ int s_mark[kWavesPerBlock][64];
   __shared__ int64_t s_act, s_edges;
+  __shared__ int64_t s_red[DIRECT ? kWavesPerBlock : 1][2];
+  __shared__ unsigned long long s_alive[DIRECT ? kMsMaxWordsPerPass : 1];
+  if (DIRECT && threadIdx.x < kMsMaxWordsPerPass) s_alive[threadIdx.x] = 0ull;
   const bool leader = blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0;
   if (threadIdx.x == 0) {
     int64_t c = 0, e = 0;
@@ -362,10 +527,11 @@ __global__ __launch_bounds__(kBlock) void k_ms_level(MsbfsArgs a) {
     }
   }
   __syncthreads();
-  // clear the block that the commit writes the next frontier into; it holds
-  // the previous level's, so only rows marked in that level's bitmap can be
-  // non-zero: tile 0 clears all words of those rows, then the bitmap word (the
-  // same thread reads and clears it, no other tile reads it)
+  // clear the previous level's frontier block (the commit writes the next
+  // frontier into it; the one-kernel form uses it a level later); only rows
+  // marked in that level's bitmap can be non-zero: tile 0 clears all words of
+  // those rows, then the bitmap word (the same thread reads and clears it, no
+  // other tile reads it)
   if (blockIdx.y == 0) {
     for (int64_t w = (int64_t)blockIdx.x * kBlock + threadIdx.x; w < a.nw;
          w += (int64_t)gridDim.x * kBlock) {
@@ -374,15 +540,30 @@ __global__ __launch_bounds__(kBlock) void k_ms_level(MsbfsArgs a) {
       while (aw) {
         const int b = __ffsll((unsigned long long)aw) - 1;
         aw &= aw - 1;
-        uint64_t *row = a.Fn + (w * 64 + b) * a.W;
+        uint64_t *row = (DIRECT ? a.Fc : a.Fn) + (w * 64 + b) * a.W;
         for (int j = 0; j < a.W; ++j) row[j] = 0ull;
       }
       a.actc[w] = 0ull;
     }
   }
   if (s_act == 0) return;
-  if (ms_decide(a, s_act, s_edges) == GRB_DIR_PUSH) ms_push(a, s_mark[threadIdx.x >> 6]);
-  else ms_pull(a, s_mark[threadIdx.x >> 6]);
+  int *mark = s_mark[threadIdx.x >> 6];
+  MsFound fo;
+  fo.s_alive = s_alive;
+  const bool push = ms_decide(a, s_act, s_edges) == GRB_DIR_PUSH;
+  if constexpr (DIRECT) {
+    if (push) ms_push_direct(a, mark, fo);
+    else ms_pull<true>(a, mark, fo);
+    ms_count(a, s_red, wave_sum64(fo.pairs), wave_sum64(fo.edges));  // (syncs)
+    if (a.alive_nxt && threadIdx.x < kMsMaxWordsPerPass) {
+      const int j = blockIdx.y * a.kt + threadIdx.x;
+      const unsigned long long x = s_alive[threadIdx.x];
+      if (x && j < a.W) atomicOr(&a.alive_nxt[j], x);
+    }
+  } else {
+    if (push) ms_push(a, mark);
+    else ms_pull<false>(a, mark, fo);
+  }
 }
 
 // The vertices the level found, a wave per word of their bitmap (dealt out
@@ -430,24 +611,17 @@ __global__ __launch_bounds__(kBlock) void k_ms_commit(MsbfsArgs a) {
       }
     }
   }
-  pairs = wave_sum64(pairs);
-  edges = wave_sum64(edges);
-  if (ln == 0) {
-    s_red[threadIdx.x >> 6][0] = pairs;
-    s_red[threadIdx.x >> 6][1] = edges;
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    int64_t c = 0, e = 0;
-    for (int i = 0; i < kWavesPerBlock; ++i) {
-      c += s_red[i][0];
-      e += s_red[i][1];
-    }
-    if (c) {
-      const int t = blockIdx.x % kCntStripes;
-      atomicAdd((unsigned long long *)&a.cnt_nxt[2 * t], (unsigned long long)c);
-      atomicAdd((unsigned long long *)&a.cnt_nxt[2 * t + 1], (unsigned long long)e);
-    }
+  ms_count(a, s_red, wave_sum64(pairs), wave_sum64(edges));
+}
+
+// Between levels: S from V for the two-kernel form, or the block cleared (Fn) for
+// the one-kernel form.
+__global__ void k_ms_form(MsbfsArgs a, bool direct) {
+  const int64_t nb = a.n * (int64_t)a.W;
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < nb;
+       i += (int64_t)gridDim.x * blockDim.x) {
+    if (direct) a.Fn[i] = 0ull;
+    else a.S[i] = a.V[i];
   }
 }
 
@@ -461,7 +635,8 @@ __global__ void k_ms_start(MsbfsArgs a, const int32_t *sources, uint64_t *act1, 
   for (int64_t i = gt; i < nb; i += nt) {
     const uint64_t v = ~qmask(a, (int)(i % a.W));  // queries beyond k count as visited
     a.V[i] = v;
-    a.S[i] = v;
+    if (a.S) a.S[i] = v;
+    else a.Fc[i] = 0ull;
     a.F[i] = 0ull;
     a.Fn[i] = 0ull;
   }
@@ -488,7 +663,8 @@ __global__ void k_ms_session_init(MsbfsArgs a, uint64_t *act1, uint64_t *act2,
   const int64_t nb = a.n * (int64_t)a.W;
   for (int64_t i = gt; i < nb; i += nt) {
     a.V[i] = ~0ull;
-    a.S[i] = ~0ull;
+    if (a.S) a.S[i] = ~0ull;
+    else a.Fc[i] = 0ull;
     a.F[i] = 0ull;
     a.Fn[i] = 0ull;
   }
@@ -505,7 +681,7 @@ __global__ void k_ms_session_init(MsbfsArgs a, uint64_t *act1, uint64_t *act2,
   }
 }
 
-// Joining queries: their bits cleared in every vertex's V and S words (clr[j]
+// Joining queries: their bits cleared in every vertex's V (and S) words (clr[j]
 // holds the joining queries of word j)
 __global__ void k_ms_session_clear(MsbfsArgs a, const uint64_t *clr) {
   const int64_t nb = a.n * (int64_t)a.W;
@@ -515,7 +691,7 @@ __global__ void k_ms_session_clear(MsbfsArgs a, const uint64_t *clr) {
     if (m) {
       const uint64_t v = a.V[i] & ~m;
       a.V[i] = v;
-      a.S[i] = v;
+      if (a.S) a.S[i] = v;
     }
   }
 }
@@ -532,7 +708,7 @@ __global__ void k_ms_session_sources(MsbfsArgs a, const int32_t *lanes, const in
   const int j = (int)(q >> 6);
   const uint64_t bit = 1ull << (q & 63);
   atomicOr((unsigned long long *)&a.V[s * a.W + j], (unsigned long long)bit);
-  atomicOr((unsigned long long *)&a.S[s * a.W + j], (unsigned long long)bit);
+  if (a.S) atomicOr((unsigned long long *)&a.S[s * a.W + j], (unsigned long long)bit);
   const uint64_t pf = atomicOr((unsigned long long *)&a.F[s * a.W + j], (unsigned long long)bit);
   atomicOr((unsigned long long *)&a.act[s >> 6], 1ull << (s & 63));
   a.levels[s * a.k + q] = 0;
@@ -570,7 +746,7 @@ __global__ void k_ms_sources(MsbfsArgs a, const int32_t *sources) {
   const int j = (int)(q >> 6);
   const uint64_t bit = 1ull << (q & 63);
   atomicOr((unsigned long long *)&a.V[s * a.W + j], (unsigned long long)bit);
-  atomicOr((unsigned long long *)&a.S[s * a.W + j], (unsigned long long)bit);
+  if (a.S) atomicOr((unsigned long long *)&a.S[s * a.W + j], (unsigned long long)bit);
   const uint64_t pf = atomicOr((unsigned long long *)&a.F[s * a.W + j], (unsigned long long)bit);
   atomicOr((unsigned long long *)&a.act[s >> 6], 1ull << (s & 63));
   a.levels[s * a.k + q] = 0;
@@ -615,9 +791,17 @@ void launch_msbfs_session_extract(const MsbfsArgs &a, const int32_t *lanes, int3
                      lanes, count, out);
 }
 
+void launch_msbfs_form(const MsbfsArgs &a, void *stream) {
+  hipLaunchKernelGGL(k_ms_form, dim3(2048), dim3(256), 0, (hipStream_t)stream, a, a.S == nullptr);
+}
+
 void launch_msbfs_level(const MsbfsArgs &a, int grid_x, void *stream) {
   const int tiles = (a.W + a.kt - 1) / a.kt;
-  hipLaunchKernelGGL(k_ms_level, dim3(grid_x, tiles), dim3(kBlock), 0, (hipStream_t)stream, a);
+  if (!a.S) {
+    hipLaunchKernelGGL(k_ms_level<true>, dim3(grid_x, tiles), dim3(kBlock), 0, (hipStream_t)stream, a);
+    return;
+  }
+  hipLaunchKernelGGL(k_ms_level<false>, dim3(grid_x, tiles), dim3(kBlock), 0, (hipStream_t)stream, a);
   int64_t g = (a.nw + kWavesPerBlock - 1) / kWavesPerBlock;
   g = g < 1 ? 1 : (g > 2048 ? 2048 : g);
   hipLaunchKernelGGL(k_ms_commit, dim3((unsigned)g), dim3(kBlock), 0, (hipStream_t)stream, a);
