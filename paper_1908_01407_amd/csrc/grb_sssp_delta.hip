@@ -428,7 +428,6 @@ __device__ __forceinline__ void list_add(DeltaShared &sh, uint64_t *pend, int lo
     } else {
       const int c = lo + l[k];
       atomicOr((unsigned long long *)&pend[c >> 6], 1ull << (c & 63));
-      __builtin_amdgcn_s_waitcnt(0);  // the next round may read it
       sh.ovf = 1;
     }
   }
@@ -564,11 +563,18 @@ __global__ __launch_bounds__(kOwnThreads) void k_sssp_delta_own(SsspArgs a, int3
   uint64_t *put1 = put + (int64_t)G * G * 2, *get1 = get + (int64_t)G * G * 2;
   uint32_t tag = delta_tag(0);
   int cur = 0, d = 0, slow = 0;  // near list, round, second exchanges so far
-  bool spill = false, over = false;  // over: near vertices beyond the list's end
+  bool spill = false, over = false;  // over: this round's near list is not whole
   for (;;) {
     const int nxt = cur ^ 1;
     const bool rec_round = d < kStatsCap;
-    if (et >= 0) {
+    if (over) {
+      // The messages of the last round left near vertices beyond the list's end:
+      // this workgroup's part of the round goes to the hand-over as it is.
+      for (int i = tid; i < n; i += kOwnThreads) {
+        const int c = lo + sh.near[cur][i];
+        atomicOr((unsigned long long *)&pend[c >> 6], 1ull << (c & 63));
+      }
+    } else if (et >= 0) {
       int esum = 0;
       for (int i0 = et & ~63; i0 < n; i0 += T) {
         const int i = i0 + ln;
@@ -609,35 +615,6 @@ __global__ __launch_bounds__(kOwnThreads) void k_sssp_delta_own(SsspArgs a, int3
             nd[q] = dv + (q0 + q < dg ? wt[rs + q0 + q] : 0.0f);
           }
           delta_expand(a, sh, pend, lo, nv, w, limit, &sh.cnt[nxt], sh.near[nxt], box, c, nd);
-        }
-      }
-      if (over) {
-        // Near vertices that the messages of the last round left beyond the
-        // list's end: the loop hands over after this round, which still takes
-        // them (a round cap counts it).  They are marked pending; marks lie
-        // below nv.
-        for (int i0 = et & ~63; i0 < nv; i0 += T) {
-          const int l = i0 + ln;
-          int rs = 0, dg = 0;
-          float dv = 0.0f;
-          if ((load_relaxed_u64(&pend[(lo + l) >> 6]) >> ln) & 1ull) {
-            dv = *(volatile float *)&sh.dist[l];
-            if (dv < limit) {
-              rs = rp[lo + l];
-              dg = rp[lo + l + 1] - rs;
-            }
-          }
-          esum += dg;
-          for (int q0 = 0; __ballot(q0 < dg) != 0ull; q0 += 4) {
-            int c[4];
-            float nd[4];
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-              c[q] = q0 + q < dg ? ci[rs + q0 + q] : -1;
-              nd[q] = dv + (q0 + q < dg ? wt[rs + q0 + q] : 0.0f);
-            }
-            delta_expand(a, sh, pend, lo, nv, w, limit, &sh.cnt[nxt], sh.near[nxt], box, c, nd);
-          }
         }
       }
       if (rec_round) {
@@ -794,7 +771,6 @@ __global__ __launch_bounds__(kOwnThreads) void k_sssp_delta_own(SsspArgs a, int3
       __syncthreads();
     }
     n = min(sh.n_new, kNearCap);
-    over = sh.n_new > kNearCap;
     cur = nxt;
     {
       uint64_t *b = box, *p = put, *g = get;
@@ -808,6 +784,7 @@ __global__ __launch_bounds__(kOwnThreads) void k_sssp_delta_own(SsspArgs a, int3
       break;
     }
     if (d >= max_rounds) break;
+    over = sh.n_new > kNearCap;
     if (state != kDeltaAdvance) continue;
     // No near vertex was left anywhere before the messages of this round,
     // and none of those was below the limit: the next bucket.  A full list
@@ -920,7 +897,8 @@ __global__ __launch_bounds__(kOwnThreads) void k_sssp_delta_own(SsspArgs a, int3
     }
   }
   if (tid == 0) {
-    atomicMin(&a.ctrl->small_levels, d);
+    // (a round left to the hand-over is not one of the loop's)
+    atomicMin(&a.ctrl->small_levels, over ? d - 1 : d);
     if (spill) atomicOr(&a.ctrl->spilled, 1);
   }
 }
