@@ -901,8 +901,14 @@ __global__ __launch_bounds__(kBlock) void k_bfs_start(BfsArgs a, int32_t source,
 // scans and 64-bit arithmetic off the usual path: slots come from ballots,
 // and the totals are judged by ballots against a per-workgroup share of the
 // bounds before any sum is taken.
+// VIS: vertices whose visited bits it holds.  Beside other streams' kernels a
+// workgroup becomes resident the later the more LDS it asks for, so small graphs
+// have a form of 45 KB (three PageRanks of 64M entries, 700 x 700 grid, 8
+// workgroups: 18 to 97 ms with 135 KB each, 5 to 58 so; alone 2.50 ms both).  A
+// form for 377,000 vertices made the 3000 x 3000 grid's levels 1.3 % longer.
+template <int VIS>
 struct OwnShared {
-  uint32_t vis[kOwnVertices / 32];
+  uint32_t vis[VIS / 32];
   int q[2][kOwnQueue];
   int cnt[2];              // entries found by the expansion into each queue
   int out[kOwnMaxGroups];  // targets sent to each workgroup in this level
@@ -945,8 +951,8 @@ static_assert(kOwnVertices <= 1 << 20 && kOwnQueue < 1 << 13 && kOwnCapMax < 256
 // vertices past its end go straight into the next frontier's bitmap with
 // their level.  One LDS atomic per wave: one per lane serialises on the
 // counter (1.8 instead of 0.9 us per level).
-template <int K>
-__device__ __forceinline__ void own_queue(const BfsArgs &a, OwnShared &sh, int *cnt, int *q,
+template <int K, class SH>
+__device__ __forceinline__ void own_queue(const BfsArgs &a, SH &sh, int *cnt, int *q,
                                           uint64_t *fn, int level, const int (&c)[K],
                                           const bool (&won)[K]) {
   uint64_t b[K];
@@ -980,7 +986,8 @@ __device__ __forceinline__ void own_queue(const BfsArgs &a, OwnShared &sh, int *
 // Claims the owned targets among c[0..4) (all four LDS atomics are issued
 // before a result is used), sends the others to their owners and queues the
 // claims won.
-__device__ __forceinline__ void own_expand(const BfsArgs &a, OwnShared &sh, int lo, int nv, int w,
+template <class SH>
+__device__ __forceinline__ void own_expand(const BfsArgs &a, SH &sh, int lo, int nv, int w,
                                            int *cnt, int *q, uint64_t *fn, int32_t *box, int level,
                                            const int (&c)[4]) {
   uint32_t old[4];
@@ -1036,16 +1043,16 @@ __device__ __forceinline__ void own_expand(const BfsArgs &a, OwnShared &sh, int 
 // corner: 16.3 ms, 2.7 us a level (from inside 2.2); a loop over shared queues
 // in device memory (claims by device atomics, a counter barrier) 36.2 ms, 6.0
 // us a level.
-// R: polled records per lane of wave 0 (G <= 64 R).  `most`: a frontier of at
+// R: polled records per lane of wave 0 (G <= 64 R); VIS: as above.  `most`: a frontier of at
 // most this many vertices is within the edge limit and one the rule pushes;
 // `share`: a level in which no workgroup found and sent more than this keeps
 // that bound and every queue.
-template <int R>
+template <int R, int VIS>
 __global__ __launch_bounds__(kOwnThreads) void k_bfs_own(BfsArgs a, int32_t source,
                                                          int max_levels, uint64_t wait_ticks,
                                                          int most, int share, uint64_t *F0,
                                                          uint64_t *F1, uint64_t *F2) {
-  __shared__ OwnShared sh;
+  __shared__ OwnShared<VIS> sh;
   constexpr int T = kOwnThreads - 64;  // threads that take queue entries (waves 1, 2, ...)
   const int tid = threadIdx.x, ln = tid & 63;
   const int et = tid - 64;  // this thread's first entry (wave 0 takes none)
@@ -1153,7 +1160,7 @@ __global__ __launch_bounds__(kOwnThreads) void k_bfs_own(BfsArgs a, int32_t sour
           }
           if (__ballot(!ok) == 0ull) break;
           if (t0 == 0) t0 = wall_clock64();
-          if (wall_clock64() - t0 >= wait_ticks) {
+          if (wall_clock64() - t0 >= (d == 0 ? kCoopFirstWait : 1) * wait_ticks) {
             state = kOwnGaveUp;
             break;
           }
@@ -1512,12 +1519,11 @@ void launch_bfs_own(const BfsArgs &a, int32_t source, int64_t max_levels, uint64
   }
   const int cap = (int)std::min<int64_t>(max_levels, kOwnMaxLevels + 1);
   const int most = (int)m, share = (int)std::min<int64_t>(m, kOwnQueue) / a.own.groups;
-  if (a.own.groups <= 64)
-    hipLaunchKernelGGL(k_bfs_own<1>, dim3(a.own.groups), dim3(kOwnThreads), 0, s, a, source,
-                       cap, wait_ticks, most, share, F[0], F[1], F[2]);
-  else
-    hipLaunchKernelGGL(k_bfs_own<4>, dim3(a.own.groups), dim3(kOwnThreads), 0, s, a, source,
-                       cap, wait_ticks, most, share, F[0], F[1], F[2]);
+  const auto kernel = a.own.groups > 64                ? k_bfs_own<4, kOwnVertices>
+                      : a.own.chunk <= kOwnVerticesLow ? k_bfs_own<1, kOwnVerticesLow>
+                                                       : k_bfs_own<1, kOwnVertices>;
+  hipLaunchKernelGGL(kernel, dim3(a.own.groups), dim3(kOwnThreads), 0, s, a, source, cap, wait_ticks,
+                     most, share, F[0], F[1], F[2]);
   hipLaunchKernelGGL(k_bfs_own_boxes, dim3(256), dim3(kBlock), 0, s, a, F[0], F[1], F[2]);
   int64_t g = (a.nw + kWavesPerBlock - 1) / kWavesPerBlock;
   g = g < 1 ? 1 : (g > kExpandGrid ? kExpandGrid : g);

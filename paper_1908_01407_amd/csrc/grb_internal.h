@@ -193,6 +193,14 @@ constexpr int kCoopEdges = 65536;  // a frontier with more edges goes to the lev
 // frontier then continues with the level kernel.  Nothing waits unboundedly,
 // also when some of the loop's workgroups are not resident.
 constexpr uint64_t kCoopWaitTicks = 100000;
+// The first exchange also waits until every workgroup is resident, and beside
+// other streams' kernels one that asks for much LDS and 8 wave slots may wait for
+// tens of ms.  It has to run in any case, also after the others gave up, and a
+// loop given up continues with a launch per level, each of which queues behind
+// those kernels: so 250 ms.  Beside two PageRanks (RMAT-22) BFS on the 3000 x 3000
+// grid took 26 or 780 ms when it waited 1 ms, 25 and 26 so; bucketed SSSP on 2003 x
+// 1009 vertices 296 and 583, then 22 and 24.
+constexpr int kCoopFirstWait = 250;
 
 // Bucket rounds of graphs too large for their distances to sit in LDS: a
 // pending queue in device memory, split evenly over the workgroups, one
@@ -219,6 +227,7 @@ constexpr int64_t kCoopMaxLevels = int64_t(1) << 24;  // arrivals stay below 2^3
 
 constexpr int kOwnThreads = 512;
 constexpr int kOwnVertices = 786432;  // BFS: visited bits a workgroup can hold (96 KB of LDS)
+constexpr int kOwnVerticesLow = 65536;  // ... in the form for smaller graphs (8 KB)
 constexpr int kOwnQueue = 4096;       // BFS: queue entries per workgroup (two queues: 32 KB)
 constexpr int kOwnMaxGroups = 256;
 constexpr int kDeltaCapMax = 8191;         // bucket rounds: messages from one workgroup to another per round

@@ -656,7 +656,7 @@ __global__ __launch_bounds__(kOwnThreads) void k_sssp_delta_own(SsspArgs a, int3
           }
           if (__ballot(!ok) == 0ull) break;
           if (t0 == 0) t0 = wall_clock64();
-          if (wall_clock64() - t0 >= wait_ticks) {
+          if (wall_clock64() - t0 >= (d == 0 ? kCoopFirstWait : 1) * wait_ticks) {
             gave_up = 1;
             state = kDeltaSpill;
             break;
