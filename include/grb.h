@@ -365,14 +365,15 @@ grb_info grb_vxm(grb_vector w, grb_vector mask, grb_binop accum, grb_semiring s,
  * keeps that depth (an atomic int, so concurrent calls on one matrix stay
  * safe; it affects speed only).  d->max_iter caps the levels (0 = none).
  * On graphs whose rows are short (at most 64 entries: road-like, high
- * diameter) and of at most 201 million vertices the levels run back to back
- * inside one kernel of 1 to 256 workgroups, which exchange their finds after
- * each level, while the frontier is small (a launch per level would
- * dominate); a frontier that outgrows its queues (4,096 vertices of one
- * workgroup, a few hundred found by one for another, or 65,536 edges), that
- * the switch rule would pull, or an exchange not reached by every workgroup
- * within 1 ms, continues with one kernel per level.  Results do not depend
- * on where that hand-over happens.
+ * diameter) the levels run back to back inside one kernel of 1 to 256
+ * workgroups, which exchange their finds after each level, while the frontier
+ * is small (a launch per level would dominate).  It continues with one kernel
+ * per level where the frontier outgrows the loop (4,096 vertices of one
+ * workgroup; 255 found by one for another with up to 16 workgroups, 92 with
+ * 32 and 64 with more; 65,536 edges), where the switch rule would pull, or
+ * where an exchange is not reached by every workgroup within 1 ms (the first
+ * one, which also waits until all are resident: 250 ms).  Results do not
+ * depend on where that hand-over happens.
  */
 grb_info grb_bfs(int32_t *levels, int32_t *parents, grb_matrix A, int32_t source,
                  const grb_descriptor *d, void *ws, size_t ws_bytes, void *stream);
@@ -405,11 +406,28 @@ grb_info grb_sssp(float *dist, grb_matrix A, int32_t source, const grb_descripto
                   void *ws, size_t ws_bytes, void *stream);
 
 /*
+ * Test hooks: grb_bfs and grb_sssp_delta whose loop on low-degree graphs has at
+ * least `groups` workgroups (1 to 256, bucketed SSSP 1 to 64, not fewer than
+ * the graph would get) or, BFS with in_device != 0, keeps its visited bits in
+ * device memory as it does above 201 million vertices (at most 64 workgroups).
+ * Results are unchanged.  Workspace: grb_loop_workspace_size for the same
+ * `groups` (op GRB_OP_BFS or GRB_OP_SSSP).  Other `groups`, or a bucketed
+ * search on more than 2.09 million vertices: GRB_INVALID_VALUE.
+ */
+grb_info grb_bfs_loop(int32_t *levels, int32_t *parents, grb_matrix A, int32_t source,
+                      int32_t groups, int32_t in_device, const grb_descriptor *d, void *ws,
+                      size_t ws_bytes, void *stream);
+grb_info grb_sssp_delta_loop(float *dist, grb_matrix A, int32_t source, float delta, int32_t groups,
+                             const grb_descriptor *d, void *ws, size_t ws_bytes, void *stream);
+grb_info grb_loop_workspace_size(grb_op op, grb_matrix A, int32_t groups, size_t *bytes);
+
+/*
  * SSSP from `source` (the computation of Section 7.2) in distance buckets
  * of width `delta` > 0: each round relaxes, by push, only the pending
- * vertices whose distance is below (B + 1) * delta for the current bucket
- * B; the others stay pending, and B moves to the nearest pending bucket
- * once none is left below the limit.  Reaches the same exact distances as
+ * vertices whose distance is below the end of the current bucket B, (B + 1)
+ * * delta (or, where that rounds to the smallest pending distance itself, the
+ * next float above it); the others stay pending, and B moves to the nearest
+ * pending bucket once none is left below the limit.  Reaches the same exact distances as
  * grb_sssp with far fewer relaxations on high-diameter graphs (the paper's
  * Bellman-Ford rounds relax a grid's edges over a hundred times each).
  * dist[n], A, workspace (GRB_OP_SSSP) and synchronisation as grb_sssp; the

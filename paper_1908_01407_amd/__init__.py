@@ -131,6 +131,10 @@ _SIGS = {
     "grb_msbfs_session_step": ([_p, _i32, _p, ctypes.POINTER(_i32), _p], _i32),
     "grb_msbfs_session_extract": ([_p, _p, _i32, _p, _p], _i32),
     "grb_msbfs_session_free": ([_PP], _i32),
+    "grb_bfs_loop": ([_p, _p, _p, _i32, _i32, _i32, ctypes.POINTER(Descriptor), _p, _sz, _p], _i32),
+    "grb_sssp_delta_loop": ([_p, _p, _i32, ctypes.c_float, _i32, ctypes.POINTER(Descriptor), _p,
+                             _sz, _p], _i32),
+    "grb_loop_workspace_size": ([_i32, _p, _i32, ctypes.POINTER(_sz)], _i32),
     "grb_bfs_noalloc": ([_p, _p, _p, _i32, ctypes.POINTER(Descriptor), _p], _i32),
     "grb_cc": ([_p, _p, ctypes.POINTER(_i32), ctypes.POINTER(Descriptor), _p, _sz, _p], _i32),
     "grb_pagerank": ([_p, _i32, _p, ctypes.c_double, _i32, ctypes.c_double,

@@ -75,24 +75,29 @@ struct BfsWs {
   size_t bytes;
 };
 
-// The BFS loop's workgroups for n vertices (0: too many for the loop).  Us
-// per level with 1 / 8 / 16 / 32 workgroups: 300 x 300 grid 1.82 / 2.53 /
-// 2.66 / 2.85, 700 x 700 3.31 / 2.38 / 2.55 / 2.69, 2003 x 1009 - / 2.61 /
-// 2.44 / 2.64, 3000 x 3000 - / - / 3.35 / 2.94: one workgroup needs no
-// exchange, and a frontier grows about as the root of n.
+// The BFS loop's workgroups for n vertices.  Us per level with 1 / 8 / 16 / 32
+// workgroups: 300 x 300 grid 1.82 / 2.53 / 2.66 / 2.85, 700 x 700 3.31 / 2.38 /
+// 2.55 / 2.69, 2003 x 1009 - / 2.61 / 2.44 / 2.64, 3000 x 3000 - / - / 3.35 / 2.94:
+// one workgroup needs no exchange, and a frontier grows about as the root of n.
+// Above 25M vertices as many as their LDS needs for the visited bits, and where
+// that is more than the chip has CUs (201M) kOwnDeviceGroups, which claim in device
+// memory: 10000 x 10000 grid, 2,000 levels from its middle 8.7 ms with 128
+// workgroups' LDS and 13.9 with 64 in device memory; 14300 x 14300 17.3 (with 32
+// 26.1; a launch per level 84).
 int own_groups(int64_t n) {
   int g = n <= (1 << 18) ? 1 : (n <= (1 << 20) ? 8 : (n <= (1 << 22) ? 16 : 32));
   while (g <= kOwnMaxGroups && (n + g - 1) / g > kOwnVertices - 64) g *= 2;
-  return g <= kOwnMaxGroups ? g : 0;
+  return g <= kOwnMaxGroups ? g : kOwnDeviceGroups;
 }
 
 OwnLoop own_layout(Carver c, int64_t n, int groups, size_t *end = nullptr) {
   OwnLoop o{};
   o.groups = groups;
-  if (!groups) return o;
   o.chunk = (int)align_up((size_t)std::max<int64_t>((n + groups - 1) / groups, 1), 64);
   o.inv_chunk = 1.0f / (float)o.chunk;
-  // box capacities: 512 KB of boxes up to 16 workgroups, 768 KB for 32
+  o.in_device = o.chunk > kOwnVertices;
+  // box capacities: 512 KB of boxes up to 16 workgroups, 768 KB for 32, 2 MB for
+  // 64, 8 for 128 and 32 for 256
   o.cap = std::min(groups <= 16 ? kOwnCapMax : (groups <= 32 ? 92 : 64), o.chunk);
   o.nrec = (int64_t)4 * groups * groups + 4 * groups;
   o.rec = c.take<uint64_t>((size_t)o.nrec);
@@ -105,7 +110,19 @@ OwnLoop own_layout(Carver c, int64_t n, int groups, size_t *end = nullptr) {
 
 constexpr int kOwnTestGroups = 4;
 
-BfsWs bfs_layout(void *ws, int64_t n, int min_groups = 1) {
+// A loop's shape: at least so many workgroups, BFS: visited bits in device memory
+// (the failure path's and the tests' calls differ from what n alone gives)
+struct LoopShape {
+  int groups = 1;
+  bool in_device = false;
+};
+
+LoopShape loop_shape(const grb_descriptor &desc) {
+  // (an exchange with one workgroup alone is never unfinished)
+  return {(desc.flags & GRB_LOOP_NO_WAIT) ? kOwnTestGroups : 1, false};
+}
+
+BfsWs bfs_layout(void *ws, int64_t n, LoopShape shape = {}) {
   Carver c(ws);
   BfsWs t{};
   const int64_t nw = words_of(n);
@@ -113,11 +130,12 @@ BfsWs bfs_layout(void *ws, int64_t n, int min_groups = 1) {
   t.stats = c.take<int64_t>((size_t)kStatsCap * kStatFields);
   t.visited = c.take<uint64_t>((size_t)nw);
   for (int i = 0; i < 3; ++i) t.F[i] = c.take<uint64_t>((size_t)nw);
-  // room for at least kOwnTestGroups workgroups (min_groups: GRB_LOOP_NO_WAIT)
-  const int groups = own_groups(n);
+  // room for at least kOwnTestGroups workgroups (GRB_LOOP_NO_WAIT)
+  const int groups = std::max(own_groups(n), shape.groups);
   size_t end = c.off;
-  own_layout(c, n, groups ? std::max(groups, kOwnTestGroups) : 0, &end);
-  t.own = own_layout(c, n, groups ? std::max(groups, min_groups) : 0);
+  own_layout(c, n, std::max(groups, kOwnTestGroups), &end);
+  t.own = own_layout(c, n, groups);
+  t.own.in_device |= shape.in_device;
   t.bytes = end;
   return t;
 }
@@ -165,7 +183,7 @@ struct SsspWs {
   size_t bytes;
 };
 
-SsspWs sssp_layout(void *ws, int64_t n, int min_groups = 1) {
+SsspWs sssp_layout(void *ws, int64_t n, LoopShape shape = {}) {
   SsspWs t{};
   t.b = bfs_layout(ws, n);
   Carver c(ws);
@@ -175,8 +193,9 @@ SsspWs sssp_layout(void *ws, int64_t n, int min_groups = 1) {
   const int groups = delta_groups(n);
   size_t end = c.off;
   const size_t fd_bytes = c.off - fd_off;
-  delta_layout(c, n, groups ? std::max(groups, kOwnTestGroups) : 0, t.fd[0], fd_bytes, &end);
-  t.own = delta_layout(c, n, groups ? std::max(groups, min_groups) : 0, t.fd[0], fd_bytes);
+  const int most = groups ? std::max(groups, shape.groups) : 0;
+  delta_layout(c, n, groups ? std::max(most, kOwnTestGroups) : 0, t.fd[0], fd_bytes, &end);
+  t.own = delta_layout(c, n, most, t.fd[0], fd_bytes);
   if (!groups) {
     t.qseg = kCoopSeg;
     t.coop = c.take<CoopCtl>(1);
@@ -610,12 +629,12 @@ void finish_stats(int op, int iterations, const std::vector<int64_t> &rec,
 // BFS: one kernel per level (all state on the device); the host reads the
 // frontier size back once per batch of levels to detect the end.
 grb_info run_bfs(grb_matrix A, int32_t source, int32_t *levels, int32_t *parents,
-                 const grb_descriptor &desc, void *ws, size_t ws_bytes, void *stream) {
+                 const grb_descriptor &desc, void *ws, size_t ws_bytes, void *stream,
+                 LoopShape shape) {
   const int64_t n = A->nrows;
   const bool can_pull = A->at.valid();
   if (!can_pull && (desc.direction == GRB_DIR_PULL || parents)) return GRB_NOT_IMPLEMENTED;
-  // (an exchange with one workgroup alone is never unfinished)
-  BfsWs w = bfs_layout(ws, n, (desc.flags & GRB_LOOP_NO_WAIT) ? kOwnTestGroups : 1);
+  BfsWs w = bfs_layout(ws, n, shape);
   grb_info info = check_ws(ws, ws_bytes, w.bytes);
   if (info != GRB_SUCCESS) return info;
   hipStream_t s = (hipStream_t)stream;
@@ -661,8 +680,7 @@ grb_info run_bfs(grb_matrix A, int32_t source, int32_t *levels, int32_t *parents
   // multi-workgroup loop while the frontier is small (no launch per level);
   // a frontier that outgrows it, or an exchange it gave up, continues with the
   // level kernel below.
-  const bool small = A->a.max_deg <= kCoopMaxDeg && desc.direction != GRB_DIR_PULL &&
-                     w.own.groups > 0;
+  const bool small = A->a.max_deg <= kCoopMaxDeg && desc.direction != GRB_DIR_PULL;
   if (small) ba.own = w.own;
   launch_bfs_start(ba, source, w.F[1], w.F[2], stream);
   if (small) {
@@ -843,9 +861,10 @@ grb_info run_sssp(grb_matrix A, int32_t source, float *dist, const grb_descripto
 // Bucketed SSSP: one push kernel per round over the pending set, the host
 // reads the counters back once per batch of rounds.
 grb_info run_sssp_delta(grb_matrix A, int32_t source, float *dist, float delta,
-                        const grb_descriptor &desc, void *ws, size_t ws_bytes, void *stream) {
+                        const grb_descriptor &desc, void *ws, size_t ws_bytes, void *stream,
+                        LoopShape shape) {
   const int64_t n = A->nrows;
-  SsspWs sw = sssp_layout(ws, n, (desc.flags & GRB_LOOP_NO_WAIT) ? kOwnTestGroups : 1);
+  SsspWs sw = sssp_layout(ws, n, shape);
   grb_info info = check_ws(ws, ws_bytes, sw.bytes);
   if (info != GRB_SUCCESS) return info;
   const BfsWs &w = sw.b;
@@ -1430,7 +1449,24 @@ grb_info grb_bfs(int32_t *levels, int32_t *parents, grb_matrix A, int32_t source
   grb_descriptor desc;
   grb_info info = resolve_desc(d, &desc);
   if (info != GRB_SUCCESS) return info;
-  return run_bfs(A, source, levels, parents, desc, ws, ws_bytes, stream);
+  return run_bfs(A, source, levels, parents, desc, ws, ws_bytes, stream, loop_shape(desc));
+}
+
+grb_info grb_bfs_loop(int32_t *levels, int32_t *parents, grb_matrix A, int32_t source,
+                      int32_t groups, int32_t in_device, const grb_descriptor *d, void *ws,
+                      size_t ws_bytes, void *stream) {
+  if (!A || !A->prepared) return GRB_UNINITIALIZED_OBJECT;
+  if (!levels) return GRB_NULL_POINTER;
+  if (A->nrows != A->ncols) return GRB_DIMENSION_MISMATCH;
+  if (source < 0 || source >= A->nrows) return GRB_INVALID_INDEX;
+  if (groups < 1 || groups > (in_device ? kOwnDeviceGroups : kOwnMaxGroups)) return GRB_INVALID_VALUE;
+  if (own_groups(A->nrows) > groups) return GRB_INVALID_VALUE;
+  const OwnLoop own = bfs_layout(nullptr, A->nrows, {groups, in_device != 0}).own;
+  if (own.in_device && own.groups > kOwnDeviceGroups) return GRB_INVALID_VALUE;
+  grb_descriptor desc;
+  grb_info info = resolve_desc(d, &desc);
+  if (info != GRB_SUCCESS) return info;
+  return run_bfs(A, source, levels, parents, desc, ws, ws_bytes, stream, {groups, in_device != 0});
 }
 
 grb_info grb_sssp(float *dist, grb_matrix A, int32_t source, const grb_descriptor *d, void *ws,
@@ -1460,7 +1496,39 @@ grb_info grb_sssp_delta(float *dist, grb_matrix A, int32_t source, float delta,
   grb_info info = resolve_desc(d, &desc);
   if (info != GRB_SUCCESS) return info;
   if (desc.direction == GRB_DIR_PULL) return GRB_NOT_IMPLEMENTED;
-  return run_sssp_delta(A, source, dist, delta, desc, ws, ws_bytes, stream);
+  return run_sssp_delta(A, source, dist, delta, desc, ws, ws_bytes, stream, loop_shape(desc));
+}
+
+grb_info grb_sssp_delta_loop(float *dist, grb_matrix A, int32_t source, float delta, int32_t groups,
+                             const grb_descriptor *d, void *ws, size_t ws_bytes, void *stream) {
+  if (!A || !A->prepared) return GRB_UNINITIALIZED_OBJECT;
+  if (!dist) return GRB_NULL_POINTER;
+  if (A->nrows != A->ncols) return GRB_DIMENSION_MISMATCH;
+  if (source < 0 || source >= A->nrows) return GRB_INVALID_INDEX;
+  if (A->a.vtype != GRB_FP32) return GRB_DOMAIN_MISMATCH;
+  if (A->a.negative || A->at.negative) return GRB_INVALID_VALUE;
+  if (!(delta > 0.0f) || !(delta < 3.0e38f)) return GRB_INVALID_VALUE;
+  if (groups < 1 || groups > kDeltaMaxGroups) return GRB_INVALID_VALUE;
+  const int least = delta_groups(A->nrows);
+  // (a box holds at least the message of its head)
+  if (least == 0 || least > groups || sssp_layout(nullptr, A->nrows, {groups, false}).own.cap < 1)
+    return GRB_INVALID_VALUE;
+  grb_descriptor desc;
+  grb_info info = resolve_desc(d, &desc);
+  if (info != GRB_SUCCESS) return info;
+  if (desc.direction == GRB_DIR_PULL) return GRB_NOT_IMPLEMENTED;
+  return run_sssp_delta(A, source, dist, delta, desc, ws, ws_bytes, stream, {groups, false});
+}
+
+grb_info grb_loop_workspace_size(grb_op op, grb_matrix A, int32_t groups, size_t *bytes) {
+  if (!bytes) return GRB_NULL_POINTER;
+  if (!A) return GRB_UNINITIALIZED_OBJECT;
+  if (groups < 1 || groups > (op == GRB_OP_BFS ? kOwnMaxGroups : kDeltaMaxGroups))
+    return GRB_INVALID_VALUE;
+  if (op == GRB_OP_BFS) *bytes = bfs_layout(nullptr, A->nrows, {groups, false}).bytes;
+  else if (op == GRB_OP_SSSP) *bytes = sssp_layout(nullptr, A->nrows, {groups, false}).bytes;
+  else return GRB_INVALID_VALUE;
+  return GRB_SUCCESS;
 }
 
 }  // extern "C"

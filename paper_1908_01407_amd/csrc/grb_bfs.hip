@@ -801,6 +801,13 @@ __global__ __launch_bounds__(kBlock) void k_bfs_level(BfsArgs a) {
   }
 }
 
+// The rows of word w that no level can find: without in-edges, or padding.
+__device__ __forceinline__ uint64_t never_found(const BfsArgs &a, int64_t w) {
+  if (a.can_pull) return a.pull.iso[w];
+  const int64_t valid = a.n - w * 64;  // bits past n are padding
+  return valid >= 64 ? 0ull : ~mask_below((int)valid);
+}
+
 __global__ __launch_bounds__(kBlock) void k_bfs_start(BfsArgs a, int32_t source, uint64_t *f1,
                                                       uint64_t *f2) {
   const int64_t tid = (int64_t)blockIdx.x * kBlock + threadIdx.x;
@@ -830,14 +837,7 @@ __global__ __launch_bounds__(kBlock) void k_bfs_start(BfsArgs a, int32_t source,
   const int64_t sw = source >> 6;
   const uint64_t sb = 1ull << (source & 63);
   for (int64_t w = tid; w < a.nw; w += nt) {
-    uint64_t vis;
-    if (a.can_pull) {
-      vis = a.pull.iso[w];
-    } else {
-      const int64_t valid = a.n - w * 64;  // bits past n are padding
-      vis = valid >= 64 ? 0ull : ~mask_below((int)valid);
-    }
-    a.visited[w] = vis | (w == sw ? sb : 0ull);
+    a.visited[w] = never_found(a, w) | (w == sw ? sb : 0ull);
     a.fcur[w] = w == sw ? sb : 0ull;
     f1[w] = 0ull;
     f2[w] = 0ull;
@@ -908,7 +908,9 @@ __global__ __launch_bounds__(kBlock) void k_bfs_start(BfsArgs a, int32_t source,
 // form for 377,000 vertices made the 3000 x 3000 grid's levels 1.3 % longer.
 template <int VIS>
 struct OwnShared {
-  uint32_t vis[VIS / 32];
+  static constexpr int kVis = VIS;
+  static constexpr int kIn = VIS ? 2 : 0;  // targets of each sender in its head
+  uint32_t vis[VIS ? VIS / 32 : 1];
   int q[2][kOwnQueue];
   int cnt[2];              // entries found by the expansion into each queue
   int out[kOwnMaxGroups];  // targets sent to each workgroup in this level
@@ -983,7 +985,14 @@ __device__ __forceinline__ void own_queue(const BfsArgs &a, SH &sh, int *cnt, in
   }
 }
 
-// Claims the owned targets among c[0..4) (all four LDS atomics are issued
+// Sets the visited bit of the owned vertex l; returns the word as it was.
+template <class SH>
+__device__ __forceinline__ uint32_t own_claim(const BfsArgs &a, SH &sh, int lo, uint32_t l) {
+  if constexpr (SH::kVis != 0) return atomicOr(&sh.vis[l >> 5], 1u << (l & 31));
+  else return atomicOr(reinterpret_cast<uint32_t *>(a.visited) + ((lo + l) >> 5), 1u << (l & 31));
+}
+
+// Claims the owned targets among c[0..4) (all four atomics are issued
 // before a result is used), sends the others to their owners and queues the
 // claims won.
 template <class SH>
@@ -998,7 +1007,7 @@ __device__ __forceinline__ void own_expand(const BfsArgs &a, SH &sh, int lo, int
     const bool own = l < (uint32_t)nv;
     far |= c[k] >= 0 && !own;
     old[k] = ~0u;
-    if (own) old[k] = atomicOr(&sh.vis[l >> 5], 1u << (l & 31));
+    if (own) old[k] = own_claim(a, sh, lo, l);
   }
   if (__ballot(far)) {
     const int G = a.own.groups, cap = a.own.cap;
@@ -1016,7 +1025,7 @@ __device__ __forceinline__ void own_expand(const BfsArgs &a, SH &sh, int lo, int
       }
       const int slot = atomicAdd(&sh.out[o], 1);
       atomicAdd(&sh.sent, 1);
-      if (slot < 2) {
+      if (slot < SH::kIn) {
         sh.msg[o][slot] = m;
       } else if (slot < cap) {
         st_coherent(&box[((int64_t)w * G + o) * cap + slot], c[k]);
@@ -1053,6 +1062,7 @@ __global__ __launch_bounds__(kOwnThreads) void k_bfs_own(BfsArgs a, int32_t sour
                                                          int most, int share, uint64_t *F0,
                                                          uint64_t *F1, uint64_t *F2) {
   __shared__ OwnShared<VIS> sh;
+  constexpr int IN = OwnShared<VIS>::kIn;
   constexpr int T = kOwnThreads - 64;  // threads that take queue entries (waves 1, 2, ...)
   const int tid = threadIdx.x, ln = tid & 63;
   const int et = tid - 64;  // this thread's first entry (wave 0 takes none)
@@ -1062,8 +1072,9 @@ __global__ __launch_bounds__(kOwnThreads) void k_bfs_own(BfsArgs a, int32_t sour
   const int lo = (int)(first < a.n ? first : a.n);
   const int nv = (int)(a.n - lo < a.own.chunk ? a.n - lo : a.own.chunk);  // vertices owned
   // visited bits as the start kernel left them (rows nothing reaches, source)
-  for (int i = tid; i < (nv + 31) / 32; i += kOwnThreads)
-    sh.vis[i] = reinterpret_cast<const uint32_t *>(a.visited)[lo / 32 + i];
+  if constexpr (VIS != 0)
+    for (int i = tid; i < (nv + 31) / 32; i += kOwnThreads)
+      sh.vis[i] = reinterpret_cast<const uint32_t *>(a.visited)[lo / 32 + i];
   if (tid < kOwnMaxGroups) sh.out[tid] = sh.msg[tid][0] = sh.msg[tid][1] = 0;
   const bool mine = source >= lo && source - lo < nv;
   if (tid == 0) {
@@ -1175,8 +1186,8 @@ __global__ __launch_bounds__(kOwnThreads) void k_bfs_own(BfsArgs a, int32_t sour
             full |= (tt[r] & 1ull) != 0;
             front |= total_n(tt[r]) != 0;
             const int kc = head_cnt(hd[r]);
-            more |= kc > 2;
-            if (__ballot(kc != 0) == 0ull) continue;
+            more |= kc > IN;
+            if (IN == 0 || __ballot(kc != 0) == 0ull) continue;
             // the first two targets of each sender
             const int m0 = head_m0(hd[r]), m1 = head_m1(hd[r]);
             uint32_t o0 = ~0u, o1 = ~0u;
@@ -1222,7 +1233,7 @@ __global__ __launch_bounds__(kOwnThreads) void k_bfs_own(BfsArgs a, int32_t sour
           if (__ballot(more)) {  // boxes: prefix of the further targets, lane-major
             int k[R], in = 0;
 #pragma unroll
-            for (int r = 0; r < R; ++r) in += k[r] = max(head_cnt(hd[r]) - 2, 0);
+            for (int r = 0; r < R; ++r) in += k[r] = max(head_cnt(hd[r]) - IN, 0);
             const int incl = wave_incl_scan(in);
             int run = incl - in;
 #pragma unroll
@@ -1304,9 +1315,9 @@ __global__ __launch_bounds__(kOwnThreads) void k_bfs_own(BfsArgs a, int32_t sour
           for (int step = 32 * R; step > 0; step >>= 1)
             if (sh.pre[at + step] <= i) at += step;
           const int sd = (at % R) * 64 + at / R;
-          c[0] = ld_coherent(&box[((int64_t)sd * G + w) * cap + 2 + (i - sh.pre[at])]);
+          c[0] = ld_coherent(&box[((int64_t)sd * G + w) * cap + IN + (i - sh.pre[at])]);
           const int l = c[0] - lo;
-          wn[0] = !((atomicOr(&sh.vis[l >> 5], 1u << (l & 31)) >> (l & 31)) & 1u);
+          wn[0] = !((own_claim(a, sh, lo, (uint32_t)l) >> (l & 31)) & 1u);
           if (wn[0]) a.levels[c[0]] = d;
         }
         own_queue(a, sh, &sh.n_new, sh.q[nxt], fn, d, c, wn);
@@ -1416,6 +1427,7 @@ __global__ __launch_bounds__(kBlock) void k_bfs_own_boxes(BfsArgs a, uint64_t *F
   const int64_t h = a.ctrl->small_levels;
   uint64_t *fh = (h % 3 == 0) ? F0 : ((h % 3 == 1) ? F1 : F2);
   const int G = a.own.groups, cap = a.own.cap, par = (int)((h - 1) & 1);
+  const int in = a.own.in_device ? 0 : 2;  // targets in the heads
   const int32_t *box = a.own.box + (int64_t)par * G * G * cap;
   const uint64_t *rec = a.own.rec + (int64_t)par * G * G * 2;
   const uint32_t tag = own_tag(h - 1);
@@ -1427,7 +1439,7 @@ __global__ __launch_bounds__(kBlock) void k_bfs_own_boxes(BfsArgs a, uint64_t *F
       const int sd = (int)(pair / G), o = (int)(pair % G), j = (int)(t % cap);
       const uint64_t hd = rec[((int64_t)o * G + sd) * 2];
       if ((uint32_t)(hd >> 48) != tag || j >= head_cnt(hd)) continue;
-      const int c = j >= 2 ? box[t] : o * a.own.chunk + (j == 0 ? head_m0(hd) : head_m1(hd));
+      const int c = j >= in ? box[t] : o * a.own.chunk + (j == 0 ? head_m0(hd) : head_m1(hd));
       atomicOr((unsigned long long *)&fh[c >> 6], 1ull << (c & 63));
     }
   }
@@ -1482,7 +1494,8 @@ __global__ __launch_bounds__(kBlock) void k_bfs_own_handover(BfsArgs a, uint64_t
       fh[w] = fm;
       f1[w] = 0ull;
       f2[w] = 0ull;
-      a.visited[w] |= vm;
+      // (with the visited bits in device memory they hold claims beyond h too)
+      a.visited[w] = vm | (a.own.in_device ? never_found(a, w) : a.visited[w]);
     }
   }
   fc = wave_sum(fc);
@@ -1519,7 +1532,8 @@ void launch_bfs_own(const BfsArgs &a, int32_t source, int64_t max_levels, uint64
   }
   const int cap = (int)std::min<int64_t>(max_levels, kOwnMaxLevels + 1);
   const int most = (int)m, share = (int)std::min<int64_t>(m, kOwnQueue) / a.own.groups;
-  const auto kernel = a.own.groups > 64                ? k_bfs_own<4, kOwnVertices>
+  const auto kernel = a.own.in_device                  ? k_bfs_own<1, 0>
+                      : a.own.groups > 64                ? k_bfs_own<4, kOwnVertices>
                       : a.own.chunk <= kOwnVerticesLow ? k_bfs_own<1, kOwnVerticesLow>
                                                        : k_bfs_own<1, kOwnVertices>;
   hipLaunchKernelGGL(kernel, dim3(a.own.groups), dim3(kOwnThreads), 0, s, a, source, cap, wait_ticks,

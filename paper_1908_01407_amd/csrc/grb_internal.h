@@ -230,6 +230,7 @@ constexpr int kOwnVertices = 786432;  // BFS: visited bits a workgroup can hold 
 constexpr int kOwnVerticesLow = 65536;  // ... in the form for smaller graphs (8 KB)
 constexpr int kOwnQueue = 4096;       // BFS: queue entries per workgroup (two queues: 32 KB)
 constexpr int kOwnMaxGroups = 256;
+constexpr int kOwnDeviceGroups = 64;  // BFS: visited bits in device memory
 constexpr int kDeltaCapMax = 8191;         // bucket rounds: messages from one workgroup to another per round
 constexpr int kDeltaMaxGroups = 64;        // ... workgroups
 constexpr int kDeltaOwnLds = 32768;        // bucket rounds: vertices whose distances fit LDS (128 KB)
@@ -247,6 +248,7 @@ struct OwnLoop {
   // SSSP messages (vertex within its owner << 32 | distance bits; the first unused)
   int32_t *box = nullptr;
   uint64_t *box64 = nullptr;
+  bool in_device = false;  // BFS: visited bits in device memory, no targets in the heads
 };
 // BFS with one kernel per level (grb_bfs.hip).  Each of the three rotating
 // frontier buffers has kCntStripes stripes of counters: frontier size, its
