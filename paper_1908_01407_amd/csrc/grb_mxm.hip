@@ -19,9 +19,9 @@
 // segment and the streamed rows are the short rows of high-degree vertices
 // that every wave re-reads from the caches.
 //
-// Triangle counting fuses the reduction into the product (the kernel
-// fusion the paper names as open work): nothing of C is written, each wave
-// counts its hits, and one atomic per workgroup adds the total.
+// Triangle counting fuses the reduction into the structure-only product (the
+// kernel fusion the paper names as open work): nothing of C is written, each
+// wave counts its hits and adds them to one of the counter's stripes.
 #include <hip/hip_runtime.h>
 
 #include "grb_device.h"
@@ -46,29 +46,11 @@ __device__ __forceinline__ int lower_pos(P col, int d, int32_t k) {
   return lo;
 }
 
-// product of A(i, k) and B(j, k) under the semiring's multiply: 1 for
-// PLUS_PAIR (structure only), a * b for PLUS_TIMES
+// Writes C(i, j) = sum of the products to c[e] for every mask entry e.
 template <class V>
-struct Mul {
-  __device__ __forceinline__ static V get(const void *aval, int64_t ia, const void *bval,
-                                          int64_t ib) {
-    return ((const V *)aval)[ia] * ((const V *)bval)[ib];
-  }
-};
-template <>
-struct Mul<int> {
-  __device__ __forceinline__ static int get(const void *, int64_t, const void *, int64_t) {
-    return 1;
-  }
-};
-
-// COUNT: add the hits into *a.count (V must be int, PLUS_PAIR); otherwise
-// write C(i, j) = sum of the products to c[e] for every mask entry e.
-template <class V, bool COUNT>
 __global__ __launch_bounds__(kBlock) void k_mxm_dot(MxmArgs a) {
   __shared__ int32_t s_col[kWavesPerBlock][kMxmLds];
   __shared__ int s_mark[kWavesPerBlock][64];
-  __shared__ unsigned long long s_cnt[kWavesPerBlock];
   const int wid = threadIdx.x >> 6;
   const int ln = threadIdx.x & 63;
   int32_t *lcol = s_col[wid];
@@ -78,16 +60,15 @@ __global__ __launch_bounds__(kBlock) void k_mxm_dot(MxmArgs a) {
   const int32_t *mrp = a.M.rp, *mci = a.M.ci;
   const int32_t *arp = a.A.rp, *aci = a.A.ci;
   const int32_t *brp = a.B.rp, *bci = a.B.ci;
+  const V *aval = (const V *)a.A.val, *bval = (const V *)a.B.val;
   V *c = (V *)a.c;
-  unsigned long long hits = 0;  // COUNT: wave-uniform
   for (int64_t i = gw; i < a.nrows; i += nwaves) {
     const int mb = mrp[i], me = mrp[i + 1];
     if (mb == me) continue;
     const int ab = arp[i];
     const int da = arp[i + 1] - ab;
     if (da == 0) {  // empty row of A: every entry of the row is zero
-      if (!COUNT)
-        for (int e = mb + ln; e < me; e += 64) c[e] = (V)0;
+      for (int e = mb + ln; e < me; e += 64) c[e] = (V)0;
       continue;
     }
     const bool in_lds = da <= kMxmLds;
@@ -146,32 +127,17 @@ __global__ __launch_bounds__(kBlock) void k_mxm_dot(MxmArgs a) {
             if (got == kk[s]) at[s] = p;
           }
         }
-        if (COUNT) {
 #pragma unroll
-          for (int s = 0; s < kUnroll; ++s) hits += (unsigned long long)__popcll(__ballot(at[s] >= 0));
-        } else {
-#pragma unroll
-          for (int s = 0; s < kUnroll; ++s) {
-            const V v = at[s] >= 0 ? Mul<V>::get(a.A.val, (int64_t)ab + at[s], a.B.val, pos[s])
-                                   : (V)0;
-            const V y = seg_sum_scan<V>(v, row[s]);
-            const V seg = __shfl(y, st[s] ? se[s] - 1 : 0);
-            if (st[s]) acc += seg;
-          }
+        for (int s = 0; s < kUnroll; ++s) {
+          const V v = at[s] >= 0 ? aval[ab + at[s]] * bval[pos[s]] : (V)0;
+          const V y = seg_sum_scan<V>(v, row[s]);
+          const V seg = __shfl(y, st[s] ? se[s] - 1 : 0);
+          if (st[s]) acc += seg;
         }
       }
-      if (!COUNT && has) c[e] = acc;
+      if (has) c[e] = acc;
     }
     if (in_lds) wave_lds_sync();  // the next row overwrites the segment
-  }
-  if (COUNT) {
-    if (ln == 0) s_cnt[wid] = hits;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      unsigned long long t = 0;
-      for (int w = 0; w < kWavesPerBlock; ++w) t += s_cnt[w];
-      if (t) atomicAdd(a.count, t);
-    }
   }
 }
 
@@ -493,9 +459,9 @@ void launch_mxm_dot(const MxmArgs &a, bool count, void *stream) {
     else if (large) hipLaunchKernelGGL((k_mxm_pair<false, 2 * kPairBits>), gp, bp, 0, s, a);
     else hipLaunchKernelGGL((k_mxm_pair<false, kPairBits>), gp, bp, 0, s, a);
   } else if (a.vt == GRB_FP32) {
-    hipLaunchKernelGGL((k_mxm_dot<float, false>), g, b, 0, s, a);
+    hipLaunchKernelGGL((k_mxm_dot<float>), g, b, 0, s, a);
   } else {
-    hipLaunchKernelGGL((k_mxm_dot<double, false>), g, b, 0, s, a);
+    hipLaunchKernelGGL((k_mxm_dot<double>), g, b, 0, s, a);
   }
 }
 

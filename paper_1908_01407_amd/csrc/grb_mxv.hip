@@ -617,8 +617,7 @@ __device__ __forceinline__ void mxv_merge(const MxvArgs &a) {
 // here; allowed longer rows are left to the fix-up kernel (their bits of
 // the output word are kept).
 template <int SR>
-__device__ void pull_word(const MxvArgs &a, int64_t wd, bool full, int *mark, int *s_end,
-                          int *s_base) {
+__device__ void pull_word(const MxvArgs &a, int64_t wd, bool full, int *s_end, int *s_base) {
   using T = typename Sr<SR>::T;
   const int ln = threadIdx.x & 63;
   const int32_t *rp = a.pull.rp, *ci = a.pull.ci;
@@ -636,113 +635,66 @@ __device__ void pull_word(const MxvArgs &a, int64_t wd, bool full, int *mark, in
   const bool act = allowed && !lng && end > cur;
   T acc = Sr<SR>::identity();
   bool has = false;
-  if constexpr (Sr<SR>::lor) {
-    // first two neighbours of every allowed row first (prepared first-two
-    // array), so that rows settled by them never stream
-    bool q0 = false, q1 = false, p0 = false, p1 = false;
-    if (act) {
-      const int2 f = a.pull.first2[i];
-      q0 = f.x >= 0;
-      q1 = f.y >= 0;
-      p0 = q0 && bit_of(a.u_bm, f.x);
-      p1 = q1 && bit_of(a.u_bm, f.y);
-      if (p0 || p1) has = true;
-      if ((p0 && u_at<T>(a, f.x) != 0 && mat_true(a.pull, cur)) ||
-          (p1 && u_at<T>(a, f.y) != 0 && mat_true(a.pull, cur + 1)))
-        acc = 1;
-      cur = min(cur + 2, end);
-    }
-    // the probes' hit rate estimates the frontier's density d; a row then
-    // streams about 2/d positions per step (its first frontier entry is
-    // expected 1/d in), so a dense frontier does not gather past the first
-    const int np = __popcll(__ballot(q0)) + __popcll(__ballot(q1));
-    const int nh = __popcll(__ballot(p0)) + __popcll(__ballot(p1));
-    const int cmin = nh == 0 ? 64 : min(64, max(4, 2 * np / nh));
-    for (;;) {
-      int len = (act && acc == 0) ? end - cur : 0;  // OR saturates at true
-      if (cmin < 64) {
-        const int nl = __popcll(__ballot(len > 0));
-        len = min(len, max(cmin, nl ? (64 + nl - 1) / nl : 64));
-      }
-      const int incl = wave_incl_scan(len);
-      const int total = lane_last(incl);
-      if (total == 0) break;
-      const int excl = incl - len;
-      const bool starts = len > 0 && excl < 64;
-      const int r = slot_rows(mark, starts, excl);
-      const int rcur = __shfl(cur, r), rexcl = __shfl(excl, r);
-      const int64_t pos = ln < total ? rcur + (ln - rexcl) : -1;
-      const int sev = min(incl, 64);
-      if (starts) cur += sev - excl;
-      const int j = pos >= 0 ? ci[pos] : -1;
-      const bool pres = j >= 0 && bit_of(a.u_bm, j);
-      const bool prod = pres && u_at<T>(a, j) != 0 && mat_true(a.pull, pos);
-      const uint64_t seg = starts ? (mask_below(sev) & ~mask_below(excl)) : 0ull;
-      if (__ballot(pres) & seg) has = true;
-      if (__ballot(prod) & seg) acc = 1;
-    }
-  } else {
-    // the word's rows as one list of `total` positions; each position finds
-    // its row by bisection of the rows' prefix ends (LDS), so the loads of
-    // kUnroll steps are in flight together; each row adds its segment of a
-    // step in step order (fixed order)
-    const int len = act ? end - cur : 0;
-    const int incl = wave_incl_scan(len);
-    const int total = lane_last(incl);
-    const int excl = incl - len;
-    s_end[ln] = incl;
-    s_base[ln] = cur - excl;
-    wave_lds_sync();
-    for (int q0 = 0; q0 < total; q0 += 64 * kUnroll) {
-      int row[kUnroll];
-      int64_t pos[kUnroll];
+  // the word's rows as one list of `total` positions; each position finds
+  // its row by bisection of the rows' prefix ends (LDS), so the loads of
+  // kUnroll steps are in flight together; each row adds its segment of a
+  // step in step order (fixed order)
+  const int len = act ? end - cur : 0;
+  const int incl = wave_incl_scan(len);
+  const int total = lane_last(incl);
+  const int excl = incl - len;
+  s_end[ln] = incl;
+  s_base[ln] = cur - excl;
+  wave_lds_sync();
+  for (int q0 = 0; q0 < total; q0 += 64 * kUnroll) {
+    int row[kUnroll];
+    int64_t pos[kUnroll];
 #pragma unroll
-      for (int s = 0; s < kUnroll; ++s) {
-        const int q = q0 + s * 64 + ln;
-        row[s] = -1;
-        pos[s] = -1;
-        if (q < total) {
-          int r = 0;
+    for (int s = 0; s < kUnroll; ++s) {
+      const int q = q0 + s * 64 + ln;
+      row[s] = -1;
+      pos[s] = -1;
+      if (q < total) {
+        int r = 0;
 #pragma unroll
-          for (int step = 32; step >= 1; step >>= 1)
-            if (s_end[r + step - 1] <= q) r += step;
-          row[s] = r;
-          pos[s] = (int64_t)s_base[r] + q;
-        }
-      }
-      int jv[kUnroll];
-#pragma unroll
-      for (int s = 0; s < kUnroll; ++s) jv[s] = pos[s] >= 0 ? ci[pos[s]] : -1;
-      bool pres[kUnroll];
-      if (full) {
-#pragma unroll
-        for (int s = 0; s < kUnroll; ++s) pres[s] = jv[s] >= 0;
-      } else {
-#pragma unroll
-        for (int s = 0; s < kUnroll; ++s) pres[s] = jv[s] >= 0 && bit_of(a.u_bm, jv[s]);
-      }
-      T prod[kUnroll];
-#pragma unroll
-      for (int s = 0; s < kUnroll; ++s)
-        prod[s] = pres[s] ? Sr<SR>::mul(mat_value<T>(a.pull, pos[s]), u_at<T>(a, jv[s]), a.pick_vec)
-                          : Sr<SR>::identity();
-#pragma unroll
-      for (int s = 0; s < kUnroll; ++s) {
-        const int sb = q0 + s * 64;
-        const T y = wave_seg_scan(prod[s], row[s], Sr<SR>::identity(), SrAdd<SR>());
-        const uint64_t pm = __ballot(pres[s]);
-        // this lane's row: its part of step s and the lane holding its end
-        const int lo = max(excl, sb) - sb, hi = min(incl, sb + 64) - sb;
-        const bool mine = len > 0 && lo < hi;
-        const T segv = __shfl(y, mine ? hi - 1 : 0);
-        if (mine && (pm & mask_below(hi) & ~mask_below(lo))) {
-          has = true;
-          acc = Sr<SR>::add(acc, segv);
-        }
+        for (int step = 32; step >= 1; step >>= 1)
+          if (s_end[r + step - 1] <= q) r += step;
+        row[s] = r;
+        pos[s] = (int64_t)s_base[r] + q;
       }
     }
-    wave_lds_sync();
+    int jv[kUnroll];
+#pragma unroll
+    for (int s = 0; s < kUnroll; ++s) jv[s] = pos[s] >= 0 ? ci[pos[s]] : -1;
+    bool pres[kUnroll];
+    if (full) {
+#pragma unroll
+      for (int s = 0; s < kUnroll; ++s) pres[s] = jv[s] >= 0;
+    } else {
+#pragma unroll
+      for (int s = 0; s < kUnroll; ++s) pres[s] = jv[s] >= 0 && bit_of(a.u_bm, jv[s]);
+    }
+    T prod[kUnroll];
+#pragma unroll
+    for (int s = 0; s < kUnroll; ++s)
+      prod[s] = pres[s] ? Sr<SR>::mul(mat_value<T>(a.pull, pos[s]), u_at<T>(a, jv[s]), a.pick_vec)
+                        : Sr<SR>::identity();
+#pragma unroll
+    for (int s = 0; s < kUnroll; ++s) {
+      const int sb = q0 + s * 64;
+      const T y = wave_seg_scan(prod[s], row[s], Sr<SR>::identity(), SrAdd<SR>());
+      const uint64_t pm = __ballot(pres[s]);
+      // this lane's row: its part of step s and the lane holding its end
+      const int lo = max(excl, sb) - sb, hi = min(incl, sb + 64) - sb;
+      const bool mine = len > 0 && lo < hi;
+      const T segv = __shfl(y, mine ? hi - 1 : 0);
+      if (mine && (pm & mask_below(hi) & ~mask_below(lo))) {
+        has = true;
+        acc = Sr<SR>::add(acc, segv);
+      }
+    }
   }
+  wave_lds_sync();
   bool out_has = false;
   if (inb && !(allowed && lng)) {
     T out = acc;
@@ -985,64 +937,31 @@ __device__ __forceinline__ void pull_piece(const MxvArgs &a, int64_t b, int64_t 
   const int32_t *ci = a.pull.ci;
   acc = Sr<SR>::identity();
   has = false;
-  if constexpr (Sr<SR>::lor) {
-    // the first step alone (a dense frontier ends the piece there), then
-    // the rest at once
-    {
-      const int64_t pos = b + ln;
-      const int j = pos < e ? ci[pos] : -1;
-      const bool pres = j >= 0 && bit_of(a.u_bm, j);
-      has = __ballot(pres) != 0ull;
-      if (__ballot(pres && u_at<T>(a, j) != 0 && mat_true(a.pull, pos))) {
-        acc = 1;
-        return;
-      }
-    }
-    int jv[kUnroll - 1];
+  int jv[kUnroll];
 #pragma unroll
-    for (int s = 1; s < kUnroll; ++s) {
-      const int64_t pos = b + s * 64 + ln;
-      jv[s - 1] = pos < e ? ci[pos] : -1;
-    }
-    bool pres[kUnroll - 1], tru[kUnroll - 1];
-#pragma unroll
-    for (int s = 1; s < kUnroll; ++s) {
-      const int64_t pos = b + s * 64 + ln;
-      pres[s - 1] = jv[s - 1] >= 0 && bit_of(a.u_bm, jv[s - 1]);
-      tru[s - 1] = pres[s - 1] && u_at<T>(a, jv[s - 1]) != 0 && mat_true(a.pull, pos);
-    }
-#pragma unroll
-    for (int s = 0; s < kUnroll - 1; ++s) {
-      if (__ballot(pres[s])) has = true;
-      if (__ballot(tru[s])) acc = 1;
-    }
-  } else {
-    int jv[kUnroll];
-#pragma unroll
-    for (int s = 0; s < kUnroll; ++s) {
-      const int64_t pos = b + s * 64 + ln;
-      jv[s] = pos < e ? ci[pos] : -1;
-    }
-    bool pres[kUnroll];
-    if (full) {
-#pragma unroll
-      for (int s = 0; s < kUnroll; ++s) pres[s] = jv[s] >= 0;
-    } else {
-#pragma unroll
-      for (int s = 0; s < kUnroll; ++s) pres[s] = jv[s] >= 0 && bit_of(a.u_bm, jv[s]);
-    }
-    T prod[kUnroll];
-#pragma unroll
-    for (int s = 0; s < kUnroll; ++s)
-      prod[s] = pres[s] ? Sr<SR>::mul(mat_value<T>(a.pull, b + s * 64 + ln), u_at<T>(a, jv[s]),
-                                      a.pick_vec)
-                        : Sr<SR>::identity();
-    // a lane's products first, in pairs, then the lanes: one scan a piece
-    static_assert(kUnroll == 4, "two pairs");
-    acc = Sr<SR>::add(Sr<SR>::add(prod[0], prod[1]), Sr<SR>::add(prod[2], prod[3]));
-    has = __ballot(pres[0] || pres[1] || pres[2] || pres[3]) != 0ull;
-    acc = lane_last(wave_scan(acc, Sr<SR>::identity(), SrAdd<SR>()));
+  for (int s = 0; s < kUnroll; ++s) {
+    const int64_t pos = b + s * 64 + ln;
+    jv[s] = pos < e ? ci[pos] : -1;
   }
+  bool pres[kUnroll];
+  if (full) {
+#pragma unroll
+    for (int s = 0; s < kUnroll; ++s) pres[s] = jv[s] >= 0;
+  } else {
+#pragma unroll
+    for (int s = 0; s < kUnroll; ++s) pres[s] = jv[s] >= 0 && bit_of(a.u_bm, jv[s]);
+  }
+  T prod[kUnroll];
+#pragma unroll
+  for (int s = 0; s < kUnroll; ++s)
+    prod[s] = pres[s] ? Sr<SR>::mul(mat_value<T>(a.pull, b + s * 64 + ln), u_at<T>(a, jv[s]),
+                                    a.pick_vec)
+                      : Sr<SR>::identity();
+  // a lane's products first, in pairs, then the lanes: one scan a piece
+  static_assert(kUnroll == 4, "two pairs");
+  acc = Sr<SR>::add(Sr<SR>::add(prod[0], prod[1]), Sr<SR>::add(prod[2], prod[3]));
+  has = __ballot(pres[0] || pres[1] || pres[2] || pres[3]) != 0ull;
+  acc = lane_last(wave_scan(acc, Sr<SR>::identity(), SrAdd<SR>()));
 }
 
 // The product: the push's tiles, or the pull sweep.
@@ -1102,7 +1021,7 @@ __global__ __launch_bounds__(kBlock) void k_mxv_product(MxvArgs a) {
       } else {
         for (; todo; todo &= todo - 1) {
           const int k = __ffsll((unsigned long long)todo) - 1;
-          pull_word<SR>(a, w0 + k, full, s.sweep.mark[wid], s.sweep.end[wid], s.sweep.base[wid]);
+          pull_word<SR>(a, w0 + k, full, s.sweep.end[wid], s.sweep.base[wid]);
         }
       }
     }
