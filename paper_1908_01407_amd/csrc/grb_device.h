@@ -288,9 +288,12 @@ __device__ __forceinline__ int coop_barrier(unsigned long long *bar, int groups,
 // Which integer comparison orders v against any float: values at or below
 // -0.0 by their unsigned bits, downwards; the others (and NaN) by their signed
 // ones.  (Testing v < 0 alone puts -0.0, INT_MIN, below every negative value.)
-__device__ __forceinline__ bool below_zero(float v) { return v <= 0.0f && __float_as_int(v) < 0; }
+__device__ __forceinline__ bool below_zero(float v) {  // from -0.0 to -inf
+  return (__float_as_uint(v) ^ 0x80000000u) <= 0x7f800000u;
+}
 __device__ __forceinline__ bool below_zero(double v) {
-  return v <= 0.0 && __double_as_longlong(v) < 0;
+  return ((unsigned long long)__double_as_longlong(v) ^ 0x8000000000000000ull) <=
+         0x7ff0000000000000ull;
 }
 
 // atomic min for floats of either sign (returns the previous value)
