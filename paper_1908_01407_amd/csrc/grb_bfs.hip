@@ -719,9 +719,10 @@ __global__ __launch_bounds__(kBlock) void k_bfs_level(BfsArgs a) {
   __shared__ int s_open, s_prev_sd;
   __shared__ int s_red[kWavesPerBlock][3];
   // A lane adds the stripes of one field, and a workgroup ends with one 8-byte
-  // add for count and degree sum: one thread reading, and clearing, all of them
-  // and two adds made RMAT-14 from three sources 75, 60 and 70 us (71, 56 and 67
-  // so) and RMAT-22 184, 187 and 217 (175, 177 and 210).
+  // add for count and degree sum.  With one thread reading, and clearing, all of
+  // them and two adds, single runs from three sources took 75, 60 and 70 us on
+  // RMAT-14 (71, 56 and 67 so) and 184, 187 and 217 on RMAT-22 (175, 177 and
+  // 210); repeated, the two differ by no more than the runs of one (7 % and 1 %).
   static_assert(kCntSlots == 128 && 64 % kCntFields == 0, "two stripes a lane");
   if (threadIdx.x < 64) {
     const int ln = threadIdx.x;

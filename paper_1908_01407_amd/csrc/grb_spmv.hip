@@ -266,8 +266,8 @@ __global__ __launch_bounds__(kBlock) void k_pr_iter(PrArgs a) {
 // for every four rows took 16 us an iteration on RMAT-22 (fp32), and the kernel
 // below 11 to read the partials of all of them; at most kPrLongGrid: 12 and 8.7.
 // A wave left with one row takes it alone, which is every wave of a graph with
-// few long rows: 300,000 vertices, fp64, 1,140 us a call with four rows' steps
-// for one, 1,132 so.
+// few long rows: with four rows' steps for one, 20,841 vertices in fp64 took
+// 583 us a call and 300,000 took 1,085, so 574 and 1,077.
 template <int K, class T, bool AD>
 __device__ __forceinline__ void pr_long_rows(const PrArgs &a, int64_t i0, int64_t nwaves, T dn,
                                              double &delta, double &dang, double &dfz,

@@ -349,14 +349,15 @@ __global__ __launch_bounds__(kBlock) void k_sssp_delta_start(SsspArgs a, int32_t
 // workgroup w owns the vertices [w * chunk, (w + 1) * chunk); its pending
 // vertices are two lists in its LDS, near (below the bucket's limit) and far,
 // with a membership bit each, and it alone relaxes their distances, which sit
-// in its LDS too (up to 64 workgroups of 32,768 vertices).  A round takes every near vertex: it relaxes the owned targets of
-// its out-edges, which join the next near list or the far one, and sends the
-// others (vertex, distance) to their owners.  Wave 0 then exchanges records
-// with the other workgroups (words that carry the round's tag; the first
-// message of each pair inside, more in a box), while the other waves load the
-// next near vertices' rows and weights.  Once no workgroup has a near vertex,
-// a second exchange finds the smallest far distance, the limit moves past its
-// bucket, and each workgroup splits its far list.
+// in its LDS too (up to 64 workgroups of 32,704 vertices).  A round takes every
+// near vertex: it relaxes the owned targets of its out-edges, which join the
+// next near list or the far one, and sends the others (vertex, distance) to
+// their owners.  Wave 0 then exchanges records with the other workgroups (words
+// that carry the round's tag; the first message of each pair inside, more in a
+// box), while the other waves load the next near vertices' rows and weights.
+// Once no workgroup has a near vertex, a second exchange finds the smallest far
+// distance, the limit moves past its bucket, and each workgroup splits its far
+// list.
 //
 // A round's near vertices read their distance after leaving the list, so one
 // improved again later in the round is queued again.  Messages are path
