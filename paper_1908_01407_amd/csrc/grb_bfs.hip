@@ -722,7 +722,7 @@ __global__ __launch_bounds__(kBlock) void k_bfs_level(BfsArgs a) {
   // add for count and degree sum.  With one thread reading, and clearing, all of
   // them and two adds, single runs from three sources took 75, 60 and 70 us on
   // RMAT-14 (71, 56 and 67 so) and 184, 187 and 217 on RMAT-22 (175, 177 and
-  // 210); repeated, the two differ by no more than the runs of one (7 % and 1 %).
+  // 210); on other cards the difference lay within that of two runs of one form.
   static_assert(kCntSlots == 128 && 64 % kCntFields == 0, "two stripes a lane");
   if (threadIdx.x < 64) {
     const int ln = threadIdx.x;
@@ -905,8 +905,9 @@ __global__ __launch_bounds__(kBlock) void k_bfs_start(BfsArgs a, int32_t source,
 // VIS: vertices whose visited bits it holds.  Beside other streams' kernels a
 // workgroup becomes resident the later the more LDS it asks for, so small graphs
 // have a form of 45 KB (three PageRanks of 64M entries, 700 x 700 grid, 8
-// workgroups: 18 to 97 ms with 135 KB each, 5 to 58 so; alone 2.50 ms both).  A
-// form for 377,000 vertices made the 3000 x 3000 grid's levels 1.3 % longer.
+// workgroups: 18 to 97 ms with 135 KB each, 5 to 58 so; alone 2.50 ms both, one
+// workgroup's searches on small grids 0 to 1.3 % longer).  A form for 377,000
+// vertices made the 3000 x 3000 grid's levels 1.3 % longer.
 template <int VIS>
 struct OwnShared {
   static constexpr int kVis = VIS;

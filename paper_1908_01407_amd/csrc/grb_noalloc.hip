@@ -6,12 +6,13 @@
 // The array holds the BFS workspace of graphs up to 2^24 vertices (visited
 // and three frontier bitmaps of n / 8 bytes each, the control block, level
 // records, and the records and boxes of the device-side level loop): 9 MiB,
-// held on every GPU the library runs on until the process ends.  Its device address is looked up once per device
-// (hipGetSymbolAddress, with that device current) on the first call there;
-// in host code the array's own name is not a device address.  Every call on
-// one GPU uses that GPU's array: calls that overlap on one GPU race (one
-// stream at a time).  The BFS start kernel rewrites every word of the
-// workspace it reads, so nothing carries over from a previous call.
+// held on every GPU the library runs on until the process ends.  Its device
+// address is looked up once per device (hipGetSymbolAddress, with that device
+// current) on the first call there; in host code the array's own name is not
+// a device address.  Every call on one GPU uses that GPU's array: calls that
+// overlap on one GPU race (one stream at a time).  The BFS start kernel
+// rewrites every word of the workspace it reads, so nothing carries over from
+// a previous call.
 #include <hip/hip_runtime.h>
 
 #include <mutex>
